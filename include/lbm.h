@@ -262,17 +262,24 @@ int32_t lbm_get_tile_rows(const struct lbm_ctx *c);
  * two-step tile; otherwise the two-step kernel applies the boundary rule in both steps (its last
  * tiles sit against the far walls).  Remaining steps run in shorter launches.  Results do not
  * depend on it (bit for bit).  With 3, a graph replay covers the largest multiple of 6 steps in the
- * graph chunk.  lbm_get_steps_per_launch returns the count in effect (0 for a NULL context). */
+ * graph chunk.  lbm_get_steps_per_launch returns the count in effect (0 for a NULL context).
+ * While every launch choice is the default (this one, cache policy, tile, strip width, tile rows),
+ * lattices of up to about 400^2 nodes take the region launch instead: work-groups of one thread per
+ * node advance small square regions by 3 to 6 steps, whatever the lattice leaves at most one
+ * region per compute unit for (bit for bit the same results; not with FP16 storage and walls
+ * through the nodes).  lbm_get_region_steps returns its steps per launch, 0 where the launches
+ * above run (and for a NULL context). */
 lbm_status lbm_set_steps_per_launch(struct lbm_ctx *c, int32_t n);
+int32_t lbm_get_region_steps(const struct lbm_ctx *c);
 int32_t lbm_get_steps_per_launch(const struct lbm_ctx *c);
 
 /* Times every supported launch shape, cache policy and steps-per-launch count on this
  * context for `steps` steps each (HIP events), the multi-step launches also with their tiles
  * row by row, in strips of 4 and 8 tiles and of one strip per XCD band, and the FP32 three-step
  * and FP16 two-step launches on
- * both their tiles,
- * keeps the fastest (read the choices with lbm_get_cache_policy, lbm_get_steps_per_launch,
- * lbm_get_strip_width, lbm_get_tile_rows),
+ * both their tiles, and the defaults where they are the region launch,
+ * keeps the fastest (read the choices with lbm_get_region_steps, and where that is 0 with
+ * lbm_get_cache_policy, lbm_get_steps_per_launch, lbm_get_strip_width, lbm_get_tile_rows),
  * restores the state it started from, and reports the tile and its time per step.
  * Synchronises. */
 lbm_status lbm_autotune(struct lbm_ctx *c, int32_t steps, int32_t *tile_x, int32_t *tile_y,

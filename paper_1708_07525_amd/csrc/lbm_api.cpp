@@ -35,6 +35,7 @@ using namespace lbmk;
 namespace {
 
 constexpr int kGraphChunk = 64;     // default steps per captured graph in lbm_step (even)
+constexpr int kRegionTiles = 256;   // regions of a region launch: one per CU
 constexpr double kCs2 = 1.0 / 3.0;  // D2Q9 sound speed squared
 
 struct DevBuf {
@@ -110,6 +111,7 @@ struct lbm_ctx {
   int64_t step = 0;
   int64_t snap_step = 0;
   Tile tile{256, 1};
+  bool tile_set = false;     // lbm_set_tile chose the tile (else default_tile)
   int cache_policy = -1;     // CP_* or -1: chosen by the bytes a step touches
   int strip = -1;            // tile order of the multi-step launches (strip width), -1: default_strip
   int tile_rows = 0;         // rows of the FP32 three-step / FP16 two-step tile, 0: default_rows
@@ -124,7 +126,7 @@ struct lbm_ctx {
   int graph_cur = -1;
   Tile graph_tile{0, 0};
   int graph_cp = -1;
-  int graph_d4 = -1, graph_spl = 0, graph_sw = -1, graph_rows = 0;
+  int graph_d4 = -1, graph_spl = 0, graph_sw = -1, graph_rows = 0, graph_side = 0;
   int graph_chunk = kGraphChunk;   // 0: plain launches only
 
   void *pop(int i) const { return base + (i ? lay.off_pop1 : lay.off_pop0); }
@@ -770,9 +772,62 @@ static int ctx_strip(const lbm_ctx *c) {
   return default_strip(c->prec, c->p.nx, c->p.ny, spl, spl == 3 ? rows3_of(c) : rows2_of(c));
 }
 
+// The region launch of small lattices (launch_region): region side and steps per launch, {0, 0} where
+// the tiled launches are faster.  A launch costs some 5 us whatever it does (its start, the gap to
+// the next, first loads, stores), a step 0.9-2 us while every CU holds at most one region of one
+// node per thread; so the steps per launch are the most that still leave at most one region per CU,
+// on regions of 16^2 nodes (four waves, one per SIMD) up to about 128^2 nodes, else of 22^2.
+// Measured (us per step, region against the tiled launches; FP32 / FP64 / FP16 storage): 64^2
+// 1.56 / 1.92 / 1.67 (16, 6 steps) against 3.41 / 3.95 / 3.69; 100 x 200 1.96 / 2.38 / 1.97 (16, 4)
+// against 3.37 / 5.74 / 3.74; 200^2 2.21 / 2.95 / 2.46 (22, 5) against 3.49 / 4.23 / 3.85; 256^2
+// 2.49 / 3.31 / 2.62 (22, 4) against 3.50 / 4.35 / 3.84; walls through the nodes 100^2 3.43 / 4.02
+// (16, 5) against 7.50 / 8.93.  Above that several regions share a CU and three steps on regions
+// of 16^2 nodes still win up to 400^2 nodes (384^2 4.00 / 7.11 / 4.27 against 4.66 / 7.94 / 4.77; node
+// walls FP32 6.49 against 7.29, but FP64 13.8 against 10.2: not there); 512^2 loses.
+// Any launch choice of the caller (steps per launch, cache policy, tile, tile order, tile rows)
+// is kept: the region launch is part of the defaults only.
+struct RegionPlan {
+  int side, steps;
+};
+static RegionPlan ctx_region(const lbm_ctx *c) {
+  const bool nee = node_walls(&c->p);
+  const int nx = c->p.nx, ny = c->p.ny;
+  if (c->steps_per_launch != 0 || c->cache_policy >= 0 || c->strip >= 0 || c->tile_rows > 0 || c->tile_set) return {0, 0};
+  if (nee && c->prec == PREC_FP16S) return {0, 0};
+  auto tiles = [&](int side, int steps) -> int64_t {
+    const int t = side - 2 * (steps - 1);
+    return (int64_t)((nx + t - 1) / t) * ((ny + t - 1) / t);
+  };
+  // with walls through the nodes the tiles sit against the far walls: the lattice holds the tile of
+  // a single-step launch, the largest
+  auto fits = [&](int side) { return !nee || (nx >= side && ny >= side); };
+  if (fits(16))
+    for (int k = 6; k >= 4; --k)
+      if (tiles(16, k) <= kRegionTiles) return {16, k};
+  if (fits(22))
+    for (int k = 5; k >= 4; --k)
+      if (tiles(22, k) <= kRegionTiles) return {22, k};
+  if (fits(16) && (int64_t)nx * ny <= 160000 && !(nee && c->prec == PREC_FP64)) return {16, 3};
+  return {0, 0};
+}
+
 // n steps with plain launches: three or two steps per launch as ctx_spl allows, the remainder
-// in shorter launches
+// in shorter launches; on small lattices region launches, the steps spread evenly over them
 static lbm_status step_plain(lbm_ctx *c, int64_t n) {
+  const RegionPlan rg = ctx_region(c);
+  if (rg.side) {
+    while (n > 0) {
+      const int64_t launches = (n + rg.steps - 1) / rg.steps;
+      const int k = (int)((n + launches - 1) / launches);
+      set_parity(c, c->cur);
+      int e = launch_region(c->prec, c->desc(), c->desc_dev(c->cur, c->d4cur), 0, k, rg.side, c->stream);
+      if (e) return hip_fail(c, (hipError_t)e, "region kernel launch");
+      c->cur ^= 1;
+      c->d4cur ^= 1;
+      n -= k;
+    }
+    return LBM_OK;
+  }
   const int cp = ctx_policy(c);
   const int spl = ctx_spl(c);
   const int sw = ctx_strip(c), rows2 = rows2_of(c), rows3 = rows3_of(c);
@@ -802,8 +857,17 @@ static lbm_status step_plain(lbm_ctx *c, int64_t n) {
 // population and the field buffer, a one-step launch the population buffer only; a replay
 // must flip each an even number of times, so that it ends on the buffers it started from:
 // three steps per launch replay the largest multiple of 6 steps in graph_chunk, two steps per
-// launch the whole chunk when it is a multiple of 4; otherwise one step per launch.
-static void graph_plan(const lbm_ctx *c, int *spl, int *steps) {
+// launch the whole chunk when it is a multiple of 4; otherwise one step per launch.  Region
+// launches (side > 0) replay the largest multiple of two launches, of fewer steps each where the
+// chunk is shorter than that.
+static void graph_plan(const lbm_ctx *c, int *spl, int *steps, int *side) {
+  const RegionPlan rg = ctx_region(c);
+  *side = c->graph_chunk > 0 ? rg.side : 0;
+  if (*side) {
+    *spl = std::min(rg.steps, c->graph_chunk / 2);
+    *steps = c->graph_chunk / (2 * *spl) * (2 * *spl);
+    return;
+  }
   const int n = ctx_spl(c);
   if (n == 3 && c->graph_chunk >= 6) {
     *spl = 3;
@@ -821,9 +885,9 @@ static void graph_plan(const lbm_ctx *c, int *spl, int *steps) {
 static lbm_status ensure_graph(lbm_ctx *c) {
   const int cp = ctx_policy(c);
   const int sw = ctx_strip(c), rows = ctx_rows(c), rows2 = rows2_of(c), rows3 = rows3_of(c);
-  int spl = 1, gsteps = 0;
-  graph_plan(c, &spl, &gsteps);
-  if (c->graph && c->graph_cur == c->cur && c->graph_tile.tx == c->tile.tx && c->graph_tile.ty == c->tile.ty &&
+  int spl = 1, gsteps = 0, side = 0;
+  graph_plan(c, &spl, &gsteps, &side);
+  if (c->graph && c->graph_side == side && c->graph_cur == c->cur && c->graph_tile.tx == c->tile.tx && c->graph_tile.ty == c->tile.ty &&
       c->graph_cp == cp && c->graph_d4 == c->d4cur && c->graph_spl == spl && c->graph_sw == sw &&
       c->graph_rows == rows)
     return LBM_OK;
@@ -837,7 +901,10 @@ static lbm_status ensure_graph(lbm_ctx *c) {
     int cur = start, d4 = c->d4cur;
     for (int k = 0; k < gsteps / spl && e == hipSuccess; ++k) {
       set_parity(c, cur, d4);
-      if (spl == 3) {
+      if (side) {
+        e = (hipError_t)launch_region(c->prec, c->desc(), c->desc_dev(cur, d4), 0, spl, side, cs);
+        d4 ^= 1;
+      } else if (spl == 3) {
         e = (hipError_t)launch_step3(c->prec, c->desc(), c->desc_dev(cur, d4), cp, 0, sw, rows3, cs);
         d4 ^= 1;
       } else if (spl == 2) {
@@ -866,6 +933,7 @@ static lbm_status ensure_graph(lbm_ctx *c) {
   c->graph_spl = spl;
   c->graph_sw = sw;
   c->graph_rows = rows;
+  c->graph_side = side;
   return LBM_OK;
 }
 
@@ -878,8 +946,8 @@ LBM_API lbm_status lbm_step(lbm_ctx *c, int64_t nsteps) {
     return fail(c, LBM_ESTATE, "the fields hold a non-finite value (reported at step %lld); restart with "
                 "lbm_set_fields or restore a state with lbm_set_state", (long long)c->step);
   int64_t left = nsteps;
-  int gspl = 1, gsteps = 0;
-  graph_plan(c, &gspl, &gsteps);
+  int gspl = 1, gsteps = 0, gside = 0;
+  graph_plan(c, &gspl, &gsteps, &gside);
   if (c->graph_chunk > 0 && left >= gsteps) {
     lbm_status s = ensure_graph(c);
     if (s != LBM_OK) return s;
@@ -1070,10 +1138,12 @@ LBM_API lbm_status lbm_set_tile(lbm_ctx *c, int32_t tx, int32_t ty) {
   if (!c) return LBM_EINVAL;
   if (tx == 0 && ty == 0) {
     c->tile = default_tile(&c->p);
+    c->tile_set = false;
     return LBM_OK;
   }
   if (!tile_supported(tx, ty)) return fail(c, LBM_EINVAL, "unsupported tile %dx%d", tx, ty);
   c->tile = Tile{tx, ty};
+  c->tile_set = true;
   return LBM_OK;
 }
 
@@ -1135,6 +1205,8 @@ LBM_API lbm_status lbm_set_steps_per_launch(lbm_ctx *c, int32_t n) {
 
 LBM_API int32_t lbm_get_steps_per_launch(const lbm_ctx *c) { return c ? ctx_spl(c) : 0; }
 
+LBM_API int32_t lbm_get_region_steps(const lbm_ctx *c) { return c ? ctx_region(c).steps : 0; }
+
 LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int32_t *ty_out, double *ms_out) {
   Range range_("lbm_autotune");
   if (!c || steps < 2) return LBM_EINVAL;
@@ -1150,6 +1222,7 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
   const Tile tile0 = c->tile;
   const int cp0 = c->cache_policy, spl0 = c->steps_per_launch, d4cur0 = c->d4cur, sw0 = c->strip;
   const int rows0 = c->tile_rows;
+  const bool tset0 = c->tile_set;
   hipError_t e = hipMemcpyAsync(save, c->pop(cur0), pop_bytes, hipMemcpyDeviceToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(save + pop_bytes, c->d4(), d4_bytes, hipMemcpyDeviceToDevice, c->stream);
   if (e == hipSuccess)
@@ -1192,9 +1265,17 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
         for (int sw : sws) cands.push_back(Cand{3, cp, tile0.tx, tile0.ty, sw, rows});
     }
   const int nsteps = (steps + 5) / 6 * 6;   // whole launches of two and of three steps
+  // the defaults, where they are the region launch
+  c->tile_set = false;
+  c->cache_policy = c->strip = -1;
+  c->steps_per_launch = c->tile_rows = 0;
+  const Tile dt = default_tile(&c->p);
+  if (ctx_region(c).side) cands.push_back(Cand{0, -1, dt.tx, dt.ty, -1, 0});
+  bool best_set = tset0;
   for (const Cand &k : cands) {
     if (e != hipSuccess) break;
     c->tile = Tile{k.tx, k.ty};
+    c->tile_set = k.spl > 0;
     c->cache_policy = k.cp;
     c->steps_per_launch = k.spl;
     c->strip = k.sw;
@@ -1213,6 +1294,7 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
       best_spl = k.spl;
       best_sw = k.sw;
       best_rows = k.rows;
+      best_set = c->tile_set;
     }
   }
   // restore
@@ -1234,6 +1316,7 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
     c->steps_per_launch = spl0;
     c->strip = sw0;
     c->tile_rows = rows0;
+    c->tile_set = tset0;
     return hip_fail(c, e, "autotune");
   }
   c->tile = best_tile;
@@ -1241,6 +1324,7 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
   c->steps_per_launch = best_spl;
   c->strip = best_sw;
   c->tile_rows = best_rows;
+  c->tile_set = best_set;
   drop_graph(c);
   if (tx_out) *tx_out = best_tile.tx;
   if (ty_out) *ty_out = best_tile.ty;

@@ -93,6 +93,11 @@ int launch_step2(int prec, const void *desc, const void *ddev, int cp, int parit
 // storage, walls half a spacing outside; fields read from d4, written to d4b; sw as above;
 // rows: tile rows, 8 (64 x 8, FP64 32 x 8) or, FP32 only, 12 (64 x 12); else hipErrorInvalidValue
 int launch_step3(int prec, const void *desc, const void *ddev, int cp, int parity, int sw, int rows, void *stream);
+// `steps` time steps per launch on small lattices: a region of side x side nodes (16 or 22) per
+// work-group, whose inner (side - 2 (steps - 1))^2 nodes, at least 4^2, it stores; fields read from
+// d4, written to d4b; walls through the nodes with FP32 and FP64 storage on lattices that hold
+// one such tile (else hipErrorInvalidValue)
+int launch_region(int prec, const void *desc, const void *ddev, int parity, int steps, int side, void *stream);
 // range: device pointer to {first item, item count} of the group to step; parity bit 0
 // selects the population buffers, bit 1 the field buffer (d4b when set)
 int launch_step_batch(int prec, int cp, const void *descs, const Item *items, const int *range, int grid, int parity,

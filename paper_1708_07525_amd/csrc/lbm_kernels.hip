@@ -124,8 +124,8 @@ __device__ __forceinline__ void velocity_solve(R a, R b, R vx, R vy, R &ux, R &u
 // (rho0_s, T0_s, C0_s); only the fields (T - T0, C - C0 and the velocity) are formed in
 // physical units.  A power of two commutes with every rounding here, so the arithmetic is that
 // of physical units, scaled exactly, without a multiply per population.
-template <typename R, bool SC>
-__device__ __forceinline__ void collide(const Desc<R> &d, R phi, R inv_phi, R a, R b, R *fd, R *gd, R *hd,
+template <typename R, bool SC, typename D>
+__device__ __forceinline__ void collide(const D &d, R phi, R inv_phi, R a, R b, R *fd, R *gd, R *hd,
                                         R *prev) {
   const R half = R(0.5);
   // density, momentum and scalars (Eqs. 16, 17, 26), deviation form
@@ -511,8 +511,8 @@ __device__ __forceinline__ void pull_inner(const Desc<typename St<S>::R> &d, con
 }
 
 // rho - rho0, u, T - T0 and C - C0 of pre-collision populations (Eqs. 16-19, 26)
-template <typename R>
-__device__ __forceinline__ void node_fields(const Desc<R> &d, R phi, R a, R b, const R *fd, const R *gd, const R *hd,
+template <typename R, typename D>
+__device__ __forceinline__ void node_fields(const D &d, R phi, R a, R b, const R *fd, const R *gd, const R *hd,
                                             R &drho, R &ux, R &uy, R &dT, R &dC) {
   const R half = R(0.5);
   drho = fd[0] + (fd[1] + fd[2] + fd[3] + fd[4]) + (fd[5] + fd[6] + fd[7] + fd[8]);
@@ -535,8 +535,8 @@ __device__ __forceinline__ void node_fields(const Desc<R> &d, R phi, R a, R b, c
 
 // deviation-form equilibria: Eq. (20) minus w_i rho0; Eq. (28) (or the Model-A form) minus
 // its value at (T0, u = 0)
-template <typename R>
-__device__ __forceinline__ void feq_dev(const Desc<R> &d, R drho, R ux, R uy, R phi, R *e) {
+template <typename R, typename D>
+__device__ __forceinline__ void feq_dev(const D &d, R drho, R ux, R uy, R phi, R *e) {
   const int EX[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
   const int EY[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
   const R W[9] = {R(4.0 / 9), R(1.0 / 9), R(1.0 / 9), R(1.0 / 9), R(1.0 / 9),
@@ -549,8 +549,8 @@ __device__ __forceinline__ void feq_dev(const Desc<R> &d, R drho, R ux, R uy, R 
   }
 }
 
-template <typename R>
-__device__ __forceinline__ void seq_dev(const Desc<R> &d, R ds, R s, R ux, R uy, R e0, R cap, R *e) {
+template <typename R, typename D>
+__device__ __forceinline__ void seq_dev(const D &d, R ds, R s, R ux, R uy, R e0, R cap, R *e) {
   const R q = R(0.25) * d.varpi * cap * ds, hs = R(0.5) * s;
   e[0] = e0 * ds;
   e[1] = q + hs * ux;
@@ -560,9 +560,100 @@ __device__ __forceinline__ void seq_dev(const Desc<R> &d, R ds, R s, R ux, R uy,
 }
 
 template <typename R>
-__device__ __forceinline__ R boundary_scalar(int kind, R fixed, R beta, R amb, R sf, R sff) {
-  if (kind == SIDE_NEE_HOT || kind == SIDE_NEE_COLD) return fixed;
+__device__ __forceinline__ R boundary_scalar(R beta, R amb, R sf, R sff) {
   return (R(4) * sf - sff + R(2) * beta * amb) / (R(3) + R(2) * beta);
+}
+
+// What the rule of the boundary node (x, y) takes from its sides (bx / by mark a wall through the
+// node in x / y): the inward direction, the wall velocity, the fixed scalars or the Biot factors
+template <typename R>
+struct NeeRule {
+  int dx, dy;
+  bool fixed;
+  R ubx, uby, Tfix, Cfix, bT, bC;
+  __device__ __forceinline__ NeeRule(const Desc<R> &d, int x, int y, bool bx, bool by) {
+    dx = bx ? (x == 0 ? 1 : -1) : 0, dy = by ? (y == 0 ? 1 : -1) : 0;
+    const int sx = x == 0 ? LEFT : RIGHT, sy = y == 0 ? BOTTOM : TOP;
+    // per-side values are picked with selects from uniform registers: indexing the descriptor
+    // with a per-lane side would turn each into a memory round trip
+    auto pick = [](auto a0, auto a1, auto a2, auto a3, int k) { return k == 0 ? a0 : k == 1 ? a1 : k == 2 ? a2 : a3; };
+    const int k0 = d.kind[0], k1 = d.kind[1], k2 = d.kind[2], k3 = d.kind[3];
+    int side, kind;
+    ubx = R(0), uby = R(0);
+    if (bx && by) {
+      const int kx = pick(k0, k1, k2, k3, sx), ky = pick(k0, k1, k2, k3, sy);
+      auto holds = [](int k) { return k == SIDE_NEE_HOT || k == SIDE_NEE_COLD; };
+      side = holds(kx) ? sx : holds(ky) ? sy : kx == SIDE_NEE_ROBIN ? sx : ky == SIDE_NEE_ROBIN ? sy : sx;
+      kind = (holds(kx) || holds(ky) || kx == SIDE_NEE_ROBIN || ky == SIDE_NEE_ROBIN) ? pick(k0, k1, k2, k3, side)
+                                                                                      : SIDE_NEE_ADIABATIC;
+    } else {
+      side = bx ? sx : sy;
+      kind = pick(k0, k1, k2, k3, side);
+      const R uw = pick(d.uwall[0], d.uwall[1], d.uwall[2], d.uwall[3], side);
+      if (bx) uby = uw;
+      else ubx = uw;
+    }
+    fixed = kind == SIDE_NEE_HOT || kind == SIDE_NEE_COLD;
+    Tfix = pick(d.Tfix[0], d.Tfix[1], d.Tfix[2], d.Tfix[3], side);
+    Cfix = pick(d.Cfix[0], d.Cfix[1], d.Cfix[2], d.Cfix[3], side);
+    bT = kind == SIDE_NEE_ROBIN ? pick(d.betaT[0], d.betaT[1], d.betaT[2], d.betaT[3], side) : R(0);
+    bC = kind == SIDE_NEE_ROBIN ? pick(d.betaC[0], d.betaC[1], d.betaC[2], d.betaC[3], side) : R(0);
+  }
+};
+
+// The rule itself, in place: the pre-collision state of f (ff, gf, hf) becomes that of the boundary
+// node; g2, h2: the scalars of the second node inward; phib, phif, phiff: the three
+// porosities; af, bf: the porous coefficients of f
+template <typename S, typename D, typename R>
+__device__ __forceinline__ void nee_extrapolate(const D &d, const NeeRule<R> &w, R phib, R phif, R phiff, R af, R bf,
+                                                R *ff, R *gf, R *hf, R *g2, R *h2) {
+  if constexpr (kScaled<S>) {
+    // the rule works in physical units; FP16 pulls carry the pre-scale
+#pragma unroll
+    for (int i = 0; i < 9; ++i) ff[i] *= d.inv_scale;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      gf[i] *= d.inv_scale;
+      hf[i] *= d.inv_scale;
+      g2[i] *= d.inv_scale;
+      h2[i] *= d.inv_scale;
+    }
+  }
+  R drho, uxf, uyf, dTf, dCf;
+  node_fields<R>(d, phif, af, bf, ff, gf, hf, drho, uxf, uyf, dTf, dCf);
+  R dTb = w.Tfix, dCb = w.Cfix;
+  if (!w.fixed) {
+    const R dTff = (g2[0] + g2[1] + g2[2] + g2[3] + g2[4]) * d.inv_sigma;
+    const R dCff = (h2[0] + h2[1] + h2[2] + h2[3] + h2[4]) / phiff;
+    // Eq. (36) is linear, so it holds for the deviations T - T0 as well
+    dTb = boundary_scalar(w.bT, d.Tinf, dTf, dTff);
+    dCb = boundary_scalar(w.bC, d.Cinf, dCf, dCff);
+  }
+  R eb[9], ef[9];
+  feq_dev<R>(d, drho, w.ubx, w.uby, phib, eb);      // Eq. (33): rho of f, velocity of the wall
+  feq_dev<R>(d, drho, uxf, uyf, phif, ef);
+#pragma unroll
+  for (int i = 0; i < 9; ++i) ff[i] = eb[i] + (ff[i] - ef[i]);
+  R sb[5], sf[5];
+  seq_dev<R>(d, dTb, d.T0 + dTb, w.ubx, w.uby, d.kg0, d.capT, sb);   // Eq. (34)
+  seq_dev<R>(d, dTf, d.T0 + dTf, uxf, uyf, d.kg0, d.capT, sf);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) gf[i] = sb[i] + (gf[i] - sf[i]);
+  const R h0b = d.model == 0 ? phib - d.varpi : (R(1) - d.varpi) * phib;
+  const R h0f = d.model == 0 ? phif - d.varpi : (R(1) - d.varpi) * phif;
+  seq_dev<R>(d, dCb, d.C0 + dCb, w.ubx, w.uby, h0b, d.model == 0 ? R(1) : phib, sb);   // Eq. (35)
+  seq_dev<R>(d, dCf, d.C0 + dCf, uxf, uyf, h0f, d.model == 0 ? R(1) : phif, sf);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) hf[i] = sb[i] + (hf[i] - sf[i]);
+  if constexpr (kScaled<S>) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) ff[i] *= d.scale;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      gf[i] *= d.scale;
+      hf[i] *= d.scale;
+    }
+  }
 }
 
 // The boundary update of node (x, y): bx / by mark a wall through the node in x / y.  Every
@@ -577,51 +668,15 @@ __device__ __forceinline__ void nee_boundary(const Desc<typename St<S>::R> &d, c
                                           typename St<S>::R *hd, typename St<S>::R *prev, typename St<S>::R &phib,
                                           Pull pull) {
   using R = typename St<S>::R;
-  const int dx = bx ? (x == 0 ? 1 : -1) : 0, dy = by ? (y == 0 ? 1 : -1) : 0;
-  const int sx = x == 0 ? LEFT : RIGHT, sy = y == 0 ? BOTTOM : TOP;
-  // per-side values are picked with selects from uniform registers: indexing the descriptor
-  // with a per-lane side would turn each into a memory round trip
-  auto pick = [](auto a0, auto a1, auto a2, auto a3, int k) { return k == 0 ? a0 : k == 1 ? a1 : k == 2 ? a2 : a3; };
-  const int k0 = d.kind[0], k1 = d.kind[1], k2 = d.kind[2], k3 = d.kind[3];
-  int side, kind;
-  R ubx = R(0), uby = R(0);
-  if (bx && by) {
-    const int kx = pick(k0, k1, k2, k3, sx), ky = pick(k0, k1, k2, k3, sy);
-    auto fixed = [](int k) { return k == SIDE_NEE_HOT || k == SIDE_NEE_COLD; };
-    side = fixed(kx) ? sx : fixed(ky) ? sy : kx == SIDE_NEE_ROBIN ? sx : ky == SIDE_NEE_ROBIN ? sy : sx;
-    kind = (fixed(kx) || fixed(ky) || kx == SIDE_NEE_ROBIN || ky == SIDE_NEE_ROBIN) ? pick(k0, k1, k2, k3, side)
-                                                                                    : SIDE_NEE_ADIABATIC;
-  } else {
-    side = bx ? sx : sy;
-    kind = pick(k0, k1, k2, k3, side);
-    const R uw = pick(d.uwall[0], d.uwall[1], d.uwall[2], d.uwall[3], side);
-    if (bx) uby = uw;
-    else ubx = uw;
-  }
-  const bool fixed_scalars = kind == SIDE_NEE_HOT || kind == SIDE_NEE_COLD;
+  const NeeRule<R> w(d, x, y, bx, by);
   // loads: pre-collision state of f and ff (the pulls of this step), porosities, and the
   // previous-step fields of the boundary node
-  const int xf = x + dx, yf = y + dy, xff = x + 2 * dx, yff = y + 2 * dy;
+  const int xf = x + w.dx, yf = y + w.dy, xff = x + 2 * w.dx, yff = y + 2 * w.dy;
   const uint32_t RS = sizeof(R), PR = (uint32_t)d.plane * RS;
   const uint32_t cb = ((uint32_t)y * d.pitch + x) * RS;
-  R ff[9], gf[5], hf[5], f2[9], g2[5], h2[5];
-  pull(xf, yf, ff, gf, hf);
+  R f2[9], g2[5], h2[5];
+  pull(xf, yf, fd, gd, hd);
   pull(xff, yff, f2, g2, h2);
-  if constexpr (kScaled<S>) {
-    // the rule works in physical units; FP16 pulls carry the pre-scale
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      ff[i] *= d.inv_scale;
-      f2[i] *= d.inv_scale;
-    }
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      gf[i] *= d.inv_scale;
-      hf[i] *= d.inv_scale;
-      g2[i] *= d.inv_scale;
-      h2[i] *= d.inv_scale;
-    }
-  }
   R phif = d.phi_u, phiff = d.phi_u;
   phib = d.phi_u;
   if (d.phi_field) {
@@ -635,61 +690,20 @@ __device__ __forceinline__ void nee_boundary(const Desc<typename St<S>::R> &d, c
   }
   R af, bf, ipf;
   porous_coeffs(d, phif, af, bf, ipf);
-  R drho, uxf, uyf, dTf, dCf;
-  node_fields(d, phif, af, bf, ff, gf, hf, drho, uxf, uyf, dTf, dCf);
-  R dTb = pick(d.Tfix[0], d.Tfix[1], d.Tfix[2], d.Tfix[3], side);
-  R dCb = pick(d.Cfix[0], d.Cfix[1], d.Cfix[2], d.Cfix[3], side);
-  if (!fixed_scalars) {
-    const R dTff = (g2[0] + g2[1] + g2[2] + g2[3] + g2[4]) * d.inv_sigma;
-    const R dCff = (h2[0] + h2[1] + h2[2] + h2[3] + h2[4]) / phiff;
-    const R bT = kind == SIDE_NEE_ROBIN ? pick(d.betaT[0], d.betaT[1], d.betaT[2], d.betaT[3], side) : R(0);
-    const R bC = kind == SIDE_NEE_ROBIN ? pick(d.betaC[0], d.betaC[1], d.betaC[2], d.betaC[3], side) : R(0);
-    // Eq. (36) is linear, so it holds for the deviations T - T0 as well
-    dTb = boundary_scalar(kind, dTb, bT, d.Tinf, dTf, dTff);
-    dCb = boundary_scalar(kind, dCb, bC, d.Cinf, dCf, dCff);
-  }
-  R eb[9], ef[9];
-  feq_dev(d, drho, ubx, uby, phib, eb);      // Eq. (33): rho of f, velocity of the wall
-  feq_dev(d, drho, uxf, uyf, phif, ef);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) fd[i] = eb[i] + (ff[i] - ef[i]);
-  R sb[5], sf[5];
-  seq_dev(d, dTb, d.T0 + dTb, ubx, uby, d.kg0, d.capT, sb);   // Eq. (34)
-  seq_dev(d, dTf, d.T0 + dTf, uxf, uyf, d.kg0, d.capT, sf);
-#pragma unroll
-  for (int i = 0; i < 5; ++i) gd[i] = sb[i] + (gf[i] - sf[i]);
-  const R h0b = d.model == 0 ? phib - d.varpi : (R(1) - d.varpi) * phib;
-  const R h0f = d.model == 0 ? phif - d.varpi : (R(1) - d.varpi) * phif;
-  seq_dev(d, dCb, d.C0 + dCb, ubx, uby, h0b, d.model == 0 ? R(1) : phib, sb);   // Eq. (35)
-  seq_dev(d, dCf, d.C0 + dCf, uxf, uyf, h0f, d.model == 0 ? R(1) : phif, sf);
-#pragma unroll
-  for (int i = 0; i < 5; ++i) hd[i] = sb[i] + (hf[i] - sf[i]);
-  if constexpr (kScaled<S>) {
-#pragma unroll
-    for (int i = 0; i < 9; ++i) fd[i] *= d.scale;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      gd[i] *= d.scale;
-      hd[i] *= d.scale;
-    }
-  }
+  nee_extrapolate<S>(d, w, phib, phif, phiff, af, bf, fd, gd, hd, g2, h2);
 }
 
-// Second half of a node update: collision (moment space) with the previous-step fields
-// `prev` and the porous coefficients a, b (Darcy and Forchheimer terms of Eq. 5), then the
-// stores.
+// The stores of a node update: post-collision populations, rounded to the storage type, and the
+// fields of the new level
 template <typename S, int CP>
-__device__ __forceinline__ void collide_store_ab(const Desc<typename St<S>::R> &d, const StepRes &rs, uint32_t c,
-                                                 uint32_t step, typename St<S>::R phi, typename St<S>::R inv_phi,
-                                                 typename St<S>::R a, typename St<S>::R b, typename St<S>::R *fd,
-                                                 typename St<S>::R *gd, typename St<S>::R *hd,
-                                                 typename St<S>::R *prev) {
+__device__ __forceinline__ void store_node(const Desc<typename St<S>::R> &d, const StepRes &rs, uint32_t c,
+                                           uint32_t step, const typename St<S>::R *fd, const typename St<S>::R *gd,
+                                           const typename St<S>::R *hd, const typename St<S>::R *prev) {
   using R = typename St<S>::R;
   constexpr uint32_t ES = sizeof(S), RS = sizeof(R);
   const uint32_t PB = (uint32_t)d.plane * ES;
   const uint32_t PR = (uint32_t)d.plane * RS;
   const uint32_t cr = c * RS;
-  collide<R, kScaled<S>>(d, phi, inv_phi, a, b, fd, gd, hd, prev);
   const R sc = d.scale;
   const uint32_t co = c * ES;
   Dither dz(c, step);
@@ -704,6 +718,19 @@ __device__ __forceinline__ void collide_store_ab(const Desc<typename St<S>::R> &
   FIO::st(prev[1], rs.d4, cr, PR);
   FIO::st(prev[2], rs.d4, cr, 2 * PR);
   FIO::st(prev[3], rs.d4, cr, 3 * PR);
+}
+
+// Second half of a node update: collision (moment space) with the previous-step fields
+// `prev` and the porous coefficients a, b (Darcy and Forchheimer terms of Eq. 5), then the
+// stores.
+template <typename S, int CP>
+__device__ __forceinline__ void collide_store_ab(const Desc<typename St<S>::R> &d, const StepRes &rs, uint32_t c,
+                                                 uint32_t step, typename St<S>::R phi, typename St<S>::R inv_phi,
+                                                 typename St<S>::R a, typename St<S>::R b, typename St<S>::R *fd,
+                                                 typename St<S>::R *gd, typename St<S>::R *hd,
+                                                 typename St<S>::R *prev) {
+  collide<typename St<S>::R, kScaled<S>>(d, phi, inv_phi, a, b, fd, gd, hd, prev);
+  store_node<S, CP>(d, rs, c, step, fd, gd, hd, prev);
 }
 
 // as collide_store_ab, with the porous coefficients of Eq. (7) computed from phi
@@ -769,10 +796,11 @@ __device__ __forceinline__ void wall_rules(const Desc<R> &d, bool okxm, bool okx
 }
 
 // Pull streaming of node (x, y) from the post-collision populations of the previous level
-// in global memory (Eq. 11), with the wall rules.  INTERIOR: every upstream node lies inside
-// the domain (no wall link, no wrap).
+// in global memory (Eq. 11), before the wall rules: a link that crosses a wall pulls the opposite
+// population of this node.  INTERIOR: every upstream node lies inside the domain (no wall link,
+// no wrap).
 template <typename S, int CP, bool INTERIOR>
-__device__ __forceinline__ void gather_global(const Desc<typename St<S>::R> &d, const StepRes &rs, int x, int y,
+__device__ __forceinline__ void gather_pulls(const Desc<typename St<S>::R> &d, const StepRes &rs, int x, int y,
                                               typename St<S>::R *fd, typename St<S>::R *gd,
                                               typename St<S>::R *hd) {
   using R = typename St<S>::R;
@@ -830,7 +858,19 @@ __device__ __forceinline__ void gather_global(const Desc<typename St<S>::R> &d, 
   hd[3] = to_real<S>(IO::ld(rs.src, o3, 14 * PB + plane(3, 1)), is);
   gd[4] = to_real<S>(IO::ld(rs.src, o4, 9 * PB + plane(4, 2)), is);
   hd[4] = to_real<S>(IO::ld(rs.src, o4, 14 * PB + plane(4, 2)), is);
-  if (!INTERIOR && !(okxm & okxp & okym & okyp)) wall_rules(d, okxm, okxp, okym, okyp, fd, gd, hd);
+}
+
+// gather_pulls with the wall rules
+template <typename S, int CP, bool INTERIOR>
+__device__ __forceinline__ void gather_global(const Desc<typename St<S>::R> &d, const StepRes &rs, int x, int y,
+                                              typename St<S>::R *fd, typename St<S>::R *gd,
+                                              typename St<S>::R *hd) {
+  gather_pulls<S, CP, INTERIOR>(d, rs, x, y, fd, gd, hd);
+  if (!INTERIOR) {
+    const bool okxm = (x > 0) | d.perx, okxp = (x < d.nx - 1) | d.perx;
+    const bool okym = (y > 0) | d.pery, okyp = (y < d.ny - 1) | d.pery;
+    if (!(okxm & okxp & okym & okyp)) wall_rules(d, okxm, okxp, okym, okyp, fd, gd, hd);
+  }
 }
 
 template <typename S, int CP, bool INTERIOR>
@@ -1429,6 +1469,271 @@ __global__ void __launch_bounds__(TS::THREADS, TS::MIN_WAVES_PER_EU) step3_kerne
   three_step_tile<S, CP, TS>(d, tx * TS::W, ty * TS::H, parity, lpop);
 }
 
+// ---------------------------------------------------------------- small lattices: a region per work-group
+// The constants of the collision, held in vector registers: read from the descriptor as they are
+// needed they cost a wait for the scalar cache each, which a kernel with one or two waves per SIMD
+// does not hide.
+template <typename R>
+struct Rates {
+  R inv_sigma, scale, inv_scale, gx, gy, gbT, gbC, rho0_s, inv_rho0_s, T0_s, C0_s;
+  R s_e, s_eps, s_j, s_q, s_v, k_e, k_eps, k_j, k_q, k_v;
+  R z_a, z_e, z_eps, e_D, e_e, e_eps, k_za, k_eD, kg3, kh3_u, c5v;
+  int phi_field, model;
+  __device__ __forceinline__ explicit Rates(const Desc<R> &d)
+      : inv_sigma(d.inv_sigma), scale(d.scale), inv_scale(d.inv_scale), gx(d.gx), gy(d.gy), gbT(d.gbT), gbC(d.gbC),
+        rho0_s(d.rho0_s), inv_rho0_s(d.inv_rho0_s), T0_s(d.T0_s), C0_s(d.C0_s), s_e(d.s_e), s_eps(d.s_eps),
+        s_j(d.s_j), s_q(d.s_q), s_v(d.s_v), k_e(d.k_e), k_eps(d.k_eps), k_j(d.k_j), k_q(d.k_q), k_v(d.k_v),
+        z_a(d.z_a), z_e(d.z_e), z_eps(d.z_eps), e_D(d.e_D), e_e(d.e_e), e_eps(d.e_eps), k_za(d.k_za), k_eD(d.k_eD),
+        kg3(d.kg3), kh3_u(d.kh3_u), c5v(d.c5v), phi_field(d.phi_field), model(d.model) {
+    R *v[] = {&inv_sigma, &scale, &inv_scale, &gx, &gy, &gbT, &gbC, &rho0_s, &inv_rho0_s, &T0_s, &C0_s,
+              &s_e, &s_eps, &s_j, &s_q, &s_v, &k_e, &k_eps, &k_j, &k_q, &k_v,
+              &z_a, &z_e, &z_eps, &e_D, &e_e, &e_eps, &k_za, &k_eD, &kg3, &kh3_u, &c5v};
+#pragma unroll
+    for (R *p : v) asm("" : "+v"(*p));
+  }
+};
+
+// What the walls beside a node do to its pulls (wall_rules), in registers: the wall terms of the
+// diagonal links and the fixed values of the x and the y wall it lies at (a node has at most one
+// of each: a lattice has at least three nodes across)
+template <typename R>
+struct NodeWalls {
+  bool okxm, okxp, okym, okyp, ok5, ok6, ok7, ok8, fix1, fix2, fix3, fix4;
+  R u5, u6, u7, u8, Tx, Cx, Ty, Cy;
+  __device__ __forceinline__ NodeWalls(const Desc<R> &d, int x, int y) {
+    okxm = (x > 0) | d.perx, okxp = (x < d.nx - 1) | d.perx;
+    okym = (y > 0) | d.pery, okyp = (y < d.ny - 1) | d.pery;
+    ok5 = okxm & okym, ok6 = okxp & okym, ok7 = okxp & okyp, ok8 = okxm & okyp;
+    const R uB = d.uw[BOTTOM], uT = d.uw[TOP], uL = d.uw[LEFT], uR = d.uw[RIGHT];
+    u5 = !okym ? uB : uL;
+    u6 = !okym ? -uB : uR;
+    u7 = !okyp ? -uT : -uR;
+    u8 = !okyp ? uT : -uL;
+    fix1 = !okxm && d.kind[LEFT] != SIDE_ADIABATIC;
+    fix3 = !okxp && d.kind[RIGHT] != SIDE_ADIABATIC;
+    fix2 = !okym && d.kind[BOTTOM] != SIDE_ADIABATIC;
+    fix4 = !okyp && d.kind[TOP] != SIDE_ADIABATIC;
+    Tx = !okxm ? d.wT[LEFT] : d.wT[RIGHT];
+    Cx = !okxm ? d.wC[LEFT] : d.wC[RIGHT];
+    Ty = !okym ? d.wT[BOTTOM] : d.wT[TOP];
+    Cy = !okym ? d.wC[BOTTOM] : d.wC[TOP];
+    R *v[] = {&u5, &u6, &u7, &u8, &Tx, &Cx, &Ty, &Cy};
+#pragma unroll
+    for (R *p : v) asm("" : "+v"(*p));
+  }
+  __device__ __forceinline__ void apply(R *fd, R *gd, R *hd) const {
+    if (okxm & okxp & okym & okyp) return;
+    // (opaque in each step, so that the products stay fused with the additions: see region_kernel)
+    R v5 = u5, v6 = u6, v7 = u7, v8 = u8;
+    asm volatile("" : "+v"(v5), "+v"(v6), "+v"(v7), "+v"(v8));
+    const R w5 = R(1.0 / 36.0);
+    if (!ok5) fd[5] += w5 * v5;
+    if (!ok6) fd[6] += w5 * v6;
+    if (!ok7) fd[7] += w5 * v7;
+    if (!ok8) fd[8] += w5 * v8;
+    gd[1] = fix1 ? Tx - gd[1] : gd[1];
+    hd[1] = fix1 ? Cx - hd[1] : hd[1];
+    gd[2] = fix2 ? Ty - gd[2] : gd[2];
+    hd[2] = fix2 ? Cy - hd[2] : hd[2];
+    gd[3] = fix3 ? Tx - gd[3] : gd[3];
+    hd[3] = fix3 ? Cx - hd[3] : hd[3];
+    gd[4] = fix4 ? Ty - gd[4] : gd[4];
+    hd[4] = fix4 ? Cy - hd[4] : hd[4];
+  }
+};
+
+// A lattice of a few ten thousand nodes leaves the chip idle: what a launch costs is its own
+// latency (start, first loads, stores), and what a step costs is the latency of one collision.
+// So a work-group takes a square region of RW x RW nodes, one node per thread, and advances it
+// `steps` steps in LDS; the nodes that are then still right are the (RW - 2 (steps - 1))^2 tile in
+// its middle, which it stores.  The nodes of a region are updated in every step, the outer ones
+// from neighbours the region does not hold: a step spoils one more ring of nodes, never a node
+// of the tile; waves whose rows are all spoilt stop.  All steps run through one copy of the
+// collision, and steps is a launch argument: the host trades longer launches against smaller
+// tiles.
+// A thread keeps its node's rest populations, fields and porous coefficients in registers, and
+// its own moving populations for the walls (half-way bounce-back); LDS holds two copies of
+// the 16 moving populations, written in turn, so that a step takes one barrier.
+// NEE: walls through the boundary nodes, as in two_step_tile (the last tiles sit against the
+// far walls, FP32 and FP64 storage); a boundary node pulls whole neighbours, so LDS holds the
+// rest populations too.
+template <int RW_>
+struct Region {
+  static constexpr int RW = RW_, NODES = RW * RW, THREADS = (NODES + 63) / 64 * 64;
+  static constexpr int PAD = RW + 1;       // the outermost nodes pull from the padding
+  static constexpr int SLOTS = NODES + 2 * PAD;
+};
+
+template <typename S, bool NEE, typename RG>
+__global__ void __launch_bounds__(RG::THREADS, RG::THREADS / 256)
+    region_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int ntx, uint32_t inv_ntx, int parity, int steps) {
+  using R = typename St<S>::R;
+  using FIO = FieldIO<S, CP_RESIDENT>;
+  constexpr int RW = RG::RW, PAD = RG::PAD;
+  constexpr uint32_t RS = sizeof(R);
+  __shared__ S lds[2][NEE ? NPOP : NPOP - 3][RG::SLOTS];
+  const Desc<R> &d = *dp;
+  const int nx = d.nx, ny = d.ny, pitch = d.pitch;
+  const uint32_t PR = (uint32_t)d.plane * RS;
+  const int cur = (d.base_parity ^ parity) & 1;
+  StepRes rs = step_resources<S>(d, cur);
+  rs.d4 = make_rsrc((parity & 1) ? d.d4b : d.d4, ND4 * PR);
+  const rsrc_t fwrite = make_rsrc((parity & 1) ? d.d4 : d.d4b, ND4 * PR);
+  const uint32_t step = d.counter[cur];
+  const int edge = steps - 1, tile = RW - 2 * edge;
+  // tile index over ntx by a multiplication with ceil(2^32 / ntx), exact for tiles x ntx < 2^32; 0: ntx = 1
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int by = inv_ntx ? (int)__umulhi((uint32_t)b, inv_ntx) : b, bx = b - by * ntx;
+  int x0 = bx * tile, y0 = by * tile;
+  if ((x0 | y0) == 0 && threadIdx.x == 0) d.counter[cur ^ 1] = step + (uint32_t)steps;
+  if (NEE) {
+    x0 = min(x0, nx - tile);
+    y0 = min(y0, ny - tile);
+  }
+  const int t = min((int)threadIdx.x, RG::NODES - 1);          // the last threads repeat the last node
+  const int lx = t % RW, ly = t / RW;
+  const int r = PAD + t;
+  const bool perx = d.perx != 0, pery = d.pery != 0;
+  // the domain node, wrapped across periodic sides (more than once on the smallest lattices)
+  const int xv = x0 - edge + lx, yv = y0 - edge + ly;
+  int X = xv, Y = yv;
+  if (perx) {
+    X %= nx;
+    X = X < 0 ? X + nx : X;
+  }
+  if (pery) {
+    Y %= ny;
+    Y = Y < 0 ? Y + ny : Y;
+  }
+  const bool live = X >= 0 && X < nx && Y >= 0 && Y < ny;      // else beyond a wall: never pulled from
+  const bool mine = (int)threadIdx.x < RG::NODES && lx >= edge && lx < edge + tile && ly >= edge &&
+                    ly < edge + tile && xv < nx && yv < ny;
+  const NodeWalls<R> w(d, X, Y);
+  const bool wx = NEE && !(w.okxm & w.okxp), wy = NEE && !(w.okym & w.okyp);
+  const uint32_t c = (uint32_t)Y * pitch + X;
+
+  R fd[9], gd[5], hd[5], prev[4], phi = d.phi_u, pa = R(0), pb = R(0), ip = R(0);
+  R phif = d.phi_u, phiff = d.phi_u, af = R(0), bf = R(0);     // of the nodes a boundary node is rebuilt from
+  const NeeRule<R> rule(d, X, Y, wx, wy);
+  if (live) {
+    // step one pulls from global memory
+    if (d.phi_field) phi = FIO::ld(rs.phi, c * RS, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) prev[k] = FIO::ld(rs.d4, c * RS, (uint32_t)k * PR);
+    if (NEE && (wx || wy)) {
+      R f2[9], g2[5], h2[5], ipf;
+      pull_inner<S, CP_RESIDENT>(d, rs, X + rule.dx, Y + rule.dy, fd, gd, hd);
+      pull_inner<S, CP_RESIDENT>(d, rs, X + 2 * rule.dx, Y + 2 * rule.dy, f2, g2, h2);
+      if (d.phi_field) {
+        phif = FIO::ld(rs.phi, ((uint32_t)(Y + rule.dy) * pitch + X + rule.dx) * RS, 0);
+        phiff = FIO::ld(rs.phi, ((uint32_t)(Y + 2 * rule.dy) * pitch + X + 2 * rule.dx) * RS, 0);
+      }
+      porous_coeffs(d, phif, af, bf, ipf);
+      nee_extrapolate<S>(d, rule, phi, phif, phiff, af, bf, fd, gd, hd, g2, h2);
+    } else {
+      gather_pulls<S, CP_RESIDENT, false>(d, rs, X, Y, fd, gd, hd);
+      if (!NEE) w.apply(fd, gd, hd);
+    }
+    porous_coeffs(d, phi, pa, pb, ip);
+  }
+  const Rates<R> q(d);
+  const R one = R(1);                      // the scale argument of to_real, which takes values as stored
+  // the wave's nodes that lie deepest in the region: it stops when a step no longer needs them
+  const int row0 = ((int)threadIdx.x & ~63) / RW, row1 = ((int)threadIdx.x | 63) / RW;
+  const int depth = __builtin_amdgcn_readfirstlane(row1 < RW / 2 ? row1 : row0 >= RW / 2 ? RW - 1 - row0 : RW / 2);
+  auto P = [](int i) { return NEE ? i : lp(i); };              // LDS plane of population i
+  bool active = live;
+  for (int s = 0;; ++s) {
+    // (opaque, so that no product of them is taken out of the loop: the compiler would no longer
+    // fuse it with the addition it feeds, and the result would differ from the other kernels')
+    asm volatile("" : "+v"(phi), "+v"(ip), "+v"(pa), "+v"(pb));
+    if (active) collide<R, kScaled<S>>(q, phi, ip, pa, pb, fd, gd, hd, prev);
+    if (s == edge) break;
+    S(*pop)[RG::SLOTS] = lds[s & 1];
+    if (active) {
+      // rounded to the storage type as a store and a reload would round them
+      Dither dz(c, step + (uint32_t)s);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        const S v = to_store<S>(fd[i], one, dz);
+        if (NEE || i > 0) pop[P(i)][r] = v;
+        fd[i] = to_real<S>(v, one);
+      }
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        const S v = to_store<S>(gd[i], one, dz);
+        if (NEE || i > 0) pop[P(9 + i)][r] = v;
+        gd[i] = to_real<S>(v, one);
+      }
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        const S v = to_store<S>(hd[i], one, dz);
+        if (NEE || i > 0) pop[P(14 + i)][r] = v;
+        hd[i] = to_real<S>(v, one);
+      }
+    }
+    __syncthreads();
+    if (depth <= s) active = false;        // step s + 2 needs the nodes at least s + 1 deep
+    if (!active) continue;
+    if (NEE && (wx || wy)) {
+      // the pulls of f and ff from LDS (beyond the region only for nodes that are spoilt anyway:
+      // their index is brought back into it)
+      auto lds_pull = [&](int at, R *f, R *g, R *h) {
+        const int q0 = min(max(at, PAD), PAD + RG::NODES - 1);
+        const int up[9] = {q0, q0 - 1, q0 - RW, q0 + 1, q0 + RW, q0 - RW - 1, q0 - RW + 1, q0 + RW + 1, q0 + RW - 1};
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = to_real<S>(pop[P(i)][up[i]], one);
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          g[i] = to_real<S>(pop[P(9 + i)][up[i]], one);
+          h[i] = to_real<S>(pop[P(14 + i)][up[i]], one);
+        }
+      };
+      R f2[9], g2[5], h2[5];
+      const int in1 = rule.dy * RW + rule.dx;
+      lds_pull(r + in1, fd, gd, hd);
+      lds_pull(r + 2 * in1, f2, g2, h2);
+      R vb = phi, vf = phif, vff = phiff, va = af, vbf = bf;
+      NeeRule<R> k = rule;
+      asm volatile("" : "+v"(vb), "+v"(vf), "+v"(vff), "+v"(va), "+v"(vbf));
+      asm volatile("" : "+v"(k.ubx), "+v"(k.uby), "+v"(k.Tfix), "+v"(k.Cfix), "+v"(k.bT), "+v"(k.bC));
+      nee_extrapolate<S>(d, k, vb, vf, vff, va, vbf, fd, gd, hd, g2, h2);
+      continue;
+    }
+    // f_i(x) = f_i*(x - e_i), or this node's own opposite population across a wall
+    auto L = [&](bool ok, int i, int off, R own) -> R {
+      const R v = to_real<S>(pop[P(i)][r + off], one);
+      return ok ? v : own;
+    };
+    {
+      const R o1 = fd[1], o2 = fd[2], o3 = fd[3], o4 = fd[4], o5 = fd[5], o6 = fd[6], o7 = fd[7], o8 = fd[8];
+      fd[1] = L(w.okxm, 1, -1, o3);
+      fd[2] = L(w.okym, 2, -RW, o4);
+      fd[3] = L(w.okxp, 3, 1, o1);
+      fd[4] = L(w.okyp, 4, RW, o2);
+      fd[5] = L(w.ok5, 5, -RW - 1, o7);
+      fd[6] = L(w.ok6, 6, -RW + 1, o8);
+      fd[7] = L(w.ok7, 7, RW + 1, o5);
+      fd[8] = L(w.ok8, 8, RW - 1, o6);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      R *e = k ? hd : gd;
+      const int p = k ? 14 : 9;
+      const R o1 = e[1], o2 = e[2], o3 = e[3], o4 = e[4];
+      e[1] = L(w.okxm, p + 1, -1, o3);
+      e[2] = L(w.okym, p + 2, -RW, o4);
+      e[3] = L(w.okxp, p + 3, 1, o1);
+      e[4] = L(w.okyp, p + 4, RW, o2);
+    }
+    if (!NEE) w.apply(fd, gd, hd);
+  }
+  if (live && mine) {
+    rs.d4 = fwrite;
+    store_node<S, CP_RESIDENT>(d, rs, c, step + (uint32_t)edge, fd, gd, hd, prev);
+  }
+}
+
 // Batched two steps over items of W x H tiles (item.tw = W, the group's shape SH): one item per
 // work-group (a loop over items keeps values live across iterations and costs a third of the
 // occupancy); the grid may exceed the item count, the extra work-groups exit at once.
@@ -1897,6 +2202,42 @@ int launch_step3(int prec, const void *desc, const void *ddev, int cp, int parit
       if (rows != ThreeStep<float>::H) return (int)hipErrorInvalidValue;
       return step3_t<float, ThreeStep<float>>(desc, ddev, cp, parity, sw, stream);
     default: return (int)hipErrorInvalidValue;   // FP16 storage: one or two steps per launch
+  }
+}
+
+template <typename S, bool NEE, typename RG>
+static int region_t(const void *desc, const void *ddev, int parity, int steps, void *stream) {
+  const auto &d = *(const Desc<typename St<S>::R> *)desc;
+  const int tile = RG::RW - 2 * (steps - 1);
+  if (tile < 4 || (NEE && (d.nx < tile || d.ny < tile))) return (int)hipErrorInvalidValue;
+  const int ntx = (d.nx + tile - 1) / tile, nty = (d.ny + tile - 1) / tile;
+  hipLaunchKernelGGL((region_kernel<S, NEE, RG>), dim3(ntx * nty), dim3(RG::THREADS), 0, (hipStream_t)stream,
+                     (const Desc<typename St<S>::R> *)ddev, ntx, ntx > 1 ? (uint32_t)(((1ull << 32) + ntx - 1) / ntx) : 0u,
+                     parity, steps);
+  return (int)hipGetLastError();
+}
+
+template <typename RG>
+static int region_rw(int prec, const void *desc, const void *ddev, int parity, int steps, void *stream) {
+  switch (prec) {
+    case PREC_FP64:
+      return ((const Desc<double> *)desc)->nee ? region_t<double, true, RG>(desc, ddev, parity, steps, stream)
+                                               : region_t<double, false, RG>(desc, ddev, parity, steps, stream);
+    case PREC_FP32:
+      return ((const Desc<float> *)desc)->nee ? region_t<float, true, RG>(desc, ddev, parity, steps, stream)
+                                              : region_t<float, false, RG>(desc, ddev, parity, steps, stream);
+    default:
+      if (((const Desc<float> *)desc)->nee) return (int)hipErrorInvalidValue;   // FP16: one step per launch
+      return region_t<_Float16, false, RG>(desc, ddev, parity, steps, stream);
+  }
+}
+
+int launch_region(int prec, const void *desc, const void *ddev, int parity, int steps, int side, void *stream) {
+  if (steps < 1) return (int)hipErrorInvalidValue;
+  switch (side) {
+    case 16: return region_rw<Region<16>>(prec, desc, ddev, parity, steps, stream);
+    case 22: return region_rw<Region<22>>(prec, desc, ddev, parity, steps, stream);
+    default: return (int)hipErrorInvalidValue;
   }
 }
 

@@ -199,3 +199,85 @@ def test_tile_order_is_a_permutation(sw):
     # within a full strip, consecutive tiles run along a row of the strip, then down
     assert [_tile_of(b, 10, 3, 4) for b in range(6)] == [(0, 0), (1, 0), (2, 0), (3, 0), (0, 1), (1, 1)]
     assert _tile_of(24, 10, 3, 4) == (8, 0) and _tile_of(25, 10, 3, 4) == (9, 0) and _tile_of(26, 10, 3, 4) == (8, 1)
+
+
+# ------------------------------------------------------------ region launch (small lattices)
+
+def _spread(side, steps, nx, ny, perx, pery, nee):
+    """Walks a region launch of `steps` steps on regions of side^2 nodes: which region nodes hold
+    right values after each step, LDS reads in the padded plane, every lattice node stored."""
+    edge, tile = steps - 1, side - 2 * (steps - 1)
+    pad, nodes = side + 1, side * side
+    stored = set()
+    for by in range(-(-ny // tile)):
+        for bx in range(-(-nx // tile)):
+            x0, y0 = bx * tile, by * tile
+            if nee:
+                x0, y0 = min(x0, nx - tile), min(y0, ny - tile)
+            at = {}
+            for t in range(nodes):
+                X, Y = x0 - edge + t % side, y0 - edge + t // side
+                if perx:
+                    X %= nx
+                if pery:
+                    Y %= ny
+                if 0 <= X < nx and 0 <= Y < ny:
+                    at[t] = (X, Y)
+            right = set(at)                     # step one pulls from global memory
+            for s in range(edge):
+                now = set()
+                for t, (X, Y) in at.items():
+                    r = pad + t
+                    w = (not perx and X in (0, nx - 1), not pery and Y in (0, ny - 1))
+                    need = []
+                    if nee and any(w):
+                        dx = (1 if X == 0 else -1) if w[0] else 0
+                        dy = (1 if Y == 0 else -1) if w[1] else 0
+                        for k in (1, 2):
+                            q = min(max(r + k * (dy * side + dx), pad), pad + nodes - 1)
+                            for ey in (-1, 0, 1):
+                                for ex in (-1, 0, 1):
+                                    assert 0 <= q + ey * side + ex < nodes + 2 * pad
+                                    need.append((t % side + k * dx + ex, t // side + k * dy + ey))
+                    else:
+                        for ey in (-1, 0, 1):
+                            for ex in (-1, 0, 1):
+                                assert 0 <= r + ey * side + ex < nodes + 2 * pad
+                                if (perx or 0 <= X + ex < nx) and (pery or 0 <= Y + ey < ny):
+                                    need.append((t % side + ex, t // side + ey))
+                    if all(0 <= a < side and 0 <= b < side and b * side + a in right for a, b in need):
+                        now.add(t)
+                # a wave stops when none of its rows is s + 1 nodes deep
+                deep = set()
+                for v in range(0, nodes, 64):
+                    r0, r1 = v // side, (v + 63) // side
+                    d = r1 if r1 < side // 2 else side - 1 - r0 if r0 >= side // 2 else side // 2
+                    if d > s:
+                        deep.update(range(v, v + 64))
+                right = now & deep
+            for j in range(tile):
+                for i in range(tile):
+                    if x0 + i < nx and y0 + j < ny:
+                        assert (edge + j) * side + edge + i in right, (side, steps, nx, ny, bx, by, i, j)
+                        stored.add((x0 + i, y0 + j))
+    assert len(stored) == nx * ny
+
+
+@pytest.mark.parametrize("side,steps", [(16, 1), (16, 3), (16, 4), (16, 5), (16, 6), (22, 2), (22, 4), (22, 5)])
+def test_region_launch_stores_right_nodes(side, steps):
+    t = side - 2 * (steps - 1)
+    for perx, pery in ((False, False), (True, False), (False, True), (True, True)):
+        for nx, ny in ((3, 3), (t, t + 1), (2 * t + 1, 7), (side + 3, 2 * t - 1)):
+            _spread(side, steps, nx, ny, perx, pery, False)
+    for perx, pery in ((False, False), (True, False), (False, True)):
+        for nx, ny in ((side, side), (side + 1, side + t - 1), (2 * t + 1 + side, side)):
+            _spread(side, steps, nx, ny, perx, pery, True)
+
+
+def test_region_tile_index_by_multiplication():
+    """The kernel divides the tile index by the tiles across with a multiplication by
+    ceil(2^32 / ntx)."""
+    for ntx in list(range(2, 300)) + [511, 512, 4000]:
+        inv = ((1 << 32) + ntx - 1) // ntx
+        for b in list(range(0, 40 * ntx, 7)) + [100 * ntx - 1, 100 * ntx]:
+            assert (b * inv) >> 32 == b // ntx

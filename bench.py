@@ -120,10 +120,10 @@ def profiled_traffic(prec, n, launch):
     """HBM bytes per launch of the step kernel from the committed rocprofv3 counter summary
     (FETCH_SIZE and WRITE_SIZE scaled by a plain copy of known size), or None when there is no
     summary for this workload, the kernel code has changed since the counters were taken, or
-    the launch [tile_x, tile_y, policy, steps per launch, strip width, tile rows] differs from
-    the profiled one."""
+    the launch [tile_x, tile_y, policy, steps per launch, strip width, tile rows, kernel] differs
+    from the profiled one."""
     import re
-    kernel = {2: "step2_kernel", 3: "step3_kernel"}.get(launch[3], "step_kernel")
+    kernel, launch = launch[6], launch[:6]
     path = os.path.join(ROOT, "profiles", f"{kernel}_{prec}_cavity{n}.md")
     if not os.path.exists(path):
         return None
@@ -144,6 +144,16 @@ def kernel_code_hash():
     src = re.sub(r"/\*.*?\*/", "", src, flags=re.S)
     src = re.sub(r"//[^\n]*", "", src)
     return hashlib.sha256("".join(src.split()).encode()).hexdigest()[:16]
+
+
+def launch_of(s):
+    """Steps per launch of a solver and the kernel that runs them."""
+    if s.get_march_steps():
+        return s.get_march_steps(), "march_kernel"
+    if s.get_region_steps():
+        return s.get_region_steps(), "region_kernel"
+    spl = s.get_steps_per_launch()
+    return spl, {2: "step2_kernel", 3: "step3_kernel"}.get(spl, "step_kernel")
 
 
 def timed_run(case, prec, steps, warmup, tile="auto", policy=None, spl=0, strip=-1, rows=0):
@@ -172,8 +182,8 @@ def timed_run(case, prec, steps, warmup, tile="auto", policy=None, spl=0, strip=
     wall = time.perf_counter() - t0
     ms = e0.elapsed_time(e1)
     ob = s.observables()
-    tile_used = list(s.get_tile()) + [s.get_cache_policy(), s.get_steps_per_launch(), s.get_strip_width(),
-                                      s.get_tile_rows()]
+    spl, kernel = launch_of(s)
+    tile_used = list(s.get_tile()) + [s.get_cache_policy(), spl, s.get_strip_width(), s.get_tile_rows(), kernel]
     s.close()
     return ms, wall, ob, tile_used
 
@@ -321,7 +331,7 @@ def precision_report(a):
             dt = time.perf_counter() - t0
             ob = s.observables()
             F = s.fields()
-            spl = s.get_steps_per_launch()
+            spl = launch_of(s)[0]
             s.close()
             ml = n * n * (steps - 2) / dt / 1e6
             rf = roofline_fields(prec, n * n, dt * 1e3 / (steps - 2), spl)
@@ -514,7 +524,7 @@ def main():
     mlups = nodes * a.steps / (ms * 1e-3) / 1e6
     spl = tile_used[3]
     rf = roofline_fields(a.precision, nodes, ms / a.steps, spl)
-    kernel = {2: "step2_kernel", 3: "step3_kernel"}.get(spl, "step_kernel")
+    kernel = tile_used[6]
     out = {
         "metric": "MLUPS (D2Q9+2xD2Q5) & % HBM roofline; batched p50/p99 solve latency",
         "value": round(mlups, 1),

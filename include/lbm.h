@@ -266,20 +266,24 @@ int32_t lbm_get_tile_rows(const struct lbm_ctx *c);
  * While every launch choice is the default (this one, cache policy, tile, strip width, tile rows),
  * lattices of up to about 400^2 nodes take the region launch instead: work-groups of one thread per
  * node advance small square regions by 3 to 6 steps, whatever the lattice leaves at most one
- * region per compute unit for (bit for bit the same results; not with FP16 storage and walls
- * through the nodes).  lbm_get_region_steps returns its steps per launch, 0 where the launches
- * above run (and for a NULL context). */
+ * region per compute unit for (not with FP16 storage and walls through the nodes), and large
+ * lattices with FP64 and FP32 storage and walls half a spacing outside (about 10^6 nodes, FP32 1.6
+ * 10^6, and more) the march: waves march up strips of columns and update four time levels as they
+ * go.  Bit for bit the same results.  lbm_get_region_steps and
+ * lbm_get_march_steps return the steps per launch of the one in effect, 0 where the launches above
+ * run (and for a NULL context). */
 lbm_status lbm_set_steps_per_launch(struct lbm_ctx *c, int32_t n);
 int32_t lbm_get_region_steps(const struct lbm_ctx *c);
+int32_t lbm_get_march_steps(const struct lbm_ctx *c);
 int32_t lbm_get_steps_per_launch(const struct lbm_ctx *c);
 
 /* Times every supported launch shape, cache policy and steps-per-launch count on this
  * context for `steps` steps each (HIP events), the multi-step launches also with their tiles
  * row by row, in strips of 4 and 8 tiles and of one strip per XCD band, and the FP32 three-step
  * and FP16 two-step launches on
- * both their tiles, and the defaults where they are the region launch,
- * keeps the fastest (read the choices with lbm_get_region_steps, and where that is 0 with
- * lbm_get_cache_policy, lbm_get_steps_per_launch, lbm_get_strip_width, lbm_get_tile_rows),
+ * both their tiles, and the defaults where they are the region launch or the march,
+ * keeps the fastest (read the choices with lbm_get_region_steps and lbm_get_march_steps, and where
+ * both are 0 with lbm_get_cache_policy, lbm_get_steps_per_launch, lbm_get_strip_width, lbm_get_tile_rows),
  * restores the state it started from, and reports the tile and its time per step.
  * Synchronises. */
 lbm_status lbm_autotune(struct lbm_ctx *c, int32_t steps, int32_t *tile_x, int32_t *tile_y,

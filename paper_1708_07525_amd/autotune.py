@@ -16,7 +16,8 @@ import os
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "lbm_dd", "autotune.json")
 # part of every key: raised when the kernels' launch choices change (three steps per launch for
 # FP32, a three-step tile with its rest populations in registers, the tile order of the
-# multi-step launches, their taller tiles, the region launch of small lattices), so that choices
+# multi-step launches, their taller tiles, the region launch of small and the march of
+# large lattices), so that choices
 # timed with older kernels are not applied to newer ones
 KERNEL_GENERATION = 5
 
@@ -64,13 +65,18 @@ def tune(solver, device_name: str, porosity_field: bool, steps: int = 20, path: 
     tile rows for this solver's class (walls through the boundary nodes are a class of their own), or
     time all of them and cache the fastest.  Returns (tile_x, tile_y), ms_per_step (None when taken from the cache)."""
     k = key(device_name, solver.precision, solver.nx, solver.ny, porosity_field, node_walls)
-    region_steps = getattr(solver, "get_region_steps", lambda: 0)
-    if region_steps():                       # lattices small enough for the region launch are a class of their own
-        k += "|region"
+
+    def launch():                            # "region", "march" or "": the launch in effect by default
+        for name in ("region", "march"):
+            if getattr(solver, f"get_{name}_steps", lambda: 0)():
+                return name
+        return ""
+    if launch():                             # lattices that take them are classes of their own
+        k += "|" + launch()
     entries = load(path)
     if not force and k in entries:
         tx, ty = entries[k]["tile"]
-        if entries[k].get("region"):         # the launch defaults were the fastest: keep them
+        if entries[k].get("launch"):         # the launch defaults were the fastest: keep them
             return (tx, ty), None
         solver.set_tile(tx, ty)
         solver.set_cache_policy(int(entries[k].get("policy", -1)))
@@ -82,7 +88,7 @@ def tune(solver, device_name: str, porosity_field: bool, steps: int = 20, path: 
     entries = load(path)          # re-read: another process may have added entries
     entries[k] = {"tile": [tx, ty], "policy": solver.get_cache_policy(),
                   "steps_per_launch": solver.get_steps_per_launch(), "strip_width": solver.get_strip_width(),
-                  "tile_rows": solver.get_tile_rows(), "region": region_steps() > 0,
+                  "tile_rows": solver.get_tile_rows(), "launch": launch(),
                   "ms_per_step": ms, "steps": steps}
     store(entries, path)
     return (tx, ty), ms

@@ -35,7 +35,8 @@ using namespace lbmk;
 namespace {
 
 constexpr int kGraphChunk = 64;     // default steps per captured graph in lbm_step (even)
-constexpr int kRegionTiles = 256;   // regions of a region launch: one per CU
+constexpr int kComputeUnits = 256;  // of the chip
+constexpr int kRegionTiles = kComputeUnits;   // regions of a region launch: one per CU
 constexpr double kCs2 = 1.0 / 3.0;  // D2Q9 sound speed squared
 
 struct DevBuf {
@@ -126,7 +127,7 @@ struct lbm_ctx {
   int graph_cur = -1;
   Tile graph_tile{0, 0};
   int graph_cp = -1;
-  int graph_d4 = -1, graph_spl = 0, graph_sw = -1, graph_rows = 0, graph_side = 0;
+  int graph_d4 = -1, graph_spl = 0, graph_sw = -1, graph_rows = 0, graph_side = 0, graph_march = 0;
   int graph_chunk = kGraphChunk;   // 0: plain launches only
 
   void *pop(int i) const { return base + (i ? lay.off_pop1 : lay.off_pop0); }
@@ -789,10 +790,13 @@ static int ctx_strip(const lbm_ctx *c) {
 struct RegionPlan {
   int side, steps;
 };
+static bool launch_defaults(const lbm_ctx *c) {
+  return c->steps_per_launch == 0 && c->cache_policy < 0 && c->strip < 0 && c->tile_rows == 0 && !c->tile_set;
+}
 static RegionPlan ctx_region(const lbm_ctx *c) {
   const bool nee = node_walls(&c->p);
   const int nx = c->p.nx, ny = c->p.ny;
-  if (c->steps_per_launch != 0 || c->cache_policy >= 0 || c->strip >= 0 || c->tile_rows > 0 || c->tile_set) return {0, 0};
+  if (!launch_defaults(c)) return {0, 0};
   if (nee && c->prec == PREC_FP16S) return {0, 0};
   auto tiles = [&](int side, int steps) -> int64_t {
     const int t = side - 2 * (steps - 1);
@@ -811,8 +815,33 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
   return {0, 0};
 }
 
+// The march of large lattices (launch_march): steps per launch and rows per chunk, {0, 0} where the
+// tiled launches are faster.  The chunks are as tall as leaves every wave slot of the chip one, so
+// that all waves run at once and end together; a chunk costs steps - 1 extra rows at either end,
+// so the lattice must be large enough for tall ones.  Measured (GLUPS, march against the tiled
+// launches; rows per chunk in brackets): FP64 4096^2 42.2 (147) against 27.6, 2048^2 39.5 (37)
+// against 30.4, 1280 x 1300 33.8 (16) against 27.8, 1024^2 29.3 (11) against 24.1, 700^2 22.1 (6)
+// against 26.1; FP32 4096^2 78.3 (74) against 72.2, 2048^2 72.2 (19) against 63.8, 1536^2 65.5
+// (11) against 58.5, 1280 x 1300 59.2 (8) against 54.1, 1024^2 48.0 (7) against 58.7.  Hence chunks
+// of at least 10 rows in FP64 and 8 in FP32.  FP16 storage (three levels) lost 2% at 2048^2, 12% at
+// 1536^2 and won 12% at 3000^2: not there.
+struct MarchPlan {
+  int steps, chunk;
+};
+static MarchPlan ctx_march(const lbm_ctx *c) {
+  if (!launch_defaults(c) || node_walls(&c->p) || c->prec == PREC_FP16S || c->p.nx < 128) return {0, 0};
+  int steps = 0, columns = 0, per_cu = 0;
+  march_shape(c->prec, &steps, &columns, &per_cu);
+  const int groups = (c->p.nx + columns - 1) / columns;
+  const int chunks = std::max(1, kComputeUnits * per_cu / groups);
+  const int chunk = (c->p.ny + chunks - 1) / chunks;
+  const int least = c->prec == PREC_FP64 ? 10 : 8;
+  return chunk >= least && c->p.ny >= 16 ? MarchPlan{steps, chunk} : MarchPlan{0, 0};
+}
+
 // n steps with plain launches: three or two steps per launch as ctx_spl allows, the remainder
-// in shorter launches; on small lattices region launches, the steps spread evenly over them
+// in shorter launches; on small lattices region launches, the steps spread evenly over them; on
+// large ones the march, the remainder as above
 static lbm_status step_plain(lbm_ctx *c, int64_t n) {
   const RegionPlan rg = ctx_region(c);
   if (rg.side) {
@@ -828,12 +857,18 @@ static lbm_status step_plain(lbm_ctx *c, int64_t n) {
     }
     return LBM_OK;
   }
+  const MarchPlan mp = ctx_march(c);
   const int cp = ctx_policy(c);
   const int spl = ctx_spl(c);
   const int sw = ctx_strip(c), rows2 = rows2_of(c), rows3 = rows3_of(c);
   while (n > 0) {
     set_parity(c, c->cur);
-    if (spl == 3 && n >= 3) {
+    if (mp.steps && n >= mp.steps) {
+      int e = launch_march(c->prec, c->desc(), c->desc_dev(c->cur, c->d4cur), 0, mp.chunk, c->stream);
+      if (e) return hip_fail(c, (hipError_t)e, "march kernel launch");
+      c->d4cur ^= 1;
+      n -= mp.steps;
+    } else if (spl == 3 && n >= 3) {
       int e = launch_step3(c->prec, c->desc(), c->desc_dev(c->cur, c->d4cur), cp, 0, sw, rows3, c->stream);
       if (e) return hip_fail(c, (hipError_t)e, "three-step kernel launch");
       c->d4cur ^= 1;
@@ -859,12 +894,15 @@ static lbm_status step_plain(lbm_ctx *c, int64_t n) {
 // three steps per launch replay the largest multiple of 6 steps in graph_chunk, two steps per
 // launch the whole chunk when it is a multiple of 4; otherwise one step per launch.  Region
 // launches (side > 0) replay the largest multiple of two launches, of fewer steps each where the
-// chunk is shorter than that.
-static void graph_plan(const lbm_ctx *c, int *spl, int *steps, int *side) {
+// chunk is shorter than that; the march (rows > 0) the largest multiple of two launches, where
+// the chunk holds two.
+static void graph_plan(const lbm_ctx *c, int *spl, int *steps, int *side, int *rows) {
   const RegionPlan rg = ctx_region(c);
+  const MarchPlan mp = ctx_march(c);
   *side = c->graph_chunk > 0 ? rg.side : 0;
-  if (*side) {
-    *spl = std::min(rg.steps, c->graph_chunk / 2);
+  *rows = mp.steps && c->graph_chunk >= 2 * mp.steps ? mp.chunk : 0;
+  if (*side || *rows) {
+    *spl = *rows ? mp.steps : std::min(rg.steps, c->graph_chunk / 2);
     *steps = c->graph_chunk / (2 * *spl) * (2 * *spl);
     return;
   }
@@ -885,9 +923,9 @@ static void graph_plan(const lbm_ctx *c, int *spl, int *steps, int *side) {
 static lbm_status ensure_graph(lbm_ctx *c) {
   const int cp = ctx_policy(c);
   const int sw = ctx_strip(c), rows = ctx_rows(c), rows2 = rows2_of(c), rows3 = rows3_of(c);
-  int spl = 1, gsteps = 0, side = 0;
-  graph_plan(c, &spl, &gsteps, &side);
-  if (c->graph && c->graph_side == side && c->graph_cur == c->cur && c->graph_tile.tx == c->tile.tx && c->graph_tile.ty == c->tile.ty &&
+  int spl = 1, gsteps = 0, side = 0, march = 0;
+  graph_plan(c, &spl, &gsteps, &side, &march);
+  if (c->graph && c->graph_side == side && c->graph_march == march && c->graph_cur == c->cur && c->graph_tile.tx == c->tile.tx && c->graph_tile.ty == c->tile.ty &&
       c->graph_cp == cp && c->graph_d4 == c->d4cur && c->graph_spl == spl && c->graph_sw == sw &&
       c->graph_rows == rows)
     return LBM_OK;
@@ -903,6 +941,9 @@ static lbm_status ensure_graph(lbm_ctx *c) {
       set_parity(c, cur, d4);
       if (side) {
         e = (hipError_t)launch_region(c->prec, c->desc(), c->desc_dev(cur, d4), 0, spl, side, cs);
+        d4 ^= 1;
+      } else if (march) {
+        e = (hipError_t)launch_march(c->prec, c->desc(), c->desc_dev(cur, d4), 0, march, cs);
         d4 ^= 1;
       } else if (spl == 3) {
         e = (hipError_t)launch_step3(c->prec, c->desc(), c->desc_dev(cur, d4), cp, 0, sw, rows3, cs);
@@ -934,6 +975,7 @@ static lbm_status ensure_graph(lbm_ctx *c) {
   c->graph_sw = sw;
   c->graph_rows = rows;
   c->graph_side = side;
+  c->graph_march = march;
   return LBM_OK;
 }
 
@@ -946,8 +988,8 @@ LBM_API lbm_status lbm_step(lbm_ctx *c, int64_t nsteps) {
     return fail(c, LBM_ESTATE, "the fields hold a non-finite value (reported at step %lld); restart with "
                 "lbm_set_fields or restore a state with lbm_set_state", (long long)c->step);
   int64_t left = nsteps;
-  int gspl = 1, gsteps = 0, gside = 0;
-  graph_plan(c, &gspl, &gsteps, &gside);
+  int gspl = 1, gsteps = 0, gside = 0, gmarch = 0;
+  graph_plan(c, &gspl, &gsteps, &gside, &gmarch);
   if (c->graph_chunk > 0 && left >= gsteps) {
     lbm_status s = ensure_graph(c);
     if (s != LBM_OK) return s;
@@ -1207,6 +1249,8 @@ LBM_API int32_t lbm_get_steps_per_launch(const lbm_ctx *c) { return c ? ctx_spl(
 
 LBM_API int32_t lbm_get_region_steps(const lbm_ctx *c) { return c ? ctx_region(c).steps : 0; }
 
+LBM_API int32_t lbm_get_march_steps(const lbm_ctx *c) { return c ? ctx_march(c).steps : 0; }
+
 LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int32_t *ty_out, double *ms_out) {
   Range range_("lbm_autotune");
   if (!c || steps < 2) return LBM_EINVAL;
@@ -1264,13 +1308,13 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
       for (int cp = 0; cp < CP_COUNT; ++cp)
         for (int sw : sws) cands.push_back(Cand{3, cp, tile0.tx, tile0.ty, sw, rows});
     }
-  const int nsteps = (steps + 5) / 6 * 6;   // whole launches of two and of three steps
-  // the defaults, where they are the region launch
+  const int nsteps = (steps + 11) / 12 * 12;   // whole launches of two, three and four steps
+  // the defaults, where they are the region launch or the march
   c->tile_set = false;
   c->cache_policy = c->strip = -1;
   c->steps_per_launch = c->tile_rows = 0;
   const Tile dt = default_tile(&c->p);
-  if (ctx_region(c).side) cands.push_back(Cand{0, -1, dt.tx, dt.ty, -1, 0});
+  if (ctx_region(c).side || ctx_march(c).steps) cands.push_back(Cand{0, -1, dt.tx, dt.ty, -1, 0});
   bool best_set = tset0;
   for (const Cand &k : cands) {
     if (e != hipSuccess) break;
@@ -1280,7 +1324,7 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
     c->steps_per_launch = k.spl;
     c->strip = k.sw;
     c->tile_rows = k.rows;
-    if (step_plain(c, 6) != LBM_OK) { e = hipErrorUnknown; break; }   // warm-up
+    if (step_plain(c, 12) != LBM_OK) { e = hipErrorUnknown; break; }   // warm-up
     e = hipEventRecord(t0, c->stream);
     if (e == hipSuccess && step_plain(c, nsteps) != LBM_OK) e = hipErrorUnknown;
     if (e == hipSuccess) e = hipEventRecord(t1, c->stream);

@@ -93,6 +93,12 @@ int launch_step2(int prec, const void *desc, const void *ddev, int cp, int parit
 // storage, walls half a spacing outside; fields read from d4, written to d4b; sw as above;
 // rows: tile rows, 8 (64 x 8, FP64 32 x 8) or, FP32 only, 12 (64 x 12); else hipErrorInvalidValue
 int launch_step3(int prec, const void *desc, const void *ddev, int cp, int parity, int sw, int rows, void *stream);
+// march_shape's `steps` time steps per launch on large lattices: waves march up chunks of `chunk` rows
+// of their strips of columns; fields read from d4, written to d4b; FP32 and FP64 storage, walls half
+// a spacing outside, at least 128 x 16 nodes (else hipErrorInvalidValue)
+int launch_march(int prec, const void *desc, const void *ddev, int parity, int chunk, void *stream);
+// steps per launch, columns a work-group stores, work-groups a CU holds (FP32 and FP64 storage)
+void march_shape(int prec, int *steps, int *group_columns, int *groups_per_cu);
 // `steps` time steps per launch on small lattices: a region of side x side nodes (16 or 22) per
 // work-group, whose inner (side - 2 (steps - 1))^2 nodes, at least 4^2, it stores; fields read from
 // d4, written to d4b; walls through the nodes with FP32 and FP64 storage on lattices that hold

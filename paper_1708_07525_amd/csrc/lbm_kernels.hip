@@ -80,6 +80,9 @@ __device__ __forceinline__ double sqrt_(double v) { return sqrt(v); }
 template <>
 __device__ __forceinline__ float sqrt_(float v) { return sqrtf(v); }
 
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 // ---------------------------------------------------------------- explicit velocity
 // Eqs. (18)-(19): u = v / (l0 + sqrt(l0^2 + l1 |v|)), l0 = (1 + a/2)/2, l1 = b/2, and |u|.
 // In FP32 the denominator is written as 1 + e, e = a/2 + l1 |v| / (l0 + sqrt(l0^2 + l1 |v|))
@@ -124,16 +127,22 @@ __device__ __forceinline__ void velocity_solve(R a, R b, R vx, R vy, R &ux, R &u
 // (rho0_s, T0_s, C0_s); only the fields (T - T0, C - C0 and the velocity) are formed in
 // physical units.  A power of two commutes with every rounding here, so the arithmetic is that
 // of physical units, scaled exactly, without a multiply per population.
+// Every fused multiply-add is written out and the compiler fuses none by itself: which of two
+// products it would fuse with their sum depends on the code around (a product taken out of a loop
+// is not fused at all), and the kernels must agree to the last bit.
 template <typename R, bool SC, typename D>
 __device__ __forceinline__ void collide(const D &d, R phi, R inv_phi, R a, R b, R *fd, R *gd, R *hd,
                                         R *prev) {
+#pragma clang fp contract(off)
   const R half = R(0.5);
   // density, momentum and scalars (Eqs. 16, 17, 26), deviation form
+  const R f13 = fd[1] - fd[3], f24 = fd[2] - fd[4], f56 = fd[5] - fd[6], f78 = fd[7] - fd[8];
+  const R s56 = fd[5] + fd[6], s78 = fd[7] + fd[8];
   const R sA = fd[1] + fd[2] + fd[3] + fd[4];
-  const R sD = fd[5] + fd[6] + fd[7] + fd[8];
+  const R sD = s56 + fd[7] + fd[8];
   const R drho = fd[0] + sA + sD;
-  const R jx = (fd[1] - fd[3]) + (fd[5] - fd[6]) - (fd[7] - fd[8]);
-  const R jy = (fd[2] - fd[4]) + (fd[5] + fd[6]) - (fd[7] + fd[8]);
+  const R jx = f13 + f56 - f78;
+  const R jy = f24 + s56 - s78;
   const R sg = gd[0] + gd[1] + gd[2] + gd[3] + gd[4];
   const R sh = hd[0] + hd[1] + hd[2] + hd[3] + hd[4];
   const R dTs = sg * d.inv_sigma;         // T - T0 (scaled with SC)
@@ -141,75 +150,82 @@ __device__ __forceinline__ void collide(const D &d, R phi, R inv_phi, R a, R b, 
   const R dT = SC ? dTs * d.inv_scale : dTs;
   const R dC = SC ? dCs * d.inv_scale : dCs;
   // buoyancy (Eq. 6) plus any constant acceleration.  Both products are rounded before the
-  // sum (no fused multiply-add), so that equal and opposite thermal and solutal terms cancel
-  // exactly, as they do in Eq. (6)
+  // sum, so that equal and opposite thermal and solutal terms cancel exactly, as they do in Eq. (6)
   const R Gx = d.gx;
-  R Gy;
-  {
-#pragma clang fp contract(off)
-    const R bT = d.gbT * dT;
-    const R bC = d.gbC * dC;
-    Gy = d.gy + (bT + bC);
-  }
+  const R Gy = d.gy + (d.gbT * dT + d.gbC * dC);
   // explicit velocity (Eqs. 18-19), delta_t = 1
-  const R vx = jx * d.inv_rho0_s + half * phi * Gx;
-  const R vy = jy * d.inv_rho0_s + half * phi * Gy;
-  R ux, uy, un;
-  velocity_solve(a, b, vx, vy, ux, uy, un);
-  const R u2 = ux * ux + uy * uy;
+  const R hphi = half * phi;
+  const R vx = fma_(hphi, Gx, jx * d.inv_rho0_s);
+  const R vy = fma_(jy, d.inv_rho0_s, hphi * Gy);
+  // (as velocity_solve) and its change since the previous step
+  R ux, uy, un, dux, duy;
+  const R l0 = fma_(R(0.25), a, half), l1 = half * b;
+  if constexpr (sizeof(R) == 4) {
+    const R vn = __builtin_amdgcn_sqrtf(fma_(vx, vx, vy * vy));
+    const R l1v = l1 * vn;
+    const R e = fma_(half, a, l1v * __builtin_amdgcn_rcpf(l0 + __builtin_amdgcn_sqrtf(fma_(l0, l0, l1v))));
+    const R w = e * __builtin_amdgcn_rcpf(R(1) + e);
+    ux = fma_(-vx, w, vx);
+    uy = fma_(-vy, w, vy);
+    un = fma_(-vn, w, vn);
+    dux = ux - prev[2];
+    duy = uy - prev[3];
+  } else {
+    const R vn = sqrt_(fma_(vx, vx, vy * vy));
+    const R inv_den = R(1) / (l0 + sqrt_(fma_(l0, l0, l1 * vn)));
+    ux = vx * inv_den;
+    uy = vy * inv_den;
+    un = vn * inv_den;
+    dux = fma_(vx, inv_den, -prev[2]);
+    duy = fma_(vy, inv_den, -prev[3]);
+  }
+  const R uy2 = uy * uy;
+  const R u2 = fma_(ux, ux, uy2);
   // total force (Eq. 5)
-  const R drag = a + b * un;
-  const R Fx = phi * Gx - drag * ux;
-  const R Fy = phi * Gy - drag * uy;
+  const R drag = fma_(b, un, a);
+  const R Fx = fma_(phi, Gx, -(drag * ux));
+  const R Fy = fma_(phi, Gy, -(drag * uy));
 
   // ---- D2Q9: moments m = M f (Eq. 13) of the deviations
-  const R m1 = R(-4) * fd[0] - sA + R(2) * sD;
-  const R m2 = R(4) * fd[0] - R(2) * sA + sD;
-  const R m4 = R(-2) * (fd[1] - fd[3]) + (fd[5] - fd[6]) - (fd[7] - fd[8]);
-  const R m6 = R(-2) * (fd[2] - fd[4]) + (fd[5] + fd[6]) - (fd[7] + fd[8]);
+  const R m1 = fma_(R(2), sD, fma_(R(-4), fd[0], -sA));
+  const R m2 = fma_(R(4), fd[0], R(-2) * sA) + sD;
+  const R m4 = fma_(R(-2), f13, f56) - f78;
+  const R m6 = fma_(R(-2), f24, s56) - s78;
   const R m7 = (fd[1] + fd[3]) - (fd[2] + fd[4]);
   const R m8 = (fd[5] + fd[7]) - (fd[6] + fd[8]);
-  // equilibrium moments (Eq. 14, alpha1 = 1, alpha2 = -3) minus those of the rest state
+  // equilibrium moments (Eq. 14, alpha1 = 1, alpha2 = -3) minus those of the rest state, and
+  // forcing moments (Eq. 15)
   const R r0 = d.rho0_s;
   const R r0p = r0 * inv_phi;
-  const R e1 = R(-2) * drho + R(3) * r0p * u2;
-  const R e2 = drho - R(3) * r0p * u2;
-  const R jxe = r0 * ux, jye = r0 * uy;
-  const R e7 = r0p * (ux * ux - uy * uy);
-  const R e8 = r0p * ux * uy;
-  // forcing moments (Eq. 15)
-  const R S1 = R(6) * r0p * (ux * Fx + uy * Fy);
+  const R r3 = R(3) * r0p;
+  const R e1 = fma_(r3, u2, R(-2) * drho);
+  const R e2 = fma_(-r3, u2, drho);
+  const R uF = uy * Fy;
+  const R S1 = R(6) * r0p * fma_(ux, Fx, uF);
   const R S3 = r0 * Fx, S5 = r0 * Fy;
-  const R S7 = R(2) * r0p * (ux * Fx - uy * Fy);
-  const R S8 = r0p * (ux * Fy + uy * Fx);
+  const R S7 = R(2) * r0p * fma_(ux, Fx, -uF);
+  const R S8 = r0p * fma_(ux, Fy, uy * Fx);
   // relaxation (Eq. 10): m* = m - s (m - meq) + (1 - s/2) S
-  const R p0 = drho;
-  const R p1 = m1 - d.s_e * (m1 - e1) + d.k_e * S1;
-  const R p2 = m2 - d.s_eps * (m2 - e2) - d.k_eps * S1;
-  const R p3 = jx - d.s_j * (jx - jxe) + d.k_j * S3;
-  const R p4 = m4 - d.s_q * (m4 + jxe) - d.k_q * S3;
-  const R p5 = jy - d.s_j * (jy - jye) + d.k_j * S5;
-  const R p6 = m6 - d.s_q * (m6 + jye) - d.k_q * S5;
-  const R p7 = m7 - d.s_v * (m7 - e7) + d.k_v * S7;
-  const R p8 = m8 - d.s_v * (m8 - e8) + d.k_v * S8;
+  const R p1 = fma_(d.k_e, S1, fma_(-d.s_e, m1 - e1, m1));
+  const R p2 = fma_(-d.k_eps, S1, fma_(-d.s_eps, m2 - e2, m2));
+  const R p3 = fma_(d.k_j, S3, fma_(-d.s_j, fma_(-r0, ux, jx), jx));
+  const R p4 = fma_(-d.k_q, S3, fma_(-d.s_q, fma_(r0, ux, m4), m4));
+  const R p5 = fma_(d.k_j, S5, fma_(-d.s_j, fma_(-r0, uy, jy), jy));
+  const R p6 = fma_(-d.k_q, S5, fma_(-d.s_q, fma_(r0, uy, m6), m6));
+  const R p7 = fma_(d.k_v, S7, fma_(-d.s_v, fma_(-r0p, fma_(ux, ux, -uy2), m7), m7));
+  const R p8 = fma_(d.k_v, S8, fma_(-d.s_v, fma_(-uy, r0p * ux, m8), m8));
   // f* = M^-1 m*
-  const R a0 = p0 * R(1.0 / 9.0);
-  const R a1 = p1 * R(1.0 / 36.0);
-  const R a2 = p2 * R(1.0 / 36.0);
-  const R a3 = p3 * R(1.0 / 6.0);
-  const R a4 = p4 * R(1.0 / 12.0);
-  const R a5 = p5 * R(1.0 / 6.0);
-  const R a6 = p6 * R(1.0 / 12.0);
-  const R a7 = p7 * R(0.25);
-  const R a8 = p8 * R(0.25);
-  const R axis = a0 - a1 - R(2) * a2;
-  const R diag = a0 + R(2) * a1 + a2;
-  fd[1] = axis + a3 - R(2) * a4 + a7;
-  fd[2] = axis + a5 - R(2) * a6 - a7;
-  fd[5] = diag + a3 + a4 + a5 + a6 + a8;
-  fd[6] = diag - a3 - a4 + a5 + a6 - a8;
-  fd[7] = diag - a3 - a4 - a5 - a6 + a8;
-  fd[8] = diag + a3 + a4 - a5 - a6 - a8;
+  const R w9 = R(1.0 / 9.0), w36 = R(1.0 / 36.0), w6 = R(1.0 / 6.0), w12 = R(1.0 / 12.0), w4 = R(0.25);
+  const R a1 = p1 * w36, a2 = p2 * w36, a4 = p4 * w12, a6 = p6 * w12;
+  const R axis = fma_(R(-2), a2, fma_(drho, w9, -a1));
+  const R diag = fma_(p2, w36, fma_(R(2), a1, drho * w9));
+  const R dp = fma_(p4, w12, fma_(p3, w6, diag)), dm = fma_(p4, -w12, fma_(p3, -w6, diag));
+  fd[1] = fma_(p7, w4, fma_(R(-2), a4, fma_(p3, w6, axis)));
+  fd[2] = fma_(p7, -w4, fma_(R(-2), a6, fma_(p5, w6, axis)));
+  fd[5] = fma_(p8, w4, fma_(p6, w12, fma_(p5, w6, dp)));
+  fd[6] = fma_(p8, -w4, fma_(p6, w12, fma_(p5, w6, dm)));
+  fd[7] = fma_(p8, w4, fma_(p6, -w12, fma_(p5, -w6, dm)));
+  fd[8] = fma_(p8, -w4, fma_(p6, -w12, fma_(p5, -w6, dp)));
   // f3, f4 and the rest population f0 are formed from the moments they must carry
   // (sum e_x f* = m3*, sum e_y f* = m5*, sum f* = rho): algebraically the same rows of
   // M^-1, but each moment then comes back up to one rounding instead of being scaled by
@@ -223,53 +239,36 @@ __device__ __forceinline__ void collide(const D &d, R phi, R inv_phi, R a, R b, 
   // of T itself does not enter; source moments N S~ = (0, d(T ux)/dt, d(T uy)/dt, 0, 0) from
   // Eq. (27) with d(T u)/dt = T0 (u - u_prev) + ((T - T0) u - (T - T0)_prev u_prev): the
   // difference of two nearly equal products T u is never formed
-  const R TuX = d.T0_s * ux + dTs * ux, TuY = d.T0_s * uy + dTs * uy;
-  const R CuX = d.C0_s * ux + dCs * ux, CuY = d.C0_s * uy + dCs * uy;
-  const R dux = ux - prev[2], duy = uy - prev[3];
-  const R pT = SC ? prev[0] * d.scale : prev[0], pC = SC ? prev[1] * d.scale : prev[1];
-  const R STx = d.T0_s * dux + (dTs * ux - pT * prev[2]), STy = d.T0_s * duy + (dTs * uy - pT * prev[3]);
-  const R SCx = d.C0_s * dux + (dCs * ux - pC * prev[2]), SCy = d.C0_s * duy + (dCs * uy - pC * prev[3]);
-  const R kh3 = !d.phi_field ? d.kh3_u : (d.model == 0 ? (d.c5v - R(4) * phi) : (d.c5v - R(4)) * phi);
+  const R kh3 = !d.phi_field ? d.kh3_u : (d.model == 0 ? fma_(R(-4), phi, d.c5v) : (d.c5v - R(4)) * phi);
   // Both scalars collide as increments: the moment changes n* - n = -Theta (n - n^eq) +
   // (I - Theta/2) S (the conserved zeroth moment does not change), taken back to populations by
   // N^-1 and added to the pulled ones.  The rest population then gives up exactly what the other
   // four gained, measured on their rounded values, so the stored sum (sigma T, phi C) keeps its
   // value up to one rounding per step instead of one per addition of the whole populations.
-  {
-    const R n1 = gd[1] - gd[3], n2 = gd[2] - gd[4];
-    const R n3 = R(-4) * gd[0] + gd[1] + gd[2] + gd[3] + gd[4];
-    const R n4 = gd[1] - gd[2] + gd[3] - gd[4];
-    const R c1 = d.k_za * STx - d.z_a * (n1 - TuX);
-    const R c2 = d.k_za * STy - d.z_a * (n2 - TuY);
-    const R c3 = -d.z_e * (n3 - d.kg3 * dTs);
-    const R c4 = -d.z_eps * n4;
-    const R a13 = R(0.05) * c3 + R(0.25) * c4, a24 = R(0.05) * c3 - R(0.25) * c4;
-    const R g1 = gd[1] + (a13 + half * c1), g3 = gd[3] + (a13 - half * c1);
-    const R g2 = gd[2] + (a24 + half * c2), g4 = gd[4] + (a24 - half * c2);
-    gd[0] = gd[0] - (((g1 - gd[1]) + (g2 - gd[2])) + ((g3 - gd[3]) + (g4 - gd[4])));
-    gd[1] = g1;
-    gd[2] = g2;
-    gd[3] = g3;
-    gd[4] = g4;
-  }
-  {
-    const R eD = d.e_D;
-    const R n1 = hd[1] - hd[3], n2 = hd[2] - hd[4];
-    const R n3 = R(-4) * hd[0] + hd[1] + hd[2] + hd[3] + hd[4];
-    const R n4 = hd[1] - hd[2] + hd[3] - hd[4];
-    const R c1 = d.k_eD * SCx - eD * (n1 - CuX);
-    const R c2 = d.k_eD * SCy - eD * (n2 - CuY);
-    const R c3 = -d.e_e * (n3 - kh3 * dCs);
-    const R c4 = -d.e_eps * n4;
-    const R a13 = R(0.05) * c3 + R(0.25) * c4, a24 = R(0.05) * c3 - R(0.25) * c4;
-    const R h1 = hd[1] + (a13 + half * c1), h3 = hd[3] + (a13 - half * c1);
-    const R h2 = hd[2] + (a24 + half * c2), h4 = hd[4] + (a24 - half * c2);
-    hd[0] = hd[0] - (((h1 - hd[1]) + (h2 - hd[2])) + ((h3 - hd[3]) + (h4 - hd[4])));
-    hd[1] = h1;
-    hd[2] = h2;
-    hd[3] = h3;
-    hd[4] = h4;
-  }
+  // s: T - T0 or C - C0; s0: T0 or C0; ps: the previous step's s; k: 1 - s_1/2; z, ze, zeps: the
+  // rates; k3: factor of the energy moment's equilibrium
+  auto scalar = [&](R *q, R s, R s0, R ps, R k, R z, R ze, R zeps, R k3) {
+#pragma clang fp contract(off)
+    const R sx = s * ux, sy = s * uy;
+    const R Sx = fma_(s0, dux, fma_(-prev[2], ps, sx)), Sy = fma_(s0, duy, fma_(-prev[3], ps, sy));
+    const R n1 = q[1] - q[3], n2 = q[2] - q[4];
+    const R n3 = fma_(R(-4), q[0], q[1]) + q[2] + q[3] + q[4];
+    const R n4 = q[1] - q[2] + q[3] - q[4];
+    const R c1 = fma_(k, Sx, -(z * (n1 - fma_(s0, ux, sx))));
+    const R c2 = fma_(k, Sy, -(z * (n2 - fma_(s0, uy, sy))));
+    const R c3 = -ze * fma_(-k3, s, n3);
+    const R c4 = R(-0.25) * (zeps * n4);
+    const R a13 = fma_(R(0.05), c3, c4), a24 = fma_(R(0.05), c3, -c4);
+    const R q1 = q[1] + fma_(half, c1, a13), q3 = q[3] + fma_(-half, c1, a13);
+    const R q2 = q[2] + fma_(half, c2, a24), q4 = q[4] + fma_(-half, c2, a24);
+    q[0] = q[0] - (((q1 - q[1]) + (q2 - q[2])) + ((q3 - q[3]) + (q4 - q[4])));
+    q[1] = q1;
+    q[2] = q2;
+    q[3] = q3;
+    q[4] = q4;
+  };
+  scalar(gd, dTs, d.T0_s, SC ? prev[0] * d.scale : prev[0], d.k_za, d.z_a, d.z_e, d.z_eps, d.kg3);
+  scalar(hd, dCs, d.C0_s, SC ? prev[1] * d.scale : prev[1], d.k_eD, d.e_D, d.e_e, d.e_eps, kh3);
   prev[0] = dT;
   prev[1] = dC;
   prev[2] = ux;
@@ -796,14 +795,11 @@ __device__ __forceinline__ void wall_rules(const Desc<R> &d, bool okxm, bool okx
 }
 
 // Pull streaming of node (x, y) from the post-collision populations of the previous level
-// in global memory (Eq. 11), before the wall rules: a link that crosses a wall pulls the opposite
-// population of this node.  INTERIOR: every upstream node lies inside the domain (no wall link,
-// no wrap).
+// in global memory (Eq. 11), before the wall rules, as stored: f0..f8, g0..g4, h0..h4 into q.  A
+// link that crosses a wall pulls the opposite population of this node.  INTERIOR: every
+// upstream node lies inside the domain (no wall link, no wrap).
 template <typename S, int CP, bool INTERIOR>
-__device__ __forceinline__ void gather_pulls(const Desc<typename St<S>::R> &d, const StepRes &rs, int x, int y,
-                                              typename St<S>::R *fd, typename St<S>::R *gd,
-                                              typename St<S>::R *hd) {
-  using R = typename St<S>::R;
+__device__ __forceinline__ void pull_raw(const Desc<typename St<S>::R> &d, const StepRes &rs, int x, int y, S *q) {
   using IO = PopIO<S, CP>;
   constexpr uint32_t ES = sizeof(S);
   const uint32_t PB = (uint32_t)d.plane * ES;        // plane stride in bytes (populations)
@@ -833,31 +829,45 @@ __device__ __forceinline__ void gather_pulls(const Desc<typename St<S>::R> &d, c
   };
   // for INTERIOR the plane is i itself
   auto plane = [&](int i, int o) -> uint32_t { return (uint32_t)(INTERIOR ? i : (i < o ? i : o)) * PB; };
-  const R is = d.inv_scale;
   const uint32_t o1 = pull(okxm, r0 + xm, 1, 3), o3 = pull(okxp, r0 + xp, 3, 1);
   const uint32_t o2 = pull(okym, rm + x, 2, 4), o4 = pull(okyp, rp + x, 4, 2);
   const uint32_t o5 = pull(ok5, rm + xm, 5, 7), o7 = pull(ok7, rp + xp, 7, 5);
   const uint32_t o6 = pull(ok6, rm + xp, 6, 8), o8 = pull(ok8, rp + xm, 8, 6);
-  fd[0] = to_real<S>(IO::ld(rs.src, c * ES, 0), is);
-  fd[1] = to_real<S>(IO::ld(rs.src, o1, plane(1, 3)), is);
-  fd[2] = to_real<S>(IO::ld(rs.src, o2, plane(2, 4)), is);
-  fd[3] = to_real<S>(IO::ld(rs.src, o3, plane(3, 1)), is);
-  fd[4] = to_real<S>(IO::ld(rs.src, o4, plane(4, 2)), is);
-  fd[5] = to_real<S>(IO::ld(rs.src, o5, plane(5, 7)), is);
-  fd[6] = to_real<S>(IO::ld(rs.src, o6, plane(6, 8)), is);
-  fd[7] = to_real<S>(IO::ld(rs.src, o7, plane(7, 5)), is);
-  fd[8] = to_real<S>(IO::ld(rs.src, o8, plane(8, 6)), is);
+  q[0] = IO::ld(rs.src, c * ES, 0);
+  q[1] = IO::ld(rs.src, o1, plane(1, 3));
+  q[2] = IO::ld(rs.src, o2, plane(2, 4));
+  q[3] = IO::ld(rs.src, o3, plane(3, 1));
+  q[4] = IO::ld(rs.src, o4, plane(4, 2));
+  q[5] = IO::ld(rs.src, o5, plane(5, 7));
+  q[6] = IO::ld(rs.src, o6, plane(6, 8));
+  q[7] = IO::ld(rs.src, o7, plane(7, 5));
+  q[8] = IO::ld(rs.src, o8, plane(8, 6));
   // g and h use the same offsets from planes 9.. and 14..
-  gd[0] = to_real<S>(IO::ld(rs.src, c * ES, 9 * PB), is);
-  hd[0] = to_real<S>(IO::ld(rs.src, c * ES, 14 * PB), is);
-  gd[1] = to_real<S>(IO::ld(rs.src, o1, 9 * PB + plane(1, 3)), is);
-  hd[1] = to_real<S>(IO::ld(rs.src, o1, 14 * PB + plane(1, 3)), is);
-  gd[2] = to_real<S>(IO::ld(rs.src, o2, 9 * PB + plane(2, 4)), is);
-  hd[2] = to_real<S>(IO::ld(rs.src, o2, 14 * PB + plane(2, 4)), is);
-  gd[3] = to_real<S>(IO::ld(rs.src, o3, 9 * PB + plane(3, 1)), is);
-  hd[3] = to_real<S>(IO::ld(rs.src, o3, 14 * PB + plane(3, 1)), is);
-  gd[4] = to_real<S>(IO::ld(rs.src, o4, 9 * PB + plane(4, 2)), is);
-  hd[4] = to_real<S>(IO::ld(rs.src, o4, 14 * PB + plane(4, 2)), is);
+  q[9] = IO::ld(rs.src, c * ES, 9 * PB);
+  q[14] = IO::ld(rs.src, c * ES, 14 * PB);
+  q[10] = IO::ld(rs.src, o1, 9 * PB + plane(1, 3));
+  q[15] = IO::ld(rs.src, o1, 14 * PB + plane(1, 3));
+  q[11] = IO::ld(rs.src, o2, 9 * PB + plane(2, 4));
+  q[16] = IO::ld(rs.src, o2, 14 * PB + plane(2, 4));
+  q[12] = IO::ld(rs.src, o3, 9 * PB + plane(3, 1));
+  q[17] = IO::ld(rs.src, o3, 14 * PB + plane(3, 1));
+  q[13] = IO::ld(rs.src, o4, 9 * PB + plane(4, 2));
+  q[18] = IO::ld(rs.src, o4, 14 * PB + plane(4, 2));
+}
+
+// pull_raw as numbers
+template <typename S, int CP, bool INTERIOR>
+__device__ __forceinline__ void gather_pulls(const Desc<typename St<S>::R> &d, const StepRes &rs, int x, int y,
+                                             typename St<S>::R *fd, typename St<S>::R *gd, typename St<S>::R *hd) {
+  S q[NPOP];
+  pull_raw<S, CP, INTERIOR>(d, rs, x, y, q);
+#pragma unroll
+  for (int i = 0; i < 9; ++i) fd[i] = to_real<S>(q[i], d.inv_scale);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    gd[i] = to_real<S>(q[9 + i], d.inv_scale);
+    hd[i] = to_real<S>(q[14 + i], d.inv_scale);
+  }
 }
 
 // gather_pulls with the wall rules
@@ -1467,6 +1477,250 @@ __global__ void __launch_bounds__(TS::THREADS, TS::MIN_WAVES_PER_EU) step3_kerne
   int tx, ty;
   tile_of(b, ntx, (int)gridDim.x / ntx, sw, tx, ty);
   three_step_tile<S, CP, TS>(d, tx * TS::W, ty * TS::H, parity, lpop);
+}
+
+// ---------------------------------------------------------------- large lattices: the march
+// lane i takes the value of lane i - 1 (from_left) or i + 1 (from_right); the first or last lane
+// takes 0.  All 64 lanes must be active (a lane that is not gives 0).
+__device__ __forceinline__ float from_left(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_right(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
+}
+typedef int Int2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double from_left(double v) {
+  Int2 p = __builtin_bit_cast(Int2, v);
+  p[0] = __builtin_amdgcn_update_dpp(0, p[0], 0x138, 0xf, 0xf, true);
+  p[1] = __builtin_amdgcn_update_dpp(0, p[1], 0x138, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, p);
+}
+__device__ __forceinline__ double from_right(double v) {
+  Int2 p = __builtin_bit_cast(Int2, v);
+  p[0] = __builtin_amdgcn_update_dpp(0, p[0], 0x130, 0xf, 0xf, true);
+  p[1] = __builtin_amdgcn_update_dpp(0, p[1], 0x130, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, p);
+}
+
+// A wave takes a strip of 64 columns and marches up a chunk of its rows, one column per lane,
+// updating K time levels in a pipeline: when level l has updated row r, level l + 1 updates row
+// r - 1 from what the wave still holds of level l.  No level goes to global memory but the first's
+// input and the last's output, rows are recomputed only at the ends of a chunk (K - 1 each side of
+// the chunk, against K - 1 rows and columns around every tile of step3_kernel), the neighbour
+// columns come from the neighbour lanes, and the next row is loaded while the levels above the
+// first are computed.  A strip stores its inner 64 - 2 (K - 1) columns; the outer ones are spoilt
+// one more per level from the edge inward.
+// Held of a level: of its last two rows the populations that move up (f2, f5, f6, g2, h2); of the
+// last one those that stay in their row (f0, f1, f3, g0, g1, g3, h0, h1, h3), the fields and
+// the porosity.  The first NL of these 14 lie in LDS (own lane's slot; the neighbour lane's is the
+// shift), the rest in registers: so many that FP64 keeps two waves per SIMD (244 VGPRs, 74 KB of
+// LDS a work-group) and FP32 four (120 VGPRs, 40 KB).  FP32 and FP64 storage.
+// Walls half a spacing outside: beyond a wall the ghost column's lane (or the ghost row) is given
+// what a bounce-back returns, so that every node pulls alike; the fixed-value and moving-wall
+// terms are added to the pulls (wall_rules).
+// The four waves of a work-group take neighbouring strips and meet at a barrier every row: their
+// rows lie side by side in the same cache lines.
+// Bound: FP64 by memory (1.7 GB a launch at 2048^2 in 410 us; its access pattern alone takes 335
+// us), FP32 by instruction issue (VALU busy 0.76, 331 instructions per level and node before the
+// steady loop was split off).  Measured (2048^2 banded cavity): FP64 39.5-41.6 GLUPS against 30.4
+// for step3_kernel, FP32 72.2-73.4 against 63.8; without the barrier FP32 62.5, with one wave per
+// SIMD (all state in registers) FP64 29.6.  FP16 storage (three levels) lost 2% to step2_kernel.
+template <typename S>
+struct March {      // FP32
+  static constexpr int K = 4, NL = 13, WAVES_PER_EU = 4;
+};
+template <>
+struct March<double> {
+  static constexpr int K = 4, NL = 12, WAVES_PER_EU = 2;
+};
+constexpr int kMarchWaves = 4;                               // strips of a work-group
+template <typename S>
+constexpr int kMarchStrip = 64 - 2 * (March<S>::K - 1);      // columns a strip stores
+
+template <typename R>
+struct MarchRows {
+  R up0[5], up1[5], row[14];
+};
+
+template <typename S>
+__global__ void __launch_bounds__(64 * kMarchWaves, March<S>::WAVES_PER_EU)
+    march_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int nstrips, int chunk, int parity) {
+  using R = typename St<S>::R;
+  constexpr int CP = CP_RESIDENT;
+  using FIO = FieldIO<S, CP>;
+  constexpr uint32_t RS = sizeof(R);
+  constexpr int K = March<S>::K, NL = March<S>::NL, H = K - 1, V = kMarchStrip<S>;
+  __shared__ R held[kMarchWaves * H * NL * 64 + 2];
+  const Desc<R> &d = *dp;
+  const int job = xcd_remap(blockIdx.x, gridDim.x);
+  const int groups = (nstrips + kMarchWaves - 1) / kMarchWaves;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  const int cy = job / groups, strip = (job - cy * groups) * kMarchWaves + wave;
+  const int nx = d.nx, ny = d.ny, pitch = d.pitch;
+  const uint32_t PR = (uint32_t)d.plane * RS;
+  const int cur = (d.base_parity ^ parity) & 1;
+  StepRes rs = step_resources<S>(d, cur);
+  rs.d4 = make_rsrc((parity & 1) ? d.d4b : d.d4, ND4 * PR);
+  StepRes ws = rs;
+  ws.d4 = make_rsrc((parity & 1) ? d.d4 : d.d4b, ND4 * PR);
+  const uint32_t step = d.counter[cur];
+  if (job == 0 && threadIdx.x == 0) d.counter[cur ^ 1] = step + (uint32_t)K;
+  if (strip >= nstrips) return;            // (a wave that has ended counts as arrived at the barriers)
+
+  const bool perx = d.perx != 0, pery = d.pery != 0;
+  const int x0 = strip * V - H, xv = x0 + lane;
+  // the lane's column: wrapped across periodic sides; beyond a wall the nearest one (its values are
+  // never used there, the ghost's are set below)
+  const int x = perx ? (xv < 0 ? xv + nx : xv >= nx ? xv - nx : xv) : min(max(xv, 0), nx - 1);
+  const bool walls_x = !perx && (x0 <= 0 || x0 + 63 >= nx - 1);  // the strip holds a node at a wall
+  const bool inner_x = x0 >= 1 && x0 + 64 <= nx - 1;             // every pull of level 1 stays inside in x
+  const bool ghost_l = !perx && xv == -1, ghost_r = !perx && xv == nx;
+  const bool mine = lane >= H && lane < H + V && xv < nx;
+  const int ya = cy * chunk, yb = min(ya + chunk, ny);
+  // rows of level l: [first(l), last(l)), rows beyond a periodic side counted on
+  auto first = [&](int l) { return pery ? ya - (K - l) : max(0, ya - (K - l)); };
+  auto last = [&](int l) { return pery ? yb + (K - l) : min(ny, yb + (K - l)); };
+  auto wrap = [&](int r) { return !pery ? r : r < 0 ? r + ny : r >= ny ? r - ny : r; };
+
+  MarchRows<R> st[H] = {};
+  R *const own = held + 1 + wave * (H * NL * 64) + lane;
+  S in[NPOP];
+  R in4[4], in_phi;
+  auto load = [&](int r) {
+    const int y = wrap(r);
+    if (inner_x && y >= 1 && y < ny - 1) pull_raw<S, CP, true>(d, rs, x, y, in);
+    else pull_raw<S, CP, false>(d, rs, x, y, in);
+    const uint32_t c = ((uint32_t)y * pitch + x) * RS;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) in4[k] = FIO::ld(rs.d4, c, (uint32_t)k * PR);
+    in_phi = d.phi_field ? FIO::ld(rs.phi, c, 0) : d.phi_u;
+  };
+  auto rules = [&](int y, R *fd, R *gd, R *hd) {
+    if (!(walls_x || (!pery && (y == 0 || y == ny - 1)))) return;
+    const bool okxm = (x > 0) | perx, okxp = (x < nx - 1) | perx;
+    const bool okym = (y > 0) | pery, okyp = (y < ny - 1) | pery;
+    if (!(okxm & okxp & okym & okyp)) wall_rules(d, okxm, okxp, okym, okyp, fd, gd, hd);
+  };
+  auto update = [&](R phi, R *fd, R *gd, R *hd, R *prev) {
+    R a, b, ip;
+    porous_coeffs(d, phi, a, b, ip);
+    collide<R, kScaled<S>>(d, phi, ip, a, b, fd, gd, hd, prev);
+  };
+  // orders the LDS accesses of different lanes for the compiler (in hardware those of a wave are)
+  auto lanes_meet = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  // Level 1 at row r, level 2 at row r - 1, ...  FULL: every level has a row to update and level 1 a
+  // next one, which leaves all copies out that would merge the two cases of a condition
+  auto iterate = [&](int r, auto full) {
+    constexpr bool FULL = decltype(full)::value;
+    __builtin_amdgcn_s_barrier();
+    static_assert(!kScaled<S>, "FP32 and FP64 storage");
+    R fd[9], gd[5], hd[5], prev[4], phi = in_phi;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) fd[i] = to_real<S>(in[i], R(0));
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      gd[i] = to_real<S>(in[9 + i], R(0));
+      hd[i] = to_real<S>(in[14 + i], R(0));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) prev[i] = in4[i];
+    if (FULL || r < last(1)) {
+      const int y = wrap(r);
+      rules(y, fd, gd, hd);
+      update(phi, fd, gd, hd, prev);
+      if (FULL || r + 1 < last(1)) load(r + 1);
+    }
+#pragma unroll
+    for (int l = 1; l < K; ++l) {
+      MarchRows<R> &s = st[l - 1];
+      const int rp = r - (l - 1);           // the row level l has just updated (fd, gd, hd, prev, phi)
+      if (walls_x) {
+        // the ghost columns; every lane takes part in the shifts
+        const R l7 = from_right(fd[7]), l3 = from_right(fd[3]), l6 = from_right(s.up0[2]);
+        const R lg = from_right(gd[3]), lh = from_right(hd[3]);
+        const R r8 = from_left(fd[8]), r1 = from_left(fd[1]), r5 = from_left(s.up0[1]);
+        const R rg = from_left(gd[1]), rh = from_left(hd[1]);
+        s.up0[1] = ghost_l ? l7 : s.up0[1];
+        fd[1] = ghost_l ? l3 : fd[1];
+        fd[8] = ghost_l ? l6 : fd[8];
+        gd[1] = ghost_l ? lg : gd[1];
+        hd[1] = ghost_l ? lh : hd[1];
+        s.up0[2] = ghost_r ? r8 : s.up0[2];
+        fd[3] = ghost_r ? r1 : fd[3];
+        fd[7] = ghost_r ? r5 : fd[7];
+        gd[3] = ghost_r ? rg : gd[3];
+        hd[3] = ghost_r ? rh : hd[3];
+      }
+      if (!FULL && !pery && rp == 0) {      // the ghost row below the bottom wall
+        s.up0[0] = fd[4];
+        s.up0[1] = from_right(fd[7]);
+        s.up0[2] = from_left(fd[8]);
+        s.up0[3] = gd[4];
+        s.up0[4] = hd[4];
+      }
+      if (!FULL && !pery && rp == ny) {     // the ghost row above the top wall
+        fd[4] = s.up0[0];
+        fd[7] = from_left(s.up0[1]);
+        fd[8] = from_right(s.up0[2]);
+        gd[4] = s.up0[3];
+        hd[4] = s.up0[4];
+      }
+      // the pulls of level l + 1 in row rp - 1
+      const int at = (l - 1) * NL * 64;
+      auto mid = [&](int i) -> R { return i < NL ? own[at + i * 64] : s.row[i]; };
+      auto left = [&](int i) -> R { return i < NL ? own[at + i * 64 - 1] : from_left(s.row[i]); };
+      auto right = [&](int i) -> R { return i < NL ? own[at + i * 64 + 1] : from_right(s.row[i]); };
+      auto hold = [&](int i, R v) {
+        if (i < NL) own[at + i * 64] = v;
+        else s.row[i] = v;
+      };
+      const R pf[9] = {mid(0), left(1), s.up1[0], right(2), fd[4], from_left(s.up1[1]), from_right(s.up1[2]),
+                       from_right(fd[7]), from_left(fd[8])};
+      const R pg[5] = {mid(3), left(4), s.up1[3], right(5), gd[4]};
+      const R ph[5] = {mid(6), left(7), s.up1[4], right(8), hd[4]};
+      const R pp[4] = {mid(9), mid(10), mid(11), mid(12)}, pphi = mid(13);
+      lanes_meet();
+      // level l's rows move on
+      const R up[5] = {fd[2], fd[5], fd[6], gd[2], hd[2]};
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        s.up1[i] = s.up0[i];
+        s.up0[i] = up[i];
+      }
+      const R row[14] = {fd[0], fd[1], fd[3], gd[0], gd[1], gd[3], hd[0],
+                         hd[1], hd[3], prev[0], prev[1], prev[2], prev[3], phi};
+#pragma unroll
+      for (int i = 0; i < 14; ++i) hold(i, row[i]);
+      lanes_meet();
+#pragma unroll
+      for (int i = 0; i < 9; ++i) fd[i] = pf[i];
+#pragma unroll
+      for (int i = 0; i < 5; ++i) {
+        gd[i] = pg[i];
+        hd[i] = ph[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) prev[i] = pp[i];
+      phi = pphi;
+      const int rn = rp - 1;
+      if (FULL || (rn >= first(l + 1) && rn < last(l + 1))) {
+        const int y = wrap(rn);
+        rules(y, fd, gd, hd);
+        if (l + 1 < K || mine) update(phi, fd, gd, hd, prev);
+        if (l + 1 == K && mine) store_node<S, CP>(d, ws, (uint32_t)y * pitch + x, step, fd, gd, hd, prev);
+      }
+    }
+  };
+  int r = first(1);
+  load(r);
+  const int end = yb + H, full0 = max(r, ya + H), full1 = last(1) - 1;
+  for (; r < full0 && r < end; ++r) iterate(r, std::false_type());
+  for (; r < full1; ++r) iterate(r, std::true_type());
+  for (; r < end; ++r) iterate(r, std::false_type());
 }
 
 // ---------------------------------------------------------------- small lattices: a region per work-group
@@ -2203,6 +2457,33 @@ int launch_step3(int prec, const void *desc, const void *ddev, int cp, int parit
       return step3_t<float, ThreeStep<float>>(desc, ddev, cp, parity, sw, stream);
     default: return (int)hipErrorInvalidValue;   // FP16 storage: one or two steps per launch
   }
+}
+
+template <typename S>
+static int march_t(const void *desc, const void *ddev, int parity, int chunk, void *stream) {
+  const auto &d = *(const Desc<typename St<S>::R> *)desc;
+  // one wrap across a periodic side, walls half a spacing outside
+  if (d.nee || d.nx < 128 || d.ny < 16 || chunk < 1) return (int)hipErrorInvalidValue;
+  const int nstrips = (d.nx + kMarchStrip<S> - 1) / kMarchStrip<S>, nch = (d.ny + chunk - 1) / chunk;
+  const int groups = (nstrips + kMarchWaves - 1) / kMarchWaves;
+  hipLaunchKernelGGL((march_kernel<S>), dim3(groups * nch), dim3(64 * kMarchWaves), 0, (hipStream_t)stream,
+                     (const Desc<typename St<S>::R> *)ddev, nstrips, chunk, parity);
+  return (int)hipGetLastError();
+}
+
+int launch_march(int prec, const void *desc, const void *ddev, int parity, int chunk, void *stream) {
+  switch (prec) {
+    case PREC_FP64: return march_t<double>(desc, ddev, parity, chunk, stream);
+    case PREC_FP32: return march_t<float>(desc, ddev, parity, chunk, stream);
+    default: return (int)hipErrorInvalidValue;   // FP16 storage: one or two steps per launch
+  }
+}
+
+void march_shape(int prec, int *steps, int *group_columns, int *groups_per_cu) {
+  *steps = prec == PREC_FP64 ? March<double>::K : March<float>::K;
+  *group_columns = kMarchWaves * (prec == PREC_FP64 ? kMarchStrip<double> : kMarchStrip<float>);
+  // work-groups of four waves, one per SIMD, that a CU holds
+  *groups_per_cu = prec == PREC_FP64 ? March<double>::WAVES_PER_EU : March<float>::WAVES_PER_EU;
 }
 
 template <typename S, bool NEE, typename RG>

@@ -29,7 +29,8 @@ EXPORTS = (
     "lbm_set_state",
     "lbm_set_tile", "lbm_get_tile", "lbm_set_cache_policy", "lbm_get_cache_policy", "lbm_set_strip_width",
     "lbm_get_strip_width", "lbm_set_tile_rows", "lbm_get_tile_rows", "lbm_set_steps_per_launch",
-    "lbm_get_steps_per_launch", "lbm_get_region_steps", "lbm_set_graph_chunk",
+    "lbm_get_steps_per_launch", "lbm_get_region_steps", "lbm_get_march_steps",
+    "lbm_set_graph_chunk",
     "lbm_autotune", "lbm_last_error", "lbm_destroy",
     "lbm_batch_create", "lbm_batch_attach", "lbm_batch_detach", "lbm_batch_step", "lbm_batch_autotune",
     "lbm_batch_set_tile", "lbm_batch_size", "lbm_batch_destroy",
@@ -127,6 +128,8 @@ def lib():
         L.lbm_get_steps_per_launch.restype = ctypes.c_int32
         L.lbm_get_region_steps.argtypes = [_VP]
         L.lbm_get_region_steps.restype = ctypes.c_int32
+        L.lbm_get_march_steps.argtypes = [_VP]
+        L.lbm_get_march_steps.restype = ctypes.c_int32
         L.lbm_set_tile.argtypes = [_VP, ctypes.c_int32, ctypes.c_int32]
         L.lbm_set_graph_chunk.argtypes = [_VP, ctypes.c_int32]
         L.lbm_get_tile.argtypes = [_VP, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
@@ -334,6 +337,11 @@ class Solver:
         """Steps per launch of the region launch of small lattices, 0 where it is not in effect
         (see include/lbm.h)."""
         return int(lib().lbm_get_region_steps(self._h))
+
+    def get_march_steps(self) -> int:
+        """Steps per launch of the march of large lattices, 0 where it is not in effect (see
+        include/lbm.h)."""
+        return int(lib().lbm_get_march_steps(self._h))
 
     def get_tile(self):
         a, b = ctypes.c_int32(), ctypes.c_int32()

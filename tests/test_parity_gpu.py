@@ -510,6 +510,39 @@ def test_region_launch_matches_one_step(prec, nx, ny, walls):
     ref.close()
 
 
+@pytest.mark.parametrize("prec,nx,ny,walls", [
+    ("fp32", 1281, 1297, "half_way"), ("fp32", 1281, 1297, "periodic_x"), ("fp32", 1400, 1190, "periodic_y"),
+    ("fp32", 300, 6007, "half_way"), ("fp32", 6000, 301, "periodic"), ("fp32", 1392, 1303, "periodic_x"),
+    ("fp64", 1024, 1000, "half_way"), ("fp64", 1045, 1011, "periodic_x"), ("fp64", 1160, 1100, "periodic_y"),
+    ("fp64", 200, 5001, "periodic"), ("fp64", 4007, 260, "half_way")])
+def test_march_matches_one_step(prec, nx, ny, walls):
+    """The march of large lattices (the default there) against one step per launch, bit for bit:
+    porosity field, moving lids, both wall kinds, strips and chunks cut by every side (1392 and 1160
+    columns: whole work-groups of strips), step counts that are no
+    multiple of the launch's, plain launches and graph replays."""
+    Solver = _solver()
+    sides = {"half_way": ("hot", "cold", "adiabatic", "hot"), "periodic_x": ("periodic", "periodic", "cold", "adiabatic"),
+             "periodic_y": ("adiabatic", "cold", "periodic", "periodic"), "periodic": ("periodic",) * 4}[walls]
+    lid = [0.0 if k == "periodic" else u for k, u in zip(sides, (0.01, -0.01, 0.015, 0.02))]
+    p = workloads.cavity_params(nx=nx, ny=ny, sides=sides, Ra=1e6, wall_u=tuple(lid), g_ext=(1e-7, 0.0))
+    rng = np.random.default_rng([nx, ny])
+    kw = dict(phi=rng.uniform(0.4, 0.8, (ny, nx)), T=rng.uniform(0.4, 0.6, (ny, nx)), C=rng.uniform(0.4, 0.6, (ny, nx)))
+    ref = Solver(p, precision=prec, **kw)
+    ref.set_steps_per_launch(1)
+    assert ref.get_march_steps() == 0
+    ref.step(23)
+    want = ref.get_state()
+    ref.close()
+    for chunk in (0, 8):
+        s = Solver(p, precision=prec, **kw)
+        s.set_graph_chunk(chunk)
+        assert s.get_march_steps() == 4
+        s.step(23)
+        d = _state_diff(s.get_state(), want)
+        assert d is None, (chunk, d)
+        s.close()
+
+
 def test_graph_replays_match_plain_launches():
     """lbm_step uses a captured graph for chunks of 64 steps; replays interleaved with other
     work must give the same state as one launch per step."""

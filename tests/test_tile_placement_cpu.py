@@ -12,6 +12,7 @@ and that a tile the kernel treats as interior holds no boundary node in its regi
 ones check the region bookkeeping of three steps per launch and that the order in which a launch
 visits its tiles (row by row or in vertical strips) covers every tile once.
 """
+import numpy as np
 import pytest
 
 # two-step tiles: 64 x 8 (FP32, FP16 storage) and 32 x 8 (FP64)
@@ -281,3 +282,97 @@ def test_region_tile_index_by_multiplication():
         inv = ((1 << 32) + ntx - 1) // ntx
         for b in list(range(0, 40 * ntx, 7)) + [100 * ntx - 1, 100 * ntx]:
             assert (b * inv) >> 32 == b // ntx
+
+
+# ------------------------------------------------------------ march (large lattices)
+
+E9 = ((0, 0), (1, 0), (0, 1), (-1, 0), (0, -1), (1, 1), (-1, 1), (-1, -1), (1, -1))
+OPP = (0, 3, 4, 1, 2, 7, 8, 5, 6)
+
+
+def _collided(q, mix):
+    return np.einsum("ij,j...->i...", mix, q)
+
+
+def _pull(q, nx, ny, perx, pery):
+    """Pulls of every node, across a wall the node's own opposite population."""
+    out = np.empty_like(q)
+    for i, (ex, ey) in enumerate(E9):
+        out[i] = np.roll(q[i], (ey, ex), (0, 1))
+        x, y = np.arange(nx), np.arange(ny)
+        wall = np.zeros((ny, nx), bool)
+        if not perx:
+            wall |= ((x - ex < 0) | (x - ex >= nx))[None, :]
+        if not pery:
+            wall |= ((y - ey < 0) | (y - ey >= ny))[:, None]
+        out[i][wall] = q[OPP[i]][wall]
+    return out
+
+
+def _march(q, K, W, chunk, perx, pery, mix):
+    """The march's bookkeeping with strips of W lanes: what a strip holds of each level, the shifts
+    between lanes, ghost columns and ghost rows, chunk ends (nine populations, a linear collision)."""
+    ny, nx = q.shape[1:]
+    H, V = K - 1, W - 2 * (K - 1)
+    pulled, out = _pull(q, nx, ny, perx, pery), np.full_like(q, np.nan)
+
+    def left(v):
+        return np.concatenate(([0.0], v[:-1]))
+
+    def right(v):
+        return np.concatenate((v[1:], [0.0]))
+    for strip in range(-(-nx // V)):
+        xv = strip * V - H + np.arange(W)
+        x = xv % nx if perx else np.clip(xv, 0, nx - 1)
+        gl, gr = (xv == -1) & (not perx), (xv == nx) & (not perx)
+        mine = (np.arange(W) >= H) & (np.arange(W) < H + V) & (xv < nx)
+        for ya in range(0, ny, chunk):
+            yb = min(ya + chunk, ny)
+
+            def first(lv):
+                return ya - (K - lv) if pery else max(0, ya - (K - lv))
+
+            def last(lv):
+                return yb + (K - lv) if pery else min(ny, yb + (K - lv))
+            up0, up1, row = (np.full((H, 3, W), np.nan) for _ in range(3))
+            for r in range(first(1), yb + H):
+                f = np.full((9, W), np.nan)
+                if r < last(1):
+                    f = _collided(pulled[:, r % ny, :][:, x], mix)
+                for lv in range(1, K):
+                    a, rp = lv - 1, r - (lv - 1)
+                    if not perx:
+                        f = f.copy()
+                        l7, l3, l6, r8, r1, r5 = (right(f[7]), right(f[3]), right(up0[a, 2]), left(f[8]), left(f[1]),
+                                                  left(up0[a, 1]))
+                        up0[a, 1][gl], f[1][gl], f[8][gl] = l7[gl], l3[gl], l6[gl]
+                        up0[a, 2][gr], f[3][gr], f[7][gr] = r8[gr], r1[gr], r5[gr]
+                    if not pery and rp == 0:
+                        up0[a] = f[4], right(f[7]), left(f[8])
+                    if not pery and rp == ny:
+                        f[4], f[7], f[8] = up0[a, 0], left(up0[a, 1]), right(up0[a, 2])
+                    p = np.stack((row[a, 0], left(row[a, 1]), up1[a, 0], right(row[a, 2]), f[4], left(up1[a, 1]),
+                                  right(up1[a, 2]), right(f[7]), left(f[8])))
+                    up1[a] = up0[a]
+                    up0[a], row[a] = f[[2, 5, 6]], f[[0, 1, 3]]
+                    f = p
+                    rn = rp - 1
+                    if first(lv + 1) <= rn < last(lv + 1):
+                        f = _collided(f, mix)
+                        if lv + 1 == K:
+                            out[:, rn, xv[mine]] = f[:, mine]
+    return out
+
+
+@pytest.mark.parametrize("K", [3, 4])
+@pytest.mark.parametrize("perx,pery", [(False, False), (True, False), (False, True), (True, True)])
+def test_march_moves_what_one_step_moves(K, perx, pery):
+    rng = np.random.default_rng(K)
+    mix = rng.uniform(-1, 1, (9, 9)) / 3
+    for W, nx, ny, chunk in ((12, 6, 9, 4), (12, 13, 11, 3), (12, 18, 8, 8), (16, 31, 17, 5), (16, 40, 21, 10)):
+        q = rng.uniform(-1, 1, (9, ny, nx))
+        want = q
+        for _ in range(K):
+            want = _collided(_pull(want, nx, ny, perx, pery), mix)
+        got = _march(q, K, W, chunk, perx, pery, mix)
+        np.testing.assert_allclose(got, want, rtol=0, atol=1e-13, err_msg=str((W, nx, ny, chunk)))

@@ -298,18 +298,21 @@ void lbm_destroy(struct lbm_ctx *c);
 
 /* ---- batched stepping of many independent cavities --------------------------------
  * A batch advances every attached context (any size, parameters and precision).  The
- * attached contexts are split per precision and size class (width <= 64, <= 128, <= 256 or
- * wider; attach order within a class) into groups whose step touches at most 200 MB together
+ * attached contexts are split per precision and launch choice (below; ordered by width, attach
+ * order within a size class) into groups whose step touches at most 200 MB together
  * (a larger context is a group of its own); each group advances `chunk` steps before the next
- * group starts, so its data stays in the 256 MB Infinity Cache from step to step.  With an
+ * group starts, so its data stays in the 256 MB Infinity Cache from step to step (groups that
+ * fit 200 MB together, such as small ones of two precisions, advance side by side).  With an
  * even chunk that is a multiple of 4 a launch advances two steps (the two-step kernel over
  * tiles of the group's shape: 64 x 8, 32 x 16 or 32 x 8 nodes; FP64 32 x 8, 16 x 16 or 16 x 8),
- * otherwise one.  With a chunk that is a multiple of 12, FP32 and FP64 groups may instead
- * advance three steps per launch (shape index 3: the three-step kernel over the tiles of shape
- * 0).  Steps that do not fill a launch run one per launch.  A group takes the tile shape and
- * cache policy lbm_batch_autotune chose for
- * its precision and size class, or by default the first shape and the default cache-policy
- * rule of lbm_set_cache_policy for the group's bytes.  Each launch walks a device-side table of
+ * otherwise one.  With a chunk that is a multiple of 12, FP32 and FP64 groups advance three
+ * steps per launch (shape index 3: the three-step kernel over the tiles of shape 0; where
+ * threes leave one or two steps, the last four or two take two-step launches) unless the choice
+ * is a two-step shape.  A step that fills no launch runs alone.  The launch choice, tile shape and
+ * cache policy, is kept per precision and size class (width <= 64, <= 128, <= 256 or wider):
+ * what lbm_batch_autotune or lbm_batch_set_tile chose, by default three steps where they are
+ * possible, else the first shape, and the default cache-policy rule of lbm_set_cache_policy for
+ * the group's bytes.  Each launch walks a device-side table of
  * (cavity, tile) work items and the launches are replayed from a captured HIP graph;
  * attaching or detaching contexts rewrites the tables between replays and re-captures only
  * when the groups' number, precisions, shapes, policies or grids change.  Per-node arithmetic

@@ -11,6 +11,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <tuple>
 #include <type_traits>
 #include <vector>
 
@@ -1377,24 +1378,29 @@ LBM_API lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, int32_t *tx_out, int3
 }
 
 // ================================================================== batch
-// A group: cavities of one precision whose step touches at most kGroupBytes together, so
-// that they stay in the Infinity Cache while the group advances a chunk of steps; items
-// [first, first + count) of the precision's item table.
+// A group: cavities of one precision and one launch choice whose step touches at most kGroupBytes
+// together, so that they stay in the Infinity Cache while the group advances a chunk of steps;
+// items [first, first + count) of the precision's item table; cls: the first cavity's size class.
 struct BatchGroup {
   int prec, cls, cp, first, count, first2, count2;   // one-step items, multi-step items
-  int grid2;   // work-groups of the multi-step launch (one per item; count2 rounded up to a
-               // power of two, so that a graph survives small changes of the group)
+  int grid2;   // work-groups of the multi-step launch (one per item; count2 rounded up to three
+               // significant bits, so that a graph survives small changes of the group)
   int shape;   // tile shape of the multi-step items (batch_tile_shape)
   int spl;     // steps per multi-step launch: 3, 2, or 1 (one-step launches only)
   int nee;     // walls through the boundary nodes: two-step launches only, last tiles against
                // the far walls; a remaining single step runs as the cavity's own launch
+  double bytes = 0;   // bytes that a step of the group touches
 };
 
-// Launch choice of the groups of one precision and size class: the two-step tile shape, or
-// kBatchThree for three steps per launch on the three-step tile (shape 0), and the cache
-// policy (-1: the default rule); set by lbm_batch_set_tile or lbm_batch_autotune.
+// Launch choice of the cavities of one precision and size class: the two-step tile shape,
+// batch_three_shape() for three steps per launch on the three-step tile (shape 0), or -1 for the
+// default, three steps per launch where the chunk and the precision allow it, else shape 0; and
+// the cache policy (-1: the default rule).  Set by lbm_batch_set_tile or lbm_batch_autotune.
+// Three against two steps (shape 0), GLUPS, 12 cavities of 64^2, 128^2, 256^2 and 8 of 512^2:
+// FP32 14.4 / 13.3, 39.2 / 36.0, 66.2 / 57.0, 68.2 / 57.6; FP64 11.9 / 10.8, 21.6 / 22.6,
+// 27.4 / 25.0, 29.4 / 25.8.
 struct BatchChoice {
-  int shape = 0, cp = -1;
+  int shape = -1, cp = -1;
 };
 int batch_three_shape() { return batch_tile_shapes(); }
 
@@ -1416,11 +1422,12 @@ struct lbm_batch {
   int item2_cap[3] = {0, 0, 0};
   std::vector<BatchGroup> groups;
   BatchChoice choice[3][kBatchClasses];   // per precision and size class
+  bool by_class = false;     // no group holds two size classes (while the autotuner times them one by one)
   int *ranges = nullptr;     // device: {first, count, first2, count2} per group
   int range_cap = 0;
   int grid = 2048;           // work-groups of the one-step batched launch
   hipGraphExec_t graph = nullptr;
-  std::vector<int> graph_key;   // (precision, cache policy) of each group when the graph was captured
+  std::vector<int> graph_key;   // batch_key when the graph was captured
   bool dirty = true;
 };
 
@@ -1438,7 +1445,7 @@ bool batch_three_ok(const lbm_batch *b, int prec) { return b->chunk % 12 == 0 &&
 
 // steps per multi-step launch of the groups of one precision under a launch choice
 int batch_group_spl(const lbm_batch *b, int prec, const BatchChoice &ch) {
-  if (ch.shape == batch_three_shape() && batch_three_ok(b, prec)) return 3;
+  if ((ch.shape < 0 || ch.shape == batch_three_shape()) && batch_three_ok(b, prec)) return 3;
   return batch_spl(b);
 }
 
@@ -1446,6 +1453,20 @@ int batch_group_spl(const lbm_batch *b, int prec, const BatchChoice &ch) {
 int batch_ctx_spl(const lbm_batch *b, const lbm_ctx *c) {
   if (node_walls(&c->p)) return 2;
   return batch_group_spl(b, c->prec, b->choice[c->prec][batch_class(c->p.nx)]);
+}
+
+// n steps of a group of spl steps per launch: three- and two-step launches, then single steps.
+// The tiles of the three-step launch are those of the two-step launch's shape 0, so two-step
+// launches take the one or two steps (or four, as two launches) that threes leave.
+struct BatchPlan {
+  int64_t threes, twos, ones;
+  int64_t multi() const { return threes + twos; }
+};
+BatchPlan batch_plan(int spl, int64_t n) {
+  if (spl < 2) return BatchPlan{0, 0, n};
+  if (spl == 2) return BatchPlan{0, n / 2, n % 2};
+  if (n < 2) return BatchPlan{0, 0, n};
+  return n % 3 == 1 ? BatchPlan{n / 3 - 1, 2, 0} : BatchPlan{n / 3, n % 3 / 2, 0};
 }
 
 void drop_batch_graph(lbm_batch *b) {
@@ -1461,14 +1482,38 @@ lbm_status batch_upload(lbm_batch *b) {
     std::vector<Desc<double>> d64;
     std::vector<Desc<float>> d32;
     double gnodes = 0;
-    // cavities of this precision by size class, those with walls through the nodes after the
-    // others of their class (attach order within each)
+    // cavities of this precision by size class (attach order within each)
     std::vector<lbm_ctx *> order;
     for (int cls = 0; cls < kBatchClasses; ++cls)
-      for (int nee = 0; nee < 2; ++nee)
-        for (lbm_ctx *c : b->ctx)
-          if (c->prec == prec && batch_class(c->p.nx) == cls && (int)node_walls(&c->p) == nee) order.push_back(c);
-    for (lbm_ctx *c : order) {
+      for (lbm_ctx *c : b->ctx)
+        if (c->prec == prec && batch_class(c->p.nx) == cls) order.push_back(c);
+    // the tile shape and the steps of a cavity's multi-step launch: node walls take two steps on the
+    // two-step tile (attach checked that the chunk allows two steps and that the cavity holds one)
+    auto launch_of = [&](const lbm_ctx *c, int *shape, int *spl) {
+      const BatchChoice &ch = b->choice[prec][batch_class(c->p.nx)];
+      *spl = node_walls(&c->p) ? 2 : batch_group_spl(b, prec, ch);
+      *shape = (*spl == 3 || node_walls(&c->p) || ch.shape < 0 || ch.shape >= batch_tile_shapes()) ? 0 : ch.shape;
+      return ch.cp;
+    };
+    // the cavities of one launch, whatever their size classes: as few groups as kGroupBytes allows, of
+    // about equal size (a group of few tiles leaves the chip idle).  12 FP32 cavities of 64^2 to
+    // 512 x 1024: 39 GLUPS with groups of one size class and two steps, 54 with this and three steps.
+    auto alike = [&](const lbm_ctx *p, const lbm_ctx *q) {
+      int ps, pn, qs, qn;
+      const int pc = launch_of(p, &ps, &pn), qc = launch_of(q, &qs, &qn);
+      return ps == qs && pn == qn && pc == qc && node_walls(&p->p) == node_walls(&q->p) &&
+             (!b->by_class || batch_class(p->p.nx) == batch_class(q->p.nx));
+    };
+    std::stable_sort(order.begin(), order.end(), [&](const lbm_ctx *p, const lbm_ctx *q) {
+      int ps, pn, qs, qn;
+      const int pc = launch_of(p, &ps, &pn), qc = launch_of(q, &qs, &qn);
+      return std::make_tuple(b->by_class ? batch_class(p->p.nx) : 0, node_walls(&p->p), pn, ps, pc) <
+             std::make_tuple(b->by_class ? batch_class(q->p.nx) : 0, node_walls(&q->p), qn, qs, qc);
+    });
+    const lbm_ctx *prev = nullptr;
+    double target = 0;         // nodes of a group of the current launch
+    for (size_t k = 0; k < order.size(); ++k) {
+      lbm_ctx *c = order[k];
       const int cls = batch_class(c->p.nx);
       const int nee = node_walls(&c->p) ? 1 : 0;
       const BatchChoice &ch = b->choice[prec][cls];
@@ -1476,16 +1521,20 @@ lbm_status batch_upload(lbm_batch *b) {
       set_parity(c, c->cur);
       if (prec == PREC_FP64) d64.push_back(c->d64);
       else d32.push_back(c->d32);
-      // groups per size class, closed when the next cavity would take the group past
-      // kGroupBytes (a larger cavity is a group of its own)
+      // a group closes when the next cavity would take it past kGroupBytes (a larger cavity is a group
+      // of its own), or past half of that cavity beyond the group's share
       const double nodes = (double)c->p.nx * c->p.ny;
-      if (b->groups.empty() || b->groups.back().prec != prec || b->groups.back().cls != cls ||
-          b->groups.back().nee != nee || (gnodes > 0 && (gnodes + nodes) * bytes_per_lu(prec) > kGroupBytes)) {
-        // node-wall groups: two steps per launch on the two-step tile (attach checked that the
-        // chunk allows two steps and that the cavity holds one tile)
-        const int spl = nee ? 2 : batch_group_spl(b, prec, ch);
-        b->groups.push_back(BatchGroup{prec, cls, 0, (int)items.size(), 0, (int)items2.size(), 0, 1,
-                                       (spl == 3 || nee) ? 0 : ch.shape, spl, nee});
+      const bool same = prev && alike(prev, c);
+      if (!same) {
+        double total = 0;
+        for (size_t j = k; j < order.size() && alike(c, order[j]); ++j) total += (double)order[j]->p.nx * order[j]->p.ny;
+        target = total / std::ceil(total * bytes_per_lu(prec) / kGroupBytes);
+      }
+      prev = c;
+      if (!same || (gnodes > 0 && ((gnodes + nodes) * bytes_per_lu(prec) > kGroupBytes || gnodes + nodes / 2 > target))) {
+        int shape, spl;
+        launch_of(c, &shape, &spl);
+        b->groups.push_back(BatchGroup{prec, cls, 0, (int)items.size(), 0, (int)items2.size(), 0, 1, shape, spl, nee});
         gnodes = 0;
       }
       gnodes += nodes;
@@ -1513,9 +1562,11 @@ lbm_status batch_upload(lbm_batch *b) {
       BatchGroup &g = b->groups.back();
       g.count = (int)items.size() - g.first;
       g.count2 = (int)items2.size() - g.first2;
-      g.grid2 = 1;
-      while (g.grid2 < g.count2) g.grid2 *= 2;
+      int unit = 1;
+      while (8 * unit < g.count2) unit *= 2;
+      g.grid2 = std::max(1, (g.count2 + unit - 1) / unit * unit);
       g.cp = ch.cp >= 0 ? ch.cp : default_policy(prec, gnodes, g.spl);
+      g.bytes = gnodes * bytes_per_lu(prec);
     }
     const int n = (int)items.size();
     if (n > b->item_cap[prec]) {
@@ -1585,8 +1636,7 @@ lbm_status batch_upload(lbm_batch *b) {
   return LBM_OK;
 }
 
-// (precision, cache policy, two-step grid) of each group: a captured graph stays valid while
-// this is unchanged
+// what the launches of each group depend on: a captured graph stays valid while this is unchanged
 std::vector<int> batch_key(const lbm_batch *b) {
   std::vector<int> k;
   for (const BatchGroup &g : b->groups) {
@@ -1595,33 +1645,33 @@ std::vector<int> batch_key(const lbm_batch *b) {
     k.push_back(g.grid2);
     k.push_back(g.shape);
     k.push_back(g.spl);
+    k.push_back(g.nee);
   }
   return k;
 }
 
-// n steps of group gi: multi-step launches (g.spl steps each) while n allows, then single
-// steps.  A multi-step launch flips the population and the field buffers; a single step
-// flips the population buffers and updates the current field buffer in place.
+// n steps of group gi, as batch_plan has them.  A multi-step launch flips the population and
+// the field buffers; a single step flips the population buffers and updates the current field
+// buffer in place.
 hipError_t batch_launch_group(lbm_batch *b, size_t gi, int64_t n, hipStream_t s) {
   const BatchGroup &g = b->groups[gi];
   const int *rg = b->ranges + 4 * gi;
-  int64_t k = 0, multi = 0;
-  if (g.spl >= 2)
-    for (; k + g.spl <= n; k += g.spl, ++multi) {
-      const int q = (int)(multi & 1);
-      const int e = g.nee      ? launch_step2_batch_nee(g.prec, g.cp, b->descs[g.prec], b->items2[g.prec], rg + 2,
-                                                        g.grid2, q, s)
-                    : g.spl == 3 ? launch_step3_batch(g.prec, g.cp, b->descs[g.prec], b->items2[g.prec], rg + 2,
-                                                      g.grid2, q, s)
-                                 : launch_step2_batch(g.prec, g.cp, g.shape, b->descs[g.prec], b->items2[g.prec],
-                                                      rg + 2, g.grid2, q, s);
-      if (e) return (hipError_t)e;
-    }
+  const BatchPlan plan = batch_plan(g.spl, n);
+  for (int64_t k = 0; k < plan.multi(); ++k) {
+    const int q = (int)(k & 1);
+    const int e = g.nee               ? launch_step2_batch_nee(g.prec, g.cp, b->descs[g.prec], b->items2[g.prec], rg + 2,
+                                                               g.grid2, q, s)
+                  : k < plan.threes ? launch_step3_batch(g.prec, g.cp, b->descs[g.prec], b->items2[g.prec], rg + 2,
+                                                         g.grid2, q, s)
+                                    : launch_step2_batch(g.prec, g.cp, g.shape, b->descs[g.prec], b->items2[g.prec],
+                                                         rg + 2, g.grid2, q, s);
+    if (e) return (hipError_t)e;
+  }
   // a remaining single step of a node-wall group is the cavity's own one-step launch (the
   // batched one-step kernel has no perimeter work), taken by lbm_batch_step after this call
   if (g.nee) return hipSuccess;
-  for (int64_t single = 0; k < n; ++k, ++single) {
-    const int parity = (int)((multi + single) & 1) | (int)((multi & 1) << 1);
+  for (int64_t single = 0; single < plan.ones; ++single) {
+    const int parity = (int)((plan.multi() + single) & 1) | (int)((plan.multi() & 1) << 1);
     int e = launch_step_batch(g.prec, g.cp, b->descs[g.prec], b->items[g.prec], rg, b->grid, parity, s);
     if (e) return (hipError_t)e;
   }
@@ -1636,6 +1686,52 @@ hipError_t batch_launch_steps(lbm_batch *b, int64_t n, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// The side streams and events of one capture; they outlive it.
+struct CaptureFork {
+  std::vector<hipStream_t> streams;
+  std::vector<hipEvent_t> events;
+  ~CaptureFork() {
+    for (hipEvent_t e : events) (void)hipEventDestroy(e);
+    for (hipStream_t q : streams) (void)hipStreamDestroy(q);
+  }
+  hipError_t stream(hipStream_t *q) {
+    const hipError_t e = hipStreamCreateWithFlags(q, hipStreamNonBlocking);
+    if (e == hipSuccess) streams.push_back(*q);
+    return e;
+  }
+  hipError_t order(hipStream_t from, hipStream_t to) {   // what `to` gets next follows what `from` has
+    hipEvent_t ev;
+    hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e != hipSuccess) return e;
+    events.push_back(ev);
+    e = hipEventRecord(ev, from);
+    return e == hipSuccess ? hipStreamWaitEvent(to, ev, 0) : e;
+  }
+};
+
+// batch_launch_steps on a capturing stream s: consecutive groups whose step touches at most
+// kGroupBytes together become parallel branches of the graph, so that a group's thin last wave
+// of tiles is filled by another group's (12 FP32 and FP16 cavities of 128^2 to 1024^2: 30.4 ms for
+// 600 steps with the groups one after the other, 26.3 ms side by side).
+hipError_t batch_capture_steps(lbm_batch *b, int64_t n, hipStream_t s, CaptureFork &fork) {
+  hipError_t e = hipSuccess;
+  for (size_t first = 0, last; first < b->groups.size() && e == hipSuccess; first = last) {
+    double bytes = 0;
+    for (last = first; last < b->groups.size(); ++last) {
+      bytes += b->groups[last].bytes;
+      if (last > first && bytes > kGroupBytes) break;
+    }
+    std::vector<hipStream_t> side(last - first, s);
+    for (size_t k = 1; k < side.size() && e == hipSuccess; ++k) {
+      e = fork.stream(&side[k]);
+      if (e == hipSuccess) e = fork.order(s, side[k]);
+    }
+    for (size_t k = 0; k < side.size() && e == hipSuccess; ++k) e = batch_launch_group(b, first + k, n, side[k]);
+    for (size_t k = 1; k < side.size() && e == hipSuccess; ++k) e = fork.order(side[k], s);
+  }
+  return e;
 }
 
 }  // namespace
@@ -1792,6 +1888,7 @@ LBM_API lbm_status lbm_batch_autotune(lbm_batch *b, int32_t steps, int32_t *shap
   if (e == hipSuccess) e = hipEventCreate(&t0);
   if (e == hipSuccess) e = hipEventCreate(&t1);
   lbm_status st = LBM_OK;
+  b->by_class = true;
   // one step per launch: no multi-step tile; three steps per launch where the chunk allows
   const int two_shapes = batch_spl(b) == 2 ? batch_tile_shapes() : 1;
   for (int prec = 0; prec < 3 && e == hipSuccess && st == LBM_OK; ++prec)
@@ -1834,6 +1931,7 @@ LBM_API lbm_status lbm_batch_autotune(lbm_batch *b, int32_t steps, int32_t *shap
   if (t1) (void)hipEventDestroy(t1);
   (void)hipFree(save);
   drop_batch_graph(b);
+  b->by_class = false;
   b->dirty = true;
   if (st != LBM_OK) return st;
   return e == hipSuccess ? LBM_OK : LBM_EDEVICE;
@@ -1852,16 +1950,16 @@ LBM_API lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps) {
   if (left >= b->chunk) {
     if (!b->graph || b->graph_key != key) {
       drop_batch_graph(b);
+      CaptureFork fork;
       hipStream_t cs;
-      if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) return LBM_EDEVICE;
+      if (fork.stream(&cs) != hipSuccess) return LBM_EDEVICE;
       hipGraph_t g = nullptr;
       hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-      if (e == hipSuccess) e = batch_launch_steps(b, b->chunk, cs);
+      if (e == hipSuccess) e = batch_capture_steps(b, b->chunk, cs, fork);
       hipError_t e2 = hipStreamEndCapture(cs, &g);
       if (e == hipSuccess) e = e2;
       if (e == hipSuccess) e = hipGraphInstantiate(&b->graph, g, nullptr, nullptr, 0);
       if (g) (void)hipGraphDestroy(g);
-      (void)hipStreamDestroy(cs);
       if (e != hipSuccess) {
         b->graph = nullptr;
         return LBM_EDEVICE;
@@ -1877,9 +1975,8 @@ LBM_API lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps) {
   // buffers flipped by the remainder, per cavity as its group launched it: the populations
   // once per launch, the fields once per multi-step launch
   for (lbm_ctx *c : b->ctx) {
-    const int spl = batch_ctx_spl(b, c);
-    const int64_t multi = spl >= 2 ? left / spl : 0;
-    const int64_t singles = left - multi * spl;
+    const BatchPlan plan = batch_plan(batch_ctx_spl(b, c), left);
+    const int64_t multi = plan.multi(), singles = plan.ones;
     c->step += nsteps;
     if (multi & 1) {
       c->cur ^= 1;

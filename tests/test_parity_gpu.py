@@ -681,6 +681,52 @@ def test_batch_member_closed_while_attached():
     mix[1].close()
 
 
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 7, 12, 13, 25, 34])
+def test_batch_default_launches_match_one_step(steps):
+    """The default launches of a batch with a chunk of 12 (groups across the size classes, three
+    steps per launch and two-step launches for what threes leave, groups of the three storage types
+    and of node walls side by side in the graph), every cavity bit for bit in the state that one step
+    per launch gives it; then a cavity is exchanged for another of its size with node walls."""
+    from paper_1708_07525_amd import Batch
+    Solver = _solver()
+    specs = [(workloads.cavity_params(nx=40, ny=52), "fp32"), (workloads.cavity_params(nx=300, ny=130, Ra=1e5), "fp32"),
+             (workloads.cavity_params(nx=200, ny=100, Ra=3e4), "fp16s"), (workloads.cavity_params(nx=66, ny=33), "fp16s"),
+             (workloads.cavity_params(nx=97, ny=70, Ra=1e5, N=-1.0), "fp64"), (workloads.cavity_params(nx=5, ny=4), "fp64"),
+             (workloads.cavity_params(nx=128, ny=64, sides=("periodic", "periodic", "cold", "hot")), "fp32"),
+             (workloads.cavity_params(nx=128, ny=64, sides=("nee_hot", "nee_cold", "nee_adiabatic", "nee_adiabatic")), "fp32")]
+
+    def alone(i, n):
+        p, prec = specs[i]
+        T, C = workloads.noise_fields(p["nx"], p["ny"], (23, i))
+        s = Solver(p, T=T, C=C, precision=prec)
+        s.set_steps_per_launch(1)
+        s.step(n)
+        got = s.get_state()
+        s.close()
+        return got
+
+    b = Batch(len(specs), chunk=12)
+    mix = []
+    for i, (p, prec) in enumerate(specs):
+        T, C = workloads.noise_fields(p["nx"], p["ny"], (23, i))
+        mix.append(Solver(p, T=T, C=C, precision=prec))
+    for s in mix[:-1]:
+        b.attach(s)
+    b.step(steps)
+    for i, s in enumerate(mix[:-1]):
+        d = _state_diff(s.get_state(), alone(i, steps))
+        assert d is None, (i, d)
+    b.detach(mix[6])
+    b.attach(mix[7])
+    b.step(steps)
+    for i, n in ((0, 2 * steps), (2, 2 * steps), (4, 2 * steps), (6, steps), (7, steps)):
+        d = _state_diff(mix[i].get_state(), alone(i, n))
+        assert d is None, (i, d)
+    b.close()
+    for s in mix:
+        s.close()
+
+
 @pytest.mark.parametrize("shape,chunk", [(0, 100), (1, 100), (2, 100), (3, 120), ("auto", 100), ("auto", 120)])
 def test_batch_tile_shapes_change_nothing(shape, chunk):
     """Every tile shape of the batched two-step launch, three steps per launch (shape 3, FP32

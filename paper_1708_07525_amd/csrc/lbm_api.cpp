@@ -824,20 +824,23 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
 // against 30.4, 1280 x 1300 33.8 (16) against 27.8, 1024^2 29.3 (11) against 24.1, 700^2 22.1 (6)
 // against 26.1; FP32 4096^2 78.3 (74) against 72.2, 2048^2 72.2 (19) against 63.8, 1536^2 65.5
 // (11) against 58.5, 1280 x 1300 59.2 (8) against 54.1, 1024^2 48.0 (7) against 58.7.  Hence chunks
-// of at least 10 rows in FP64 and 8 in FP32.  FP16 storage (three levels) lost 2% at 2048^2, 12% at
+// of at least 10 rows in FP64 and 8 in FP32.  Walls through the nodes, where the tiled launch takes
+// two steps: FP32 4096^2 77.0 against 50.9, 2048^2 66.2 against 48.3, 1280 x 1300 53.4 (8) against 42.1,
+// 1150^2 49.6 (6) against 50.6; FP64 4096^2 40.8 against 22.9, 2048^2 38.9 against 23.5, 900^2 25.4
+// (8) against 19.6, 800^2 22.9 (7) against 22.5, 700^2 19.0 (6) against 19.8: from 7 rows in FP64.  FP16 storage (three levels) lost 2% at 2048^2, 12% at
 // 1536^2 and won 12% at 3000^2: not there.
 struct MarchPlan {
   int steps, chunk;
 };
 static MarchPlan ctx_march(const lbm_ctx *c) {
-  if (!launch_defaults(c) || node_walls(&c->p) || c->prec == PREC_FP16S || c->p.nx < 128) return {0, 0};
+  if (!launch_defaults(c) || c->prec == PREC_FP16S || c->p.nx < 128) return {0, 0};
   int steps = 0, columns = 0, per_cu = 0;
   march_shape(c->prec, &steps, &columns, &per_cu);
   const int groups = (c->p.nx + columns - 1) / columns;
   const int chunks = std::max(1, kComputeUnits * per_cu / groups);
   const int chunk = (c->p.ny + chunks - 1) / chunks;
-  const int least = c->prec == PREC_FP64 ? 10 : 8;
-  return chunk >= least && c->p.ny >= 16 ? MarchPlan{steps, chunk} : MarchPlan{0, 0};
+  const int least = c->prec == PREC_FP32 ? 8 : node_walls(&c->p) ? 7 : 10;
+  return chunk >= least && c->p.ny >= (node_walls(&c->p) ? 64 : 16) ? MarchPlan{steps, chunk} : MarchPlan{0, 0};
 }
 
 // n steps with plain launches: three or two steps per launch as ctx_spl allows, the remainder

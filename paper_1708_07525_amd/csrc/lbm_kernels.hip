@@ -1537,12 +1537,21 @@ constexpr int kMarchWaves = 4;                               // strips of a work
 template <typename S>
 constexpr int kMarchStrip = 64 - 2 * (March<S>::K - 1);      // columns a strip stores
 
+// NEE, walls through the boundary nodes: the march takes the nodes at least kMarchFrame from a wall,
+// whose K levels never meet one, and region_kernel the frame, in a launch before it (2048^2: FP32
+// 29 us of 255, FP64 51 of 440; as a parallel branch of the graph the fork and join of every launch
+// cost more, 59.7 GLUPS against 66.2).  2048^2 FP32 66.2 GLUPS against 48.3 for step2_kernel, FP64
+// 38.9 against 23.5.
+constexpr int kFrameRegion = 22;                             // region side of the frame's launch
+template <typename S>
+constexpr int kMarchFrame = kFrameRegion - 2 * (March<S>::K - 1);
+
 template <typename R>
 struct MarchRows {
   R up0[5], up1[5], row[14];
 };
 
-template <typename S>
+template <typename S, bool NEE>
 __global__ void __launch_bounds__(64 * kMarchWaves, March<S>::WAVES_PER_EU)
     march_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int nstrips, int chunk, int parity) {
   using R = typename St<S>::R;
@@ -1567,16 +1576,17 @@ __global__ void __launch_bounds__(64 * kMarchWaves, March<S>::WAVES_PER_EU)
   if (job == 0 && threadIdx.x == 0) d.counter[cur ^ 1] = step + (uint32_t)K;
   if (strip >= nstrips) return;            // (a wave that has ended counts as arrived at the barriers)
 
-  const bool perx = d.perx != 0, pery = d.pery != 0;
-  const int x0 = strip * V - H, xv = x0 + lane;
+  const bool perx = NEE || d.perx != 0, pery = NEE || d.pery != 0;   // (NEE: no wall in reach)
+  const int fx = NEE && !d.perx ? kMarchFrame<S> : 0, fy = NEE && !d.pery ? kMarchFrame<S> : 0;
+  const int x0 = fx + strip * V - H, xv = x0 + lane;
   // the lane's column: wrapped across periodic sides; beyond a wall the nearest one (its values are
   // never used there, the ghost's are set below)
   const int x = perx ? (xv < 0 ? xv + nx : xv >= nx ? xv - nx : xv) : min(max(xv, 0), nx - 1);
   const bool walls_x = !perx && (x0 <= 0 || x0 + 63 >= nx - 1);  // the strip holds a node at a wall
   const bool inner_x = x0 >= 1 && x0 + 64 <= nx - 1;             // every pull of level 1 stays inside in x
   const bool ghost_l = !perx && xv == -1, ghost_r = !perx && xv == nx;
-  const bool mine = lane >= H && lane < H + V && xv < nx;
-  const int ya = cy * chunk, yb = min(ya + chunk, ny);
+  const bool mine = lane >= H && lane < H + V && xv < nx - fx;
+  const int ya = fy + cy * chunk, yb = min(ya + chunk, ny - fy);
   // rows of level l: [first(l), last(l)), rows beyond a periodic side counted on
   auto first = [&](int l) { return pery ? ya - (K - l) : max(0, ya - (K - l)); };
   auto last = [&](int l) { return pery ? yb + (K - l) : min(ny, yb + (K - l)); };
@@ -1820,7 +1830,8 @@ struct Region {
 
 template <typename S, bool NEE, typename RG>
 __global__ void __launch_bounds__(RG::THREADS, RG::THREADS / 256)
-    region_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int ntx, uint32_t inv_ntx, int parity, int steps) {
+    region_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int ntx, uint32_t inv_ntx, int parity, int steps,
+                  int nty) {
   using R = typename St<S>::R;
   using FIO = FieldIO<S, CP_RESIDENT>;
   constexpr int RW = RG::RW, PAD = RG::PAD;
@@ -1837,7 +1848,16 @@ __global__ void __launch_bounds__(RG::THREADS, RG::THREADS / 256)
   const int edge = steps - 1, tile = RW - 2 * edge;
   // tile index over ntx by a multiplication with ceil(2^32 / ntx), exact for tiles x ntx < 2^32; 0: ntx = 1
   const int b = xcd_remap(blockIdx.x, gridDim.x);
-  const int by = inv_ntx ? (int)__umulhi((uint32_t)b, inv_ntx) : b, bx = b - by * ntx;
+  int by = inv_ntx ? (int)__umulhi((uint32_t)b, inv_ntx) : b, bx = b - by * ntx;
+  if (NEE && nty > 0) {                    // the frame of ntx x nty tiles: first and last rows, then columns
+    const int q = b - (d.pery ? 0 : 2 * ntx);
+    if (q < 0) {
+      by = by ? nty - 1 : 0;
+    } else {
+      bx = q & 1 ? ntx - 1 : 0;
+      by = (d.pery ? 0 : 1) + (q >> 1);
+    }
+  }
   int x0 = bx * tile, y0 = by * tile;
   if ((x0 | y0) == 0 && threadIdx.x == 0) d.counter[cur ^ 1] = step + (uint32_t)steps;
   if (NEE) {
@@ -2459,15 +2479,37 @@ int launch_step3(int prec, const void *desc, const void *ddev, int cp, int parit
   }
 }
 
+template <typename S, bool NEE, typename RG>
+static int region_t(const void *desc, const void *ddev, int parity, int steps, void *stream, bool frame = false) {
+  const auto &d = *(const Desc<typename St<S>::R> *)desc;
+  const int tile = RG::RW - 2 * (steps - 1);
+  if (tile < 4 || (NEE && (d.nx < tile || d.ny < tile))) return (int)hipErrorInvalidValue;
+  const int ntx = (d.nx + tile - 1) / tile, nty = (d.ny + tile - 1) / tile;
+  const int grid = !frame ? ntx * nty : (d.pery ? 0 : 2 * ntx) + (d.perx ? 0 : 2 * (nty - (d.pery ? 0 : 2)));
+  hipLaunchKernelGGL((region_kernel<S, NEE, RG>), dim3(grid), dim3(RG::THREADS), 0, (hipStream_t)stream,
+                     (const Desc<typename St<S>::R> *)ddev, ntx, ntx > 1 ? (uint32_t)(((1ull << 32) + ntx - 1) / ntx) : 0u,
+                     parity, steps, frame ? nty : 0);
+  return (int)hipGetLastError();
+}
+
 template <typename S>
 static int march_t(const void *desc, const void *ddev, int parity, int chunk, void *stream) {
   const auto &d = *(const Desc<typename St<S>::R> *)desc;
-  // one wrap across a periodic side, walls half a spacing outside
-  if (d.nee || d.nx < 128 || d.ny < 16 || chunk < 1) return (int)hipErrorInvalidValue;
-  const int nstrips = (d.nx + kMarchStrip<S> - 1) / kMarchStrip<S>, nch = (d.ny + chunk - 1) / chunk;
+  // one wrap across a periodic side; three frame tiles side by side at least
+  if (d.nx < 128 || d.ny < (d.nee ? 64 : 16) || chunk < 1) return (int)hipErrorInvalidValue;
+  const int frame = d.nee ? 2 * kMarchFrame<S> : 0;
+  const int w = d.nx - (d.perx ? 0 : frame), h = d.ny - (d.pery ? 0 : frame);
+  const int nstrips = (w + kMarchStrip<S> - 1) / kMarchStrip<S>, nch = (h + chunk - 1) / chunk;
   const int groups = (nstrips + kMarchWaves - 1) / kMarchWaves;
-  hipLaunchKernelGGL((march_kernel<S>), dim3(groups * nch), dim3(64 * kMarchWaves), 0, (hipStream_t)stream,
-                     (const Desc<typename St<S>::R> *)ddev, nstrips, chunk, parity);
+  const auto *dd = (const Desc<typename St<S>::R> *)ddev;
+  const dim3 grid(groups * nch), block(64 * kMarchWaves);
+  if (d.nee) {
+    const int e = region_t<S, true, Region<kFrameRegion>>(desc, ddev, parity, March<S>::K, stream, true);
+    if (e) return e;
+    hipLaunchKernelGGL((march_kernel<S, true>), grid, block, 0, (hipStream_t)stream, dd, nstrips, chunk, parity);
+  } else {
+    hipLaunchKernelGGL((march_kernel<S, false>), grid, block, 0, (hipStream_t)stream, dd, nstrips, chunk, parity);
+  }
   return (int)hipGetLastError();
 }
 
@@ -2484,18 +2526,6 @@ void march_shape(int prec, int *steps, int *group_columns, int *groups_per_cu) {
   *group_columns = kMarchWaves * (prec == PREC_FP64 ? kMarchStrip<double> : kMarchStrip<float>);
   // work-groups of four waves, one per SIMD, that a CU holds
   *groups_per_cu = prec == PREC_FP64 ? March<double>::WAVES_PER_EU : March<float>::WAVES_PER_EU;
-}
-
-template <typename S, bool NEE, typename RG>
-static int region_t(const void *desc, const void *ddev, int parity, int steps, void *stream) {
-  const auto &d = *(const Desc<typename St<S>::R> *)desc;
-  const int tile = RG::RW - 2 * (steps - 1);
-  if (tile < 4 || (NEE && (d.nx < tile || d.ny < tile))) return (int)hipErrorInvalidValue;
-  const int ntx = (d.nx + tile - 1) / tile, nty = (d.ny + tile - 1) / tile;
-  hipLaunchKernelGGL((region_kernel<S, NEE, RG>), dim3(ntx * nty), dim3(RG::THREADS), 0, (hipStream_t)stream,
-                     (const Desc<typename St<S>::R> *)ddev, ntx, ntx > 1 ? (uint32_t)(((1ull << 32) + ntx - 1) / ntx) : 0u,
-                     parity, steps);
-  return (int)hipGetLastError();
 }
 
 template <typename RG>

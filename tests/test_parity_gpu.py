@@ -543,6 +543,37 @@ def test_march_matches_one_step(prec, nx, ny, walls):
         s.close()
 
 
+@pytest.mark.parametrize("prec,nx,ny,walls", [
+    ("fp32", 1281, 1297, "nee"), ("fp32", 1400, 1190, "nee_x"), ("fp32", 1392, 1313, "nee_y"),
+    ("fp32", 6000, 301, "nee"), ("fp32", 192, 9001, "nee"),
+    ("fp64", 1024, 1000, "nee"), ("fp64", 1160, 1100, "nee_x"), ("fp64", 1045, 1011, "nee_y"), ("fp64", 200, 5001, "nee")])
+def test_march_with_node_walls_matches_one_step(prec, nx, ny, walls):
+    """The march between walls through the boundary nodes (the nodes near a wall in a launch of their
+    own) against one step per launch, bit for bit: the four kinds of sides, moving lids, a porosity
+    field, periodic in x or y, the last tile of the frame placed against the far wall."""
+    Solver = _solver()
+    sides = {"nee": ("nee_hot", "nee_robin", "nee_adiabatic", "nee_cold"),
+             "nee_x": ("nee_hot", "nee_robin", "periodic", "periodic"),
+             "nee_y": ("periodic", "periodic", "nee_cold", "nee_hot")}[walls]
+    lid = [0.0 if k == "periodic" else u for k, u in zip(sides, (0.01, -0.01, 0.015, 0.02))]
+    p = workloads.cavity_params(nx=nx, ny=ny, sides=sides, Ra=1e6, wall_u=tuple(lid), Bi_T=2.0, Bi_C=0.5)
+    rng = np.random.default_rng([nx, ny])
+    kw = dict(phi=rng.uniform(0.4, 0.8, (ny, nx)), T=rng.uniform(0.4, 0.6, (ny, nx)), C=rng.uniform(0.4, 0.6, (ny, nx)))
+    ref = Solver(p, precision=prec, **kw)
+    ref.set_steps_per_launch(1)
+    ref.step(23)
+    want = ref.get_state()
+    ref.close()
+    for chunk in (0, 8):
+        s = Solver(p, precision=prec, **kw)
+        s.set_graph_chunk(chunk)
+        assert s.get_march_steps() == 4
+        s.step(23)
+        d = _state_diff(s.get_state(), want)
+        assert d is None, (chunk, d)
+        s.close()
+
+
 def test_graph_replays_match_plain_launches():
     """lbm_step uses a captured graph for chunks of 64 steps; replays interleaved with other
     work must give the same state as one launch per step."""

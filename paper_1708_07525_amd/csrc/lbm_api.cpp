@@ -5,12 +5,16 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <tuple>
 #include <type_traits>
 #include <vector>
@@ -87,8 +91,8 @@ Layout plan_layout(int nx, int ny, int prec) {
   L.off_snap = take((size_t)ND4 * L.plane * rs);
   L.off_counter = take(2 * sizeof(unsigned));
   L.off_desc = take(4 * kDescSlot);
-  // small: wall T (4), wall C (4), obs out (32), partials
-  L.off_small = take((8 + 32 + (size_t)L.nblocks_obs * 12) * sizeof(double));
+  // small: wall T (4), wall C (4), partials
+  L.off_small = take((8 + (size_t)L.nblocks_obs * 12) * sizeof(double));
   L.total = off;
   return L;
 }
@@ -104,6 +108,7 @@ struct lbm_ctx {
   char *base = nullptr;      // device memory (arena or owned)
   bool owned = false;
   bool ready = false;
+  double *host = nullptr;    // pinned: kObsOut observables, then export_doubles of exported fields
   bool unstable = false;     // lbm_observables found a non-finite value: lbm_step refuses to go on
   double *scratch = nullptr; // device address of the fixed scratch on this context's device
   lbm_batch *batch = nullptr;   // the batch this context is attached to, if any
@@ -138,8 +143,7 @@ struct lbm_ctx {
   void *snap() const { return base + lay.off_snap; }
   unsigned *counter() const { return (unsigned *)(base + lay.off_counter); }
   double *wall_dev() const { return (double *)(base + lay.off_small); }
-  double *obs_out() const { return wall_dev() + 8; }
-  double *partials() const { return wall_dev() + 40; }
+  double *partials() const { return wall_dev() + 8; }
   const void *desc() const { return prec == PREC_FP64 ? (const void *)&d64 : (const void *)&d32; }
   // the device copy of the descriptor for population buffer `pc` and field buffer `fc`
   const void *desc_dev(int pc, int fc) const { return base + lay.off_desc + (size_t)(2 * pc + fc) * kDescSlot; }
@@ -573,6 +577,65 @@ LBM_API lbm_status lbm_derive(const lbm_params *p, lbm_derived *out) {
   return LBM_OK;
 }
 
+// Pinned buffers of large exports (HostExport), kept between calls: allocating one for every call
+// costs 0.1-1 ms.  At most kKept of them, given back with the last context of the process; a call
+// that finds none idle (several threads export at once) or needs a larger one takes its own.
+class PinnedPool {
+ public:
+  static constexpr size_t kBytes = 16 << 20, kKept = 2;
+  void *take(size_t bytes) {
+    if (bytes <= kBytes) {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (!idle_.empty()) {
+        void *p = idle_.back();
+        idle_.pop_back();
+        return p;
+      }
+      bytes = kBytes;
+    }
+    void *p = nullptr;
+    if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  void give(void *p, size_t bytes) {
+    if (bytes <= kBytes) {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (contexts_ > 0 && idle_.size() < kKept) {
+        idle_.push_back(p);
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+  void context(int change) {   // a context more (1) or less (-1)
+    std::vector<void *> drop;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      contexts_ += change;
+      if (contexts_ == 0) drop.swap(idle_);
+    }
+    for (void *p : drop) (void)hipHostFree(p);
+  }
+
+ private:
+  std::mutex mu_;
+  std::vector<void *> idle_;
+  int contexts_ = 0;
+};
+static PinnedPool &pinned_pool() {
+  static PinnedPool *pool = new PinnedPool;   // never destroyed: contexts may outlive static objects
+  return *pool;
+}
+
+// The fields of a small lattice (up to this many bytes) go through pinned memory that the context
+// keeps (c->host).
+constexpr size_t kHostExport = 256 << 10;
+static size_t host_export_doubles(const lbm_ctx *c) {
+  const size_t n = 5 * (size_t)c->p.nx * c->p.ny;
+  return n * sizeof(double) <= kHostExport ? n : 0;
+}
+
 LBM_API lbm_status lbm_create(const lbm_params *p, lbm_ctx **out) {
   if (!p || !out) return LBM_EINVAL;
   std::string msg;
@@ -609,6 +672,14 @@ LBM_API lbm_status lbm_create(const lbm_params *p, lbm_ctx **out) {
     }
     c->owned = true;
   }
+  if (hipHostMalloc((void **)&c->host, (kObsOut + host_export_doubles(c)) * sizeof(double), hipHostMallocDefault) !=
+      hipSuccess) {
+    (void)hipGetLastError();
+    if (c->owned) (void)hipFree(c->base);
+    delete c;
+    return LBM_ENOMEM;
+  }
+  pinned_pool().context(1);
   *out = c;
   return LBM_OK;
 }
@@ -628,7 +699,9 @@ LBM_API void lbm_destroy(lbm_ctx *c) {
   }
   drop_graph(c);
   if (c->owned && c->base) (void)hipFree(c->base);
+  (void)hipHostFree(c->host);
   delete c;
+  pinned_pool().context(-1);
 }
 
 LBM_API const char *lbm_last_error(const lbm_ctx *c) {
@@ -1008,15 +1081,140 @@ LBM_API lbm_status lbm_step(lbm_ctx *c, int64_t nsteps) {
   return LBM_OK;
 }
 
-// FP64 fields of the current level into host memory through a device staging buffer: `stage`
-// (5 nx ny doubles), or one allocated for the call when stage is NULL
+// One export of a larger lattice: chunks of rows, which export_kernel writes straight into the
+// slots of a pinned buffer and threads copy on into the caller's array, one plane of one chunk at
+// a time, while the next chunks are written.  Bound by the page faults of a caller's array that is
+// new; the kernel's stores reach 53 GB/s.
+struct HostExport {
+  static constexpr size_t kLeast = 2 << 20;  // bytes from which it pays: see export_fields
+  static constexpr size_t kChunkBytes = 2 << 20, kSlots = 8;
+  static_assert(kChunkBytes * kSlots <= PinnedPool::kBytes, "the pool's buffers hold the slots");
+  static constexpr int kMaxThreads = 8;
+  lbm_ctx *c;
+  double *fields, *pinned;
+  size_t slots;                              // slots of the pinned buffer, rows * nx * 5 doubles each
+  int rows, chunks;
+  std::vector<hipEvent_t> written;           // per slot
+  std::mutex mu;
+  std::condition_variable changed;
+  int launched = 0;                          // chunks the stream has (guarded by mu, as the next two)
+  std::vector<int> left;                     // planes of a chunk that are still to be copied
+  hipError_t failed = hipSuccess;
+  std::atomic<int> next{0};                  // the next (chunk, plane)
+
+  int rows_of(int k) const { return std::min(rows, c->p.ny - k * rows); }
+  double *slot(int k) const { return pinned + (k % slots) * ((size_t)rows * c->p.nx * 5); }
+  hipError_t launch(int k) {
+    hipError_t e = (hipError_t)launch_export(c->prec, c->desc(), 0, k * rows, rows_of(k), slot(k), c->stream);
+    return e == hipSuccess ? hipEventRecord(written[k % slots], c->stream) : e;
+  }
+  void copy(int k, int plane) const {
+    const size_t nx = c->p.nx, len = nx * rows_of(k);
+    std::memcpy(fields + plane * nx * c->p.ny + (size_t)k * rows * nx, slot(k) + plane * len, len * sizeof(double));
+  }
+  // a thread's share: the pieces in order, each once its chunk is written
+  void work() {
+    (void)hipSetDevice(c->device);
+    for (;;) {
+      const int piece = next.fetch_add(1), k = piece / 5;
+      if (k >= chunks) return;
+      std::unique_lock<std::mutex> lock(mu);
+      changed.wait(lock, [&] { return launched > k || failed != hipSuccess; });
+      if (failed != hipSuccess) return;
+      lock.unlock();
+      const hipError_t e = hipEventSynchronize(written[k % slots]);
+      if (e == hipSuccess) copy(k, piece % 5);
+      lock.lock();
+      if (e != hipSuccess) failed = e;
+      left[k] -= 1;
+      changed.notify_all();
+      if (failed != hipSuccess) return;
+    }
+  }
+  hipError_t run(int nthreads) {
+    std::vector<std::thread> threads;
+    hipError_t e = hipSuccess;
+    try {
+      threads.reserve(nthreads);
+      for (int t = 0; t < nthreads; ++t) threads.emplace_back([this] { work(); });
+    } catch (...) {   // fewer threads than asked for, or none
+    }
+    for (int k = 0; k < chunks && e == hipSuccess; ++k) {
+      if (k >= (int)slots) {                 // the slot's last chunk has been copied
+        std::unique_lock<std::mutex> lock(mu);
+        changed.wait(lock, [&] { return left[k - slots] == 0 || failed != hipSuccess; });
+        if (failed != hipSuccess) break;
+      }
+      e = launch(k);
+      if (e == hipSuccess && threads.empty()) {
+        e = hipEventSynchronize(written[k % slots]);
+        for (int q = 0; q < 5 && e == hipSuccess; ++q) copy(k, q);
+        left[k] = 0;
+      }
+      std::lock_guard<std::mutex> lock(mu);
+      launched = k + 1;
+      if (e != hipSuccess) failed = e;
+      changed.notify_all();
+    }
+    for (std::thread &t : threads) t.join();
+    return e != hipSuccess ? e : failed;
+  }
+};
+
+// FP64 fields of the current level into host memory: through the context's pinned memory (small
+// lattices), through `stage` (5 nx ny doubles of device memory) where it is given, by HostExport
+// (large ones), else through device memory of this call.  Measured against a device buffer
+// and a copy for every size: 64^2 22 us against 95, 256^2 0.33 ms against 0.65, 512^2 0.50 against
+// 1.32, 1024^2 1.2 against 4.6, 2048^2 3.9 against 16.3; 200^2, below kLeast, takes 0.11 either way.
 static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = nullptr) {
   set_parity(c, c->cur);
-  const size_t n = (size_t)c->p.nx * c->p.ny;
+  const size_t n = 5 * (size_t)c->p.nx * c->p.ny, bytes = n * sizeof(double);
+  hipError_t he;
+  // (a caller's array in device memory takes the copy)
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, fields) != hipSuccess) (void)hipGetLastError();
+  const bool host = at.type != hipMemoryTypeDevice;
+  if (host && host_export_doubles(c)) {
+    double *out = c->host + kObsOut;
+    he = (hipError_t)launch_export(c->prec, c->desc(), 0, 0, c->p.ny, out, c->stream);
+    if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
+    if (he != hipSuccess) return hip_fail(c, he, "field export");
+    std::memcpy(fields, out, bytes);
+    return LBM_OK;
+  }
+  if (host && !stage && bytes >= HostExport::kLeast) {
+    HostExport x{};
+    x.c = c;
+    x.fields = fields;
+    const size_t row = 5 * (size_t)c->p.nx * sizeof(double);
+    x.rows = (int)std::min<size_t>(c->p.ny, std::max<size_t>(1, HostExport::kChunkBytes / row));
+    x.chunks = (c->p.ny + x.rows - 1) / x.rows;
+    x.slots = std::min<size_t>(x.chunks, HostExport::kSlots);
+    x.left.assign(x.chunks, 5);
+    const size_t pinned_bytes = x.slots * x.rows * row;
+    x.pinned = (double *)pinned_pool().take(pinned_bytes);
+    if (x.pinned) {
+      he = hipSuccess;
+      for (size_t k = 0; k < x.slots && he == hipSuccess; ++k) {
+        hipEvent_t ev;
+        he = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        if (he == hipSuccess) x.written.push_back(ev);
+      }
+      // a thread per half MB: starting one takes some 15 us, copying half a MB into new pages 150 us
+      const size_t cpus = std::max(1u, std::thread::hardware_concurrency());
+      const int threads = (int)std::min<size_t>({bytes >> 19, cpus, (size_t)HostExport::kMaxThreads});
+      if (he == hipSuccess) he = x.run(threads);
+      const hipError_t drained = hipStreamSynchronize(c->stream);   // nothing writes to the slots any more
+      if (he == hipSuccess) he = drained;
+      for (hipEvent_t ev : x.written) (void)hipEventDestroy(ev);
+      pinned_pool().give(x.pinned, pinned_bytes);
+      return he == hipSuccess ? LBM_OK : hip_fail(c, he, "field export");
+    }
+  }
   const bool own = stage == nullptr;
-  if (own) HIP_CHECK(c, hipMalloc((void **)&stage, 5 * n * sizeof(double)), "hipMalloc export");
-  hipError_t he = (hipError_t)launch_export(c->prec, c->desc(), 0, stage, c->stream);
-  if (he == hipSuccess) he = hipMemcpyAsync(fields, stage, 5 * n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+  if (own) HIP_CHECK(c, hipMalloc((void **)&stage, bytes), "hipMalloc export");
+  he = (hipError_t)launch_export(c->prec, c->desc(), 0, 0, c->p.ny, stage, c->stream);
+  if (he == hipSuccess) he = hipMemcpyAsync(fields, stage, bytes, hipMemcpyDeviceToHost, c->stream);
   if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
   if (own) (void)hipFree(stage);
   if (he != hipSuccess) return hip_fail(c, he, "field export");
@@ -1032,21 +1230,20 @@ LBM_API lbm_status lbm_get_fields(lbm_ctx *c, double *fields) {
 // The observables of the current level, with the per-block partial sums in `partials`, the 20
 // result slots in `slots` and, when fields is not NULL, the field export staged in `stage`
 // (NULL: allocated for the call).
-static lbm_status observe(lbm_ctx *c, lbm_obs *out, double *fields, double *partials, double *slots,
-                          double *stage) {
+static lbm_status observe(lbm_ctx *c, lbm_obs *out, double *fields, double *partials, double *stage) {
   set_parity(c, c->cur);
   const int nb = c->lay.nblocks_obs;
-  int e = launch_observables(c->prec, c->desc(), 0, c->snap(), partials, nb, slots, c->wall_dev(),
+  int e = launch_observables(c->prec, c->desc(), 0, c->snap(), partials, nb, c->host, c->wall_dev(),
                              c->wall_dev() + 4, c->dv.dT != 0 ? c->dv.L / c->dv.dT : 0.0,
                              c->dv.dC != 0 ? c->dv.L / c->dv.dC : 0.0, c->stream);
   if (e) return hip_fail(c, (hipError_t)e, "observables launch");
-  double r[20];
-  HIP_CHECK(c, hipMemcpyAsync(r, slots, sizeof r, hipMemcpyDeviceToHost, c->stream), "observables copy");
-  if (fields) {
+  if (fields) {   // waits for the stream
     lbm_status fs = export_fields(c, fields, stage);
     if (fs != LBM_OK) return fs;
+  } else {
+    HIP_CHECK(c, hipStreamSynchronize(c->stream), "observables sync");
   }
-  HIP_CHECK(c, hipStreamSynchronize(c->stream), "observables sync");
+  const double *r = c->host;
   std::memset(out, 0, sizeof *out);
   out->step = c->step;
   out->mass = r[0];
@@ -1077,7 +1274,7 @@ LBM_API lbm_status lbm_observables(lbm_ctx *c, lbm_obs *out, double *fields) {
   Range range_("lbm_observables");
   if (!c || !out) return LBM_EINVAL;
   if (!c->ready) return fail(c, LBM_ESTATE, "lbm_observables before lbm_set_fields");
-  return observe(c, out, fields, c->partials(), c->obs_out(), nullptr);
+  return observe(c, out, fields, c->partials(), nullptr);
 }
 
 LBM_API lbm_status lbm_observables_static(lbm_ctx *c, lbm_obs *out, double *fields) {
@@ -1092,7 +1289,7 @@ LBM_API lbm_status lbm_observables_static(lbm_ctx *c, lbm_obs *out, double *fiel
   if (fields && (long long)c->p.nx * c->p.ny > L.max_nodes)
     return fail(c, LBM_EINVAL, "lbm_observables_static exports the fields of lattices of at most %lld nodes "
                 "(this one has %lld)", L.max_nodes, (long long)c->p.nx * c->p.ny);
-  return observe(c, out, fields, c->scratch + L.partials, c->scratch + L.out, c->scratch + L.fields);
+  return observe(c, out, fields, c->scratch + L.partials, c->scratch + L.fields);
 }
 
 LBM_API lbm_status lbm_get_derived(const lbm_ctx *c, lbm_derived *out) {

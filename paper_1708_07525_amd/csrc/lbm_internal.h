@@ -129,18 +129,20 @@ void two_step_tile_shape(int prec, int *w, int *h);
 int batch_tile_shapes();
 void batch_tile_shape(int prec, int shape, int *w, int *h);
 // observables: partial sums per block, then a final fixed-order reduction.
-// out: 16 doubles + Nu[4] + Sh[4] (see lbm_api.cpp for the slots)
+// out: kObsOut doubles, 12 slots (see lbm_api.cpp), Nu[4], Sh[4]
 int launch_observables(int prec, const void *desc, int parity, void *snap, double *partials,
                        int nblocks, double *out, const double *wall_T, const double *wall_C,
                        double L_over_dT, double L_over_dC, void *stream);
-int launch_export(int prec, const void *desc, int parity, double *fields, void *stream);
+constexpr int kObsOut = 20;
+// fields of `rows` rows from y0 on: 5 planes of nx * rows
+int launch_export(int prec, const void *desc, int parity, int y0, int rows, double *fields, void *stream);
 int observables_blocks(int ny);
 
 // Fixed device scratch of the no-allocation observables (offsets in doubles)
 struct StaticScratchLayout {
   int max_rows;              // tallest lattice whose observables partials fit
   long long max_nodes;       // largest lattice whose exported fields fit
-  long long out, partials, fields, doubles;
+  long long partials, fields, doubles;
 };
 StaticScratchLayout static_scratch_layout();
 // device address of the scratch array on `device`, which must be current (looked up once per

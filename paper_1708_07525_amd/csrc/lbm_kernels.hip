@@ -2235,17 +2235,16 @@ __global__ void __launch_bounds__(OBS_THREADS) obs_partial_kernel(Desc<typename 
   }
 }
 
-// Mean Nusselt / Sherwood numbers of Eq. (38) at the four sides; one block per side.
+// Mean Nusselt / Sherwood numbers of Eq. (38) at the four sides; one work-group per side.
 // Half-way wall: gradient along the inward normal (-8 s_w + 9 s_0 - s_1)/3, mean over the
 // nodes.  Wall through the nodes: (-3 s_b + 4 s_1 - s_2)/2, trapezoidal mean along the wall.
 // Both stencils sum to zero, so they act on the stored deviations T - T0, C - C0 (wT, wC: the
 // wall values minus T0, C0) unchanged.
 // Heat entering through a hot side or leaving through a cold or convective side is positive.
 template <typename R>
-__global__ void __launch_bounds__(256) wall_kernel(Desc<R> d, const double *__restrict__ wT,
-                                                   const double *__restrict__ wC, double LdT, double LdC,
-                                                   double *__restrict__ out) {
-  const int side = blockIdx.x;
+__device__ __forceinline__ void wall_means(const Desc<R> &d, int side, const double *__restrict__ wT,
+                                           const double *__restrict__ wC, double LdT, double LdC,
+                                           double *__restrict__ out) {
   const R *d4 = (const R *)d.d4;
   const long long P = d.plane;
   const int kind = d.kind[side];
@@ -2291,9 +2290,8 @@ __global__ void __launch_bounds__(256) wall_kernel(Desc<R> d, const double *__re
 // One work-group per slot: thread t combines the partials t, t + 256, ... in index order, then
 // the waves reduce with lane shuffles and the four wave results are combined in wave order (a
 // fixed tree: the result depends on the number of partials only).
-__global__ void __launch_bounds__(OBS_THREADS) obs_final_kernel(const double *__restrict__ partials, int nblocks,
-                                                                double *__restrict__ out) {
-  const int s = blockIdx.x;
+__device__ __forceinline__ void obs_slot(int s, const double *__restrict__ partials, int nblocks,
+                                         double *__restrict__ out) {
   const bool is_max = s == 9 || s == 10;
   double v = 0.0;
   for (int b = threadIdx.x; b < nblocks; b += OBS_THREADS) {
@@ -2311,16 +2309,29 @@ __global__ void __launch_bounds__(OBS_THREADS) obs_final_kernel(const double *__
   }
 }
 
-// FP64 fields rho, ux, uy, T, C of the current level (5 planes of nx*ny, x fastest)
+// The observables' last launch: a work-group per slot and one per side.  out: NSLOT + 8 doubles,
+// in pinned host memory, where the caller reads them once the stream has drained: the copy that
+// this replaces cost 20 us.
+template <typename R>
+__global__ void __launch_bounds__(OBS_THREADS) obs_final_kernel(Desc<R> d, const double *__restrict__ partials,
+                                                                int nblocks, const double *__restrict__ wT,
+                                                                const double *__restrict__ wC, double LdT, double LdC,
+                                                                double *__restrict__ out) {
+  if (blockIdx.x < NSLOT) obs_slot((int)blockIdx.x, partials, nblocks, out);
+  else wall_means(d, (int)blockIdx.x - NSLOT, wT, wC, LdT, LdC, out);
+}
+
+// FP64 fields rho, ux, uy, T, C of the current level in the rows from y0 on, 5 planes of nx * rows,
+// x fastest
 template <typename S>
-__global__ void __launch_bounds__(256) export_kernel(Desc<typename St<S>::R> d, int parity,
+__global__ void __launch_bounds__(256) export_kernel(Desc<typename St<S>::R> d, int parity, int y0, int rows,
                                                      double *__restrict__ f) {
   using R = typename St<S>::R;
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y;
   if (x >= d.nx) return;
-  const long long P = d.plane, c = (long long)y * d.pitch + x;
-  const long long n = (long long)d.nx * d.ny, k = (long long)y * d.nx + x;
+  const long long P = d.plane, c = (long long)(y0 + y) * d.pitch + x;
+  const long long n = (long long)d.nx * rows, k = (long long)y * d.nx + x;
   const int cur = (d.base_parity ^ parity) & 1;
   const S *pop = (const S *)(cur ? d.pop1 : d.pop0);
   const R *d4 = (const R *)d.d4;
@@ -2725,8 +2736,8 @@ static int obs_t(const void *desc, int parity, void *snap, double *partials, int
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(obs_partial_kernel<S>, dim3(nblocks), dim3(OBS_THREADS), 0, s, d, parity, (R *)snap,
                      partials);
-  hipLaunchKernelGGL(obs_final_kernel, dim3(NSLOT), dim3(OBS_THREADS), 0, s, partials, nblocks, out);
-  hipLaunchKernelGGL(wall_kernel<R>, dim3(4), dim3(256), 0, s, d, wT, wC, LdT, LdC, out);
+  hipLaunchKernelGGL(obs_final_kernel<R>, dim3(NSLOT + 4), dim3(OBS_THREADS), 0, s, d, partials, nblocks, wT, wC,
+                     LdT, LdC, out);
   return (int)hipGetLastError();
 }
 
@@ -2741,15 +2752,13 @@ int launch_observables(int prec, const void *desc, int parity, void *snap, doubl
 }
 
 // ---------------------------------------------------------------- fixed scratch
-// Device memory of lbm_observables_static, for callers that cannot allocate: the result slots,
-// the per-block partial sums of the observables of a lattice of up to kStaticRows rows, and the
-// staging of the exported FP64 fields of a lattice of up to kStaticNodes nodes.  One copy per
-// device, held until the process ends, shared by every context on that device.
+// Device memory of lbm_observables_static, for callers that cannot allocate: the per-block partial
+// sums of the observables of a lattice of up to kStaticRows rows, and the staging of the exported
+// FP64 fields of a lattice of up to kStaticNodes nodes.  One copy per device, held until the process ends, shared by every context on that device.
 constexpr int kStaticRows = 16384;
 constexpr long long kStaticNodes = 1LL << 20;
-constexpr long long kStaticOut = 32;
 constexpr long long kStaticPartials = (long long)((kStaticRows + OBS_ROWS - 1) / OBS_ROWS) * NSLOT;
-constexpr long long kStaticDoubles = kStaticOut + kStaticPartials + 5 * kStaticNodes;
+constexpr long long kStaticDoubles = kStaticPartials + 5 * kStaticNodes;
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) double scratch[kStaticDoubles];
 
@@ -2757,9 +2766,8 @@ StaticScratchLayout static_scratch_layout() {
   StaticScratchLayout l;
   l.max_rows = kStaticRows;
   l.max_nodes = kStaticNodes;
-  l.out = 0;
-  l.partials = kStaticOut;
-  l.fields = kStaticOut + kStaticPartials;
+  l.partials = 0;
+  l.fields = kStaticPartials;
   l.doubles = kStaticDoubles;
   return l;
 }
@@ -2785,18 +2793,19 @@ int static_scratch_address(int device, double **ptr) {
 }
 
 template <typename S>
-static int export_t(const void *desc, int parity, double *fields, void *stream) {
+static int export_t(const void *desc, int parity, int y0, int rows, double *fields, void *stream) {
   const auto &d = *(const Desc<typename St<S>::R> *)desc;
-  dim3 grid((d.nx + 255) / 256, d.ny);
-  hipLaunchKernelGGL(export_kernel<S>, grid, dim3(256), 0, (hipStream_t)stream, d, parity, fields);
+  if (y0 < 0 || rows < 1 || rows > d.ny - y0) return (int)hipErrorInvalidValue;
+  dim3 grid((d.nx + 255) / 256, rows);
+  hipLaunchKernelGGL(export_kernel<S>, grid, dim3(256), 0, (hipStream_t)stream, d, parity, y0, rows, fields);
   return (int)hipGetLastError();
 }
 
-int launch_export(int prec, const void *desc, int parity, double *fields, void *stream) {
+int launch_export(int prec, const void *desc, int parity, int y0, int rows, double *fields, void *stream) {
   switch (prec) {
-    case PREC_FP64: return export_t<double>(desc, parity, fields, stream);
-    case PREC_FP32: return export_t<float>(desc, parity, fields, stream);
-    default: return export_t<_Float16>(desc, parity, fields, stream);
+    case PREC_FP64: return export_t<double>(desc, parity, y0, rows, fields, stream);
+    case PREC_FP32: return export_t<float>(desc, parity, y0, rows, fields, stream);
+    default: return export_t<_Float16>(desc, parity, y0, rows, fields, stream);
   }
 }
 

@@ -574,6 +574,42 @@ def test_march_with_node_walls_matches_one_step(prec, nx, ny, walls):
         s.close()
 
 
+@pytest.mark.parametrize("prec,nx,ny", [("fp32", 3, 3), ("fp64", 80, 81), ("fp16s", 81, 81), ("fp32", 300, 250),
+                                        ("fp32", 512, 103), ("fp64", 1000, 1000), ("fp16s", 333, 2000),
+                                        ("fp32", 60000, 17)])
+def test_fields_reach_the_host_whole(prec, nx, ny):
+    """lbm_get_fields through pinned memory (kept up to 256 KB, else chunks of rows copied on by
+    threads; one chunk, a last chunk of one row, more chunks than slots, rows longer than a chunk)
+    against lbm_observables_static, whose fields take a device buffer and one copy: bit for bit,
+    and from four contexts at once."""
+    import threading
+    Solver = _solver()
+    rng = np.random.default_rng([nx, ny])
+    s = [Solver(workloads.cavity_params(nx=nx, ny=ny), T=rng.uniform(0.4, 0.6, (ny, nx)),
+                C=rng.uniform(0.4, 0.6, (ny, nx)), precision=prec) for _ in range(4)]
+    for k, x in enumerate(s):
+        x.step(3 + k)
+    want = [x.observables(fields=True, static=True) for x in s]
+    got = [None] * 4
+
+    def export(k):
+        got[k] = s[k].fields()
+
+    threads = [threading.Thread(target=export, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    again = s[0].observables(fields=True)
+    assert all(again[k] == want[0][k] for k in ("mass", "heat", "solute", "Nu", "Sh", "max_ux"))
+    for k in ("rho", "ux", "uy", "T", "C"):
+        assert np.array_equal(again["fields"][k], want[0]["fields"][k]), k
+        for g, w in zip(got, want):
+            assert np.array_equal(g[k], w["fields"][k]), k
+    for x in s:
+        x.close()
+
+
 def test_graph_replays_match_plain_launches():
     """lbm_step uses a captured graph for chunks of 64 steps; replays interleaved with other
     work must give the same state as one launch per step."""

@@ -265,11 +265,10 @@ int32_t lbm_get_tile_rows(const struct lbm_ctx *c);
  * depend on it (bit for bit).  With 3, a graph replay covers the largest multiple of 6 steps in the
  * graph chunk.  lbm_get_steps_per_launch returns the count in effect (0 for a NULL context).
  * While every launch choice is the default (this one, cache policy, tile, strip width, tile rows),
- * lattices of up to about 400^2 nodes take the region launch instead: work-groups of one thread per
- * node advance small square regions by 3 to 6 steps, whatever the lattice leaves at most one
- * region per compute unit for (not with FP16 storage and walls through the nodes), and large
- * lattices with FP64 and FP32 storage and walls half a spacing outside (about 10^6 nodes, FP32 1.6
- * 10^6, and more) the march: waves march up strips of columns and update four time levels as they
+ * lattices of up to about 400^2 nodes (with walls through the nodes 10^6 nodes in FP32, 8 10^5 in
+ * FP16) take the region launch instead: work-groups of one thread per
+ * node advance small square regions by 3 to 6 steps, and large
+ * lattices with FP64 and FP32 storage (about 10^6 nodes, FP32 1.6 10^6, and more) the march: waves march up strips of columns and update four time levels as they
  * go.  Bit for bit the same results.  lbm_get_region_steps and
  * lbm_get_march_steps return the steps per launch of the one in effect, 0 where the launches above
  * run (and for a NULL context). */

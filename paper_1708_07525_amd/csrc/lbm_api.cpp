@@ -857,8 +857,12 @@ static int ctx_strip(const lbm_ctx *c) {
 // against 3.37 / 5.74 / 3.74; 200^2 2.21 / 2.95 / 2.46 (22, 5) against 3.49 / 4.23 / 3.85; 256^2
 // 2.49 / 3.31 / 2.62 (22, 4) against 3.50 / 4.35 / 3.84; walls through the nodes 100^2 3.43 / 4.02
 // (16, 5) against 7.50 / 8.93.  Above that several regions share a CU and three steps on regions
-// of 16^2 nodes still win up to 400^2 nodes (384^2 4.00 / 7.11 / 4.27 against 4.66 / 7.94 / 4.77; node
-// walls FP32 6.49 against 7.29, but FP64 13.8 against 10.2: not there); 512^2 loses.
+// of 16^2 nodes still win up to 400^2 nodes (384^2 4.00 / 7.11 / 4.27 against 4.66 / 7.94 / 4.77); 512^2 loses.
+// Node walls above 256 regions, against two steps per launch in FP32 and FP64 and one in FP16:
+// FP32 22^2 with 3 steps 512^2 8.56 against 9.61, 768^2 13.8 against 15.3, 1024^2 20.7 against 21.6,
+// 1200^2 30.7 against 30.5; FP64 22^2 with 4 steps 320^2 9.6 against 10.5, but 380 x 400 12.8 against
+// 11.8 (a region fills a CU: the third round of them starts): not there; FP16 16^2 with 3 steps (never 22^2: 256^2 4.8 either way, 200^2 5.2 against 4.9) 256^2
+// 4.8 against 17.5, 400^2 7.3 against 8.7, 768^2 16.8 against 27.3, 900^2 20.0 against 19.4.
 // Any launch choice of the caller (steps per launch, cache policy, tile, tile order, tile rows)
 // is kept: the region launch is part of the defaults only.
 struct RegionPlan {
@@ -871,7 +875,6 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
   const bool nee = node_walls(&c->p);
   const int nx = c->p.nx, ny = c->p.ny;
   if (!launch_defaults(c)) return {0, 0};
-  if (nee && c->prec == PREC_FP16S) return {0, 0};
   auto tiles = [&](int side, int steps) -> int64_t {
     const int t = side - 2 * (steps - 1);
     return (int64_t)((nx + t - 1) / t) * ((ny + t - 1) / t);
@@ -882,11 +885,14 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
   if (fits(16))
     for (int k = 6; k >= 4; --k)
       if (tiles(16, k) <= kRegionTiles) return {16, k};
+  const int64_t nodes = (int64_t)nx * ny;
+  if (nee && c->prec == PREC_FP16S) return fits(16) && nodes <= 800000 ? RegionPlan{16, 3} : RegionPlan{0, 0};
   if (fits(22))
     for (int k = 5; k >= 4; --k)
       if (tiles(22, k) <= kRegionTiles) return {22, k};
-  if (fits(16) && (int64_t)nx * ny <= 160000 && !(nee && c->prec == PREC_FP64)) return {16, 3};
-  return {0, 0};
+  if (nee)
+    return fits(22) && c->prec == PREC_FP32 && nodes <= 1000000 ? RegionPlan{22, 3} : RegionPlan{0, 0};
+  return nodes <= 160000 ? RegionPlan{16, 3} : RegionPlan{0, 0};
 }
 
 // The march of large lattices (launch_march): steps per launch and rows per chunk, {0, 0} where the

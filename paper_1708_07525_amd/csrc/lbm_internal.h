@@ -102,8 +102,7 @@ int launch_march(int prec, const void *desc, const void *ddev, int parity, int c
 void march_shape(int prec, int *steps, int *group_columns, int *groups_per_cu);
 // `steps` time steps per launch on small lattices: a region of side x side nodes (16 or 22) per
 // work-group, whose inner (side - 2 (steps - 1))^2 nodes, at least 4^2, it stores; fields read from
-// d4, written to d4b; walls through the nodes with FP32 and FP64 storage on lattices that hold
-// one such tile (else hipErrorInvalidValue)
+// d4, written to d4b; walls through the nodes on lattices that hold one such tile (else hipErrorInvalidValue)
 int launch_region(int prec, const void *desc, const void *ddev, int parity, int steps, int side, void *stream);
 // range: device pointer to {first item, item count} of the group to step; parity bit 0
 // selects the population buffers, bit 1 the field buffer (d4b when set)

@@ -1819,7 +1819,7 @@ struct NodeWalls {
 // its own moving populations for the walls (half-way bounce-back); LDS holds two copies of
 // the 16 moving populations, written in turn, so that a step takes one barrier.
 // NEE: walls through the boundary nodes, as in two_step_tile (the last tiles sit against the
-// far walls, FP32 and FP64 storage); a boundary node pulls whole neighbours, so LDS holds the
+// far walls); a boundary node pulls whole neighbours, so LDS holds the
 // rest populations too.
 template <int RW_>
 struct Region {
@@ -2549,8 +2549,8 @@ static int region_rw(int prec, const void *desc, const void *ddev, int parity, i
       return ((const Desc<float> *)desc)->nee ? region_t<float, true, RG>(desc, ddev, parity, steps, stream)
                                               : region_t<float, false, RG>(desc, ddev, parity, steps, stream);
     default:
-      if (((const Desc<float> *)desc)->nee) return (int)hipErrorInvalidValue;   // FP16: one step per launch
-      return region_t<_Float16, false, RG>(desc, ddev, parity, steps, stream);
+      return ((const Desc<float> *)desc)->nee ? region_t<_Float16, true, RG>(desc, ddev, parity, steps, stream)
+                                              : region_t<_Float16, false, RG>(desc, ddev, parity, steps, stream);
   }
 }
 

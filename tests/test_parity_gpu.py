@@ -609,6 +609,33 @@ def test_fields_reach_the_host_whole(prec, nx, ny):
         x.close()
 
 
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("walls", ["half_way", "periodic_x", "periodic_y"])
+def test_three_step_tile_at_every_remainder(prec, walls):
+    """The three-step tile, whose LDS planes share the rows that are written but never read, against
+    one step per launch, bit for bit: a wall or a wrap at every row of the last tile (and of its ring)
+    and at some of its columns."""
+    Solver = _solver()
+    sides = {"half_way": ("hot", "cold", "adiabatic", "hot"), "periodic_x": ("periodic", "periodic", "cold", "adiabatic"),
+             "periodic_y": ("adiabatic", "cold", "periodic", "periodic")}[walls]
+    lid = tuple(0.0 if k == "periodic" else u for k, u in zip(sides, (0.01, -0.01, 0.015, 0.02)))
+    for k in range(8):
+        nx, ny = 64 + (k * 9) % 33, 40 + k
+        rng = np.random.default_rng([nx, ny])
+        p = workloads.cavity_params(nx=nx, ny=ny, sides=sides, Ra=1e4, wall_u=lid)
+        kw = dict(phi=rng.uniform(0.4, 0.8, (ny, nx)), T=rng.uniform(0.4, 0.6, (ny, nx)),
+                  C=rng.uniform(0.4, 0.6, (ny, nx)))
+        state = []
+        for spl in (1, 3):
+            s = Solver(p, precision=prec, **kw)
+            s.set_steps_per_launch(spl)
+            s.step(24)
+            state.append(s.get_state())
+            s.close()
+        d = _state_diff(state[1], state[0])
+        assert d is None, (nx, ny, d)
+
+
 def test_graph_replays_match_plain_launches():
     """lbm_step uses a captured graph for chunks of 64 steps; replays interleaved with other
     work must give the same state as one launch per step."""

@@ -577,21 +577,25 @@ LBM_API lbm_status lbm_derive(const lbm_params *p, lbm_derived *out) {
   return LBM_OK;
 }
 
-// Pinned buffers of large exports (HostExport), kept between calls: allocating one for every call
-// costs 0.1-1 ms.  At most kKept of them, given back with the last context of the process; a call
-// that finds none idle (several threads export at once) or needs a larger one takes its own.
+// Pinned host memory: of every context (kObsOut values, and the fields of a small lattice) and of a
+// call that exports the fields of a large one (HostExport).  Allocating it costs 0.06 ms (a context)
+// to 1 ms (an export), so blocks of three sizes are kept between uses, a bounded number of each, and
+// given back with the last context of the process.  A caller that finds none idle takes a new one.
 class PinnedPool {
  public:
-  static constexpr size_t kBytes = 16 << 20, kKept = 2;
+  static constexpr int kClasses = 3;
+  static constexpr size_t kBytes[kClasses] = {4 << 10, 260 << 10, 16 << 20};
+  static constexpr size_t kKept[kClasses] = {16, 16, 2};
   void *take(size_t bytes) {
-    if (bytes <= kBytes) {
+    const int k = size_class(bytes);
+    if (k < kClasses) {
       std::lock_guard<std::mutex> lock(mu_);
-      if (!idle_.empty()) {
-        void *p = idle_.back();
-        idle_.pop_back();
+      if (!idle_[k].empty()) {
+        void *p = idle_[k].back();
+        idle_[k].pop_back();
         return p;
       }
-      bytes = kBytes;
+      bytes = kBytes[k];
     }
     void *p = nullptr;
     if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return p;
@@ -599,10 +603,12 @@ class PinnedPool {
     return nullptr;
   }
   void give(void *p, size_t bytes) {
-    if (bytes <= kBytes) {
+    if (!p) return;
+    const int k = size_class(bytes);
+    if (k < kClasses) {
       std::lock_guard<std::mutex> lock(mu_);
-      if (contexts_ > 0 && idle_.size() < kKept) {
-        idle_.push_back(p);
+      if (contexts_ > 0 && idle_[k].size() < kKept[k]) {
+        idle_[k].push_back(p);
         return;
       }
     }
@@ -613,14 +619,23 @@ class PinnedPool {
     {
       std::lock_guard<std::mutex> lock(mu_);
       contexts_ += change;
-      if (contexts_ == 0) drop.swap(idle_);
+      if (contexts_ == 0)
+        for (auto &v : idle_) {
+          drop.insert(drop.end(), v.begin(), v.end());
+          v.clear();
+        }
     }
     for (void *p : drop) (void)hipHostFree(p);
   }
 
  private:
+  static int size_class(size_t bytes) {
+    int k = 0;
+    while (k < kClasses && bytes > kBytes[k]) ++k;
+    return k;
+  }
   std::mutex mu_;
-  std::vector<void *> idle_;
+  std::vector<void *> idle_[kClasses];
   int contexts_ = 0;
 };
 static PinnedPool &pinned_pool() {
@@ -635,6 +650,7 @@ static size_t host_export_doubles(const lbm_ctx *c) {
   const size_t n = 5 * (size_t)c->p.nx * c->p.ny;
   return n * sizeof(double) <= kHostExport ? n : 0;
 }
+static size_t host_bytes(const lbm_ctx *c) { return (kObsOut + host_export_doubles(c)) * sizeof(double); }
 
 LBM_API lbm_status lbm_create(const lbm_params *p, lbm_ctx **out) {
   if (!p || !out) return LBM_EINVAL;
@@ -672,9 +688,8 @@ LBM_API lbm_status lbm_create(const lbm_params *p, lbm_ctx **out) {
     }
     c->owned = true;
   }
-  if (hipHostMalloc((void **)&c->host, (kObsOut + host_export_doubles(c)) * sizeof(double), hipHostMallocDefault) !=
-      hipSuccess) {
-    (void)hipGetLastError();
+  c->host = (double *)pinned_pool().take(host_bytes(c));
+  if (!c->host) {
     if (c->owned) (void)hipFree(c->base);
     delete c;
     return LBM_ENOMEM;
@@ -699,7 +714,7 @@ LBM_API void lbm_destroy(lbm_ctx *c) {
   }
   drop_graph(c);
   if (c->owned && c->base) (void)hipFree(c->base);
-  (void)hipHostFree(c->host);
+  pinned_pool().give(c->host, host_bytes(c));
   delete c;
   pinned_pool().context(-1);
 }
@@ -900,7 +915,7 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
 // that all waves run at once and end together; a chunk costs steps - 1 extra rows at either end,
 // so the lattice must be large enough for tall ones.  Measured (GLUPS, march against the tiled
 // launches; rows per chunk in brackets): FP64 4096^2 42.2 (147) against 27.6, 2048^2 39.5 (37)
-// against 30.4, 1280 x 1300 33.8 (16) against 27.8, 1024^2 29.3 (11) against 24.1, 700^2 22.1 (6)
+// against 30.4, 1280 x 1300 33.8 (16) against 27.8, 1024^2 29.3 (11) against 27.8, 700^2 22.1 (6)
 // against 26.1; FP32 4096^2 78.3 (74) against 72.2, 2048^2 72.2 (19) against 63.8, 1536^2 65.5
 // (11) against 58.5, 1280 x 1300 59.2 (8) against 54.1, 1024^2 48.0 (7) against 58.7.  Hence chunks
 // of at least 10 rows in FP64 and 8 in FP32.  Walls through the nodes, where the tiled launch takes
@@ -1094,7 +1109,7 @@ LBM_API lbm_status lbm_step(lbm_ctx *c, int64_t nsteps) {
 struct HostExport {
   static constexpr size_t kLeast = 2 << 20;  // bytes from which it pays: see export_fields
   static constexpr size_t kChunkBytes = 2 << 20, kSlots = 8;
-  static_assert(kChunkBytes * kSlots <= PinnedPool::kBytes, "the pool's buffers hold the slots");
+  static_assert(kChunkBytes * kSlots <= PinnedPool::kBytes[2], "the pool's blocks hold the slots");
   static constexpr int kMaxThreads = 8;
   lbm_ctx *c;
   double *fields, *pinned;
@@ -1603,8 +1618,8 @@ struct BatchGroup {
 // default, three steps per launch where the chunk and the precision allow it, else shape 0; and
 // the cache policy (-1: the default rule).  Set by lbm_batch_set_tile or lbm_batch_autotune.
 // Three against two steps (shape 0), GLUPS, 12 cavities of 64^2, 128^2, 256^2 and 8 of 512^2:
-// FP32 14.4 / 13.3, 39.2 / 36.0, 66.2 / 57.0, 68.2 / 57.6; FP64 11.9 / 10.8, 21.6 / 22.6,
-// 27.4 / 25.0, 29.4 / 25.8.
+// FP32 14.4 / 13.3, 39.2 / 36.0, 66.2 / 57.0, 68.2 / 57.6; FP64 11.9 / 10.8, 26.6 / 22.6,
+// 30.4 / 24.9, 33.0 / 26.4.
 struct BatchChoice {
   int shape = -1, cp = -1;
 };

@@ -578,54 +578,50 @@ LBM_API lbm_status lbm_derive(const lbm_params *p, lbm_derived *out) {
 }
 
 // Pinned host memory: of every context (kObsOut values, and the fields of a small lattice) and of a
-// call that exports the fields of a large one (HostExport).  Allocating it costs 0.06 ms (a context)
-// to 1 ms (an export), so blocks of three sizes are kept between uses, a bounded number of each, and
-// given back with the last context of the process.  A caller that finds none idle takes a new one.
+// call that exports the fields of a large one (HostExport).  Allocating and freeing it costs 0.06-0.3
+// ms, so blocks of three sizes are kept between uses and given back with the last context of the
+// process.  The contexts' blocks are cut from slabs, as many as the contexts that lived at once
+// needed; of the exports' at most kKept stay idle.  A caller that finds none idle takes new memory.
 class PinnedPool {
  public:
   static constexpr int kClasses = 3;
   static constexpr size_t kBytes[kClasses] = {4 << 10, 260 << 10, 16 << 20};
-  static constexpr size_t kKept[kClasses] = {16, 16, 2};
+  static constexpr size_t kSlab[kClasses] = {16, 4, 1};       // blocks of one allocation
+  static constexpr size_t kKept = 2;
   void *take(size_t bytes) {
     const int k = size_class(bytes);
-    if (k < kClasses) {
-      std::lock_guard<std::mutex> lock(mu_);
-      if (!idle_[k].empty()) {
-        void *p = idle_[k].back();
-        idle_[k].pop_back();
-        return p;
-      }
-      bytes = kBytes[k];
+    std::lock_guard<std::mutex> lock(mu_);
+    if (k < kClasses && !idle_[k].empty()) {
+      void *p = idle_[k].back();
+      idle_[k].pop_back();
+      return p;
     }
     void *p = nullptr;
-    if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return p;
-    (void)hipGetLastError();
-    return nullptr;
+    if (hipHostMalloc(&p, k < kClasses ? kSlab[k] * kBytes[k] : bytes, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    if (k < kClasses && kSlab[k] > 1) {
+      slabs_.push_back(p);
+      for (size_t b = 1; b < kSlab[k]; ++b) idle_[k].push_back((char *)p + b * kBytes[k]);
+    }
+    return p;
   }
   void give(void *p, size_t bytes) {
     if (!p) return;
     const int k = size_class(bytes);
-    if (k < kClasses) {
-      std::lock_guard<std::mutex> lock(mu_);
-      if (contexts_ > 0 && idle_[k].size() < kKept[k]) {
-        idle_[k].push_back(p);
-        return;
-      }
-    }
-    (void)hipHostFree(p);
+    std::lock_guard<std::mutex> lock(mu_);
+    if (k < kClasses && (kSlab[k] > 1 || (contexts_ > 0 && idle_[k].size() < kKept))) idle_[k].push_back(p);
+    else (void)hipHostFree(p);
   }
   void context(int change) {   // a context more (1) or less (-1)
-    std::vector<void *> drop;
-    {
-      std::lock_guard<std::mutex> lock(mu_);
-      contexts_ += change;
-      if (contexts_ == 0)
-        for (auto &v : idle_) {
-          drop.insert(drop.end(), v.begin(), v.end());
-          v.clear();
-        }
-    }
-    for (void *p : drop) (void)hipHostFree(p);
+    std::lock_guard<std::mutex> lock(mu_);
+    contexts_ += change;
+    if (contexts_ > 0) return;
+    for (void *p : idle_[2]) (void)hipHostFree(p);
+    for (void *p : slabs_) (void)hipHostFree(p);
+    slabs_.clear();
+    for (auto &v : idle_) v.clear();
   }
 
  private:
@@ -635,7 +631,7 @@ class PinnedPool {
     return k;
   }
   std::mutex mu_;
-  std::vector<void *> idle_[kClasses];
+  std::vector<void *> idle_[kClasses], slabs_;
   int contexts_ = 0;
 };
 static PinnedPool &pinned_pool() {
@@ -688,13 +684,14 @@ LBM_API lbm_status lbm_create(const lbm_params *p, lbm_ctx **out) {
     }
     c->owned = true;
   }
+  pinned_pool().context(1);   // before it takes a block of the pool's
   c->host = (double *)pinned_pool().take(host_bytes(c));
   if (!c->host) {
+    pinned_pool().context(-1);
     if (c->owned) (void)hipFree(c->base);
     delete c;
     return LBM_ENOMEM;
   }
-  pinned_pool().context(1);
   *out = c;
   return LBM_OK;
 }

@@ -11,7 +11,7 @@
 // Cavities whose walls pass through the boundary nodes (Eqs. 33-37, 39) have their
 // perimeter nodes rebuilt by non-equilibrium extrapolation: in a one-step launch by
 // work-groups of their own at its front (nee_node, the tiles skip those nodes), in the
-// two-step kernel by the tiles themselves.
+// two-step kernel and the region kernel by the tiles themselves.
 // The 9x9 and 5x5 transforms are written out as sums with the integer / rational
 // coefficients of M, N and their inverses (the inverse of an orthogonal-row matrix is its
 // transpose over the squared row norms 9, 36, 36, 6, 12, 6, 12, 4, 4 and 5, 2, 2, 20, 4).
@@ -26,7 +26,9 @@
 // one step's loads and stores per launch; they visit their tiles in vertical strips (tile_of),
 // so that the halo rows a tile reads from global memory are still in its XCD's L2, and FP32
 // (three steps) and FP16 storage (two steps) have a taller tile for lattices that stream from
-// HBM.
+// HBM.  Large FP32 and FP64 lattices take march_kernel (waves march up strips of columns, four
+// time levels in a pipeline of rows), small lattices region_kernel (one thread per node of a
+// small square region, 3 to 6 steps in LDS).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -1543,8 +1545,8 @@ __device__ __forceinline__ double from_right(double v) {
 // The four waves of a work-group take neighbouring strips and meet at a barrier every row: their
 // rows lie side by side in the same cache lines.
 // Bound: FP64 by memory (1.7 GB a launch at 2048^2 in 410 us; its access pattern alone takes 335
-// us), FP32 by instruction issue (VALU busy 0.76, 331 instructions per level and node before the
-// steady loop was split off).  Measured (2048^2 banded cavity): FP64 39.5-41.6 GLUPS against 30.4
+// us; VALU busy 0.51), FP32 by instruction issue (VALU busy 0.79, 408 lane-instructions per node and
+// step).  Measured (2048^2 banded cavity): FP64 39.5-41.6 GLUPS against 30.4
 // for step3_kernel, FP32 72.2-73.4 against 63.8; without the barrier FP32 62.5, with one wave per
 // SIMD (all state in registers) FP64 29.6.  FP16 storage (three levels) lost 2% to step2_kernel.
 template <typename S>

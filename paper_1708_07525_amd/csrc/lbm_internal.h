@@ -128,9 +128,10 @@ void two_step_tile_shape(int prec, int *w, int *h);
 int batch_tile_shapes();
 void batch_tile_shape(int prec, int shape, int *w, int *h);
 // observables: partial sums per block, then a final fixed-order reduction.
-// out: kObsOut doubles, 12 slots (see lbm_api.cpp), Nu[4], Sh[4]
+// out: kObsOut doubles, 12 slots (see lbm_api.cpp), Nu[4], Sh[4]; fields: NULL, or the fields of
+// all rows as launch_export gives them
 int launch_observables(int prec, const void *desc, int parity, void *snap, double *partials,
-                       int nblocks, double *out, const double *wall_T, const double *wall_C,
+                       int nblocks, double *out, double *fields, const double *wall_T, const double *wall_C,
                        double L_over_dT, double L_over_dC, void *stream);
 constexpr int kObsOut = 20;
 // fields of `rows` rows from y0 on: 5 planes of nx * rows

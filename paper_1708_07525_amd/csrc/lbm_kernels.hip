@@ -2204,7 +2204,8 @@ __device__ __forceinline__ double wave_max(double v) {
 template <typename S>
 __global__ void __launch_bounds__(OBS_THREADS) obs_partial_kernel(Desc<typename St<S>::R> d, int parity,
                                                                   typename St<S>::R *__restrict__ snap,
-                                                                  double *__restrict__ partials) {
+                                                                  double *__restrict__ partials,
+                                                                  double *__restrict__ fields) {
   using R = typename St<S>::R;
   const long long P = d.plane;
   const int cur = (d.base_parity ^ parity) & 1;
@@ -2238,6 +2239,14 @@ __global__ void __launch_bounds__(OBS_THREADS) obs_partial_kernel(Desc<typename 
       acc[10] = fmax(acc[10], fabs(uy));
       const bool bad = !(isfinite(rho) && isfinite(T) && isfinite(C) && isfinite(ux) && isfinite(uy));
       acc[11] += bad ? 1.0 : 0.0;
+      if (fields) {                        // as export_kernel
+        const long long n = (long long)d.nx * d.ny, k = (long long)y * d.nx + x;
+        fields[k] = rho;
+        fields[n + k] = ux;
+        fields[2 * n + k] = uy;
+        fields[3 * n + k] = T;
+        fields[4 * n + k] = C;
+      }
       snap[c] = (R)dT;
       snap[P + c] = (R)dC;
       snap[2 * P + c] = (R)ux;
@@ -2753,25 +2762,25 @@ int launch_step_batch(int prec, int cp, const void *descs, const Item *items, co
 int observables_blocks(int ny) { return (ny + OBS_ROWS - 1) / OBS_ROWS; }
 
 template <typename S>
-static int obs_t(const void *desc, int parity, void *snap, double *partials, int nblocks, double *out,
+static int obs_t(const void *desc, int parity, void *snap, double *partials, int nblocks, double *out, double *fields,
                  const double *wT, const double *wC, double LdT, double LdC, void *stream) {
   using R = typename St<S>::R;
   const auto &d = *(const Desc<R> *)desc;
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(obs_partial_kernel<S>, dim3(nblocks), dim3(OBS_THREADS), 0, s, d, parity, (R *)snap,
-                     partials);
+                     partials, fields);
   hipLaunchKernelGGL(obs_final_kernel<R>, dim3(NSLOT + 4), dim3(OBS_THREADS), 0, s, d, partials, nblocks, wT, wC,
                      LdT, LdC, out);
   return (int)hipGetLastError();
 }
 
 int launch_observables(int prec, const void *desc, int parity, void *snap, double *partials, int nblocks,
-                       double *out, const double *wT, const double *wC, double LdT, double LdC,
+                       double *out, double *fields, const double *wT, const double *wC, double LdT, double LdC,
                        void *stream) {
   switch (prec) {
-    case PREC_FP64: return obs_t<double>(desc, parity, snap, partials, nblocks, out, wT, wC, LdT, LdC, stream);
-    case PREC_FP32: return obs_t<float>(desc, parity, snap, partials, nblocks, out, wT, wC, LdT, LdC, stream);
-    default: return obs_t<_Float16>(desc, parity, snap, partials, nblocks, out, wT, wC, LdT, LdC, stream);
+    case PREC_FP64: return obs_t<double>(desc, parity, snap, partials, nblocks, out, fields, wT, wC, LdT, LdC, stream);
+    case PREC_FP32: return obs_t<float>(desc, parity, snap, partials, nblocks, out, fields, wT, wC, LdT, LdC, stream);
+    default: return obs_t<_Float16>(desc, parity, snap, partials, nblocks, out, fields, wT, wC, LdT, LdC, stream);
   }
 }
 

@@ -596,12 +596,23 @@ class PinnedPool {
       idle_[k].pop_back();
       return p;
     }
+    const bool slab = k < kClasses && kSlab[k] > 1;
+    try {                      // room first, so that nothing below can throw (nor give() for a slab's block)
+      if (slab) {
+        slabs_.reserve(slabs_.size() + 1);
+        idle_[k].reserve((slabs_.size() + 1) * kSlab[k]);
+      }
+      idle_[2].reserve(kKept);
+    } catch (const std::bad_alloc &) {
+      return nullptr;
+    }
     void *p = nullptr;
-    if (hipHostMalloc(&p, k < kClasses ? kSlab[k] * kBytes[k] : bytes, hipHostMallocPortable) != hipSuccess) {
+    if (hipHostMalloc(&p, k < kClasses ? kSlab[k] * kBytes[k] : bytes, hipHostMallocPortable | hipHostMallocCoherent) !=
+        hipSuccess) {
       (void)hipGetLastError();
       return nullptr;
     }
-    if (k < kClasses && kSlab[k] > 1) {
+    if (slab) {
       slabs_.push_back(p);
       for (size_t b = 1; b < kSlab[k]; ++b) idle_[k].push_back((char *)p + b * kBytes[k]);
     }
@@ -1211,14 +1222,19 @@ static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = null
     x.rows = (int)std::min<size_t>(c->p.ny, std::max<size_t>(1, HostExport::kChunkBytes / row));
     x.chunks = (c->p.ny + x.rows - 1) / x.rows;
     x.slots = std::min<size_t>(x.chunks, HostExport::kSlots);
-    x.left.assign(x.chunks, 5);
+    try {
+      x.left.assign(x.chunks, 5);
+      x.written.reserve(x.slots);
+    } catch (const std::bad_alloc &) {
+      return fail(c, LBM_ENOMEM, "field export");
+    }
     const size_t pinned_bytes = x.slots * x.rows * row;
     x.pinned = (double *)pinned_pool().take(pinned_bytes);
     if (x.pinned) {
       he = hipSuccess;
       for (size_t k = 0; k < x.slots && he == hipSuccess; ++k) {
         hipEvent_t ev;
-        he = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        he = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem);
         if (he == hipSuccess) x.written.push_back(ev);
       }
       // a thread per half MB: starting one takes some 15 us, copying half a MB into new pages 150 us
@@ -1924,14 +1940,22 @@ struct CaptureFork {
   }
   hipError_t stream(hipStream_t *q) {
     const hipError_t e = hipStreamCreateWithFlags(q, hipStreamNonBlocking);
-    if (e == hipSuccess) streams.push_back(*q);
-    return e;
+    return e == hipSuccess ? keep(streams, *q) : e;
+  }
+  template <typename V, typename T>
+  static hipError_t keep(V &v, T x) {
+    try {
+      v.push_back(x);
+    } catch (const std::bad_alloc &) {
+      return hipErrorOutOfMemory;
+    }
+    return hipSuccess;
   }
   hipError_t order(hipStream_t from, hipStream_t to) {   // what `to` gets next follows what `from` has
     hipEvent_t ev;
     hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = keep(events, ev);
     if (e != hipSuccess) return e;
-    events.push_back(ev);
     e = hipEventRecord(ev, from);
     return e == hipSuccess ? hipStreamWaitEvent(to, ev, 0) : e;
   }

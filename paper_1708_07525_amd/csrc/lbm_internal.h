@@ -76,6 +76,28 @@ struct Tile {
   int tx, ty;
 };
 
+// Tile of work-group b in a region launch over tiles ntx across, row by row (kernels and host).
+struct TileIndex {
+  int bx, by;
+};
+// b / ntx by a multiplication with ceil(2^32 / ntx), 0 standing for ntx = 1.  It adds less than
+// b / 2^32 to the quotient, whose distance to the next whole number is at least 1 / ntx: exact
+// while tiles x ntx <= 2^32.
+constexpr uint32_t tile_divisor(int ntx) { return ntx > 1 ? (uint32_t)(((1ull << 32) + ntx - 1) / ntx) : 0u; }
+constexpr bool tile_divisor_exact(long long tiles, int ntx) { return ntx == 1 || tiles * ntx <= 1ll << 32; }
+constexpr TileIndex region_tile(int b, int ntx, uint32_t divisor) {
+  const int by = divisor ? (int)(((unsigned long long)(uint32_t)b * divisor) >> 32) : b;
+  return TileIndex{b - by * ntx, by};
+}
+// The frame of ntx x nty tiles: the first and the last row (unless periodic in y), then the other
+// rows' first and last tiles.  Two rows need no quotient, which would not be exact for every
+// width that a lattice can have (from 46508 tiles on).
+constexpr TileIndex frame_tile(int b, int ntx, int nty, bool pery) {
+  const int q = b - (pery ? 0 : 2 * ntx);
+  if (q < 0) return b < ntx ? TileIndex{b, 0} : TileIndex{b - ntx, nty - 1};
+  return TileIndex{q & 1 ? ntx - 1 : 0, (pery ? 0 : 1) + (q >> 1)};
+}
+
 // ---- launchers (defined in lbm_kernels.hip) ---------------------------------------------
 // All take a hipStream_t as void*; return a hipError_t as int.
 int launch_init(int prec, const void *desc, const double *T, const double *C, const double *ux,

@@ -1870,19 +1870,9 @@ __global__ void __launch_bounds__(RG::THREADS, RG::THREADS / 256)
   const rsrc_t fwrite = make_rsrc((parity & 1) ? d.d4 : d.d4b, ND4 * PR);
   const uint32_t step = d.counter[cur];
   const int edge = steps - 1, tile = RW - 2 * edge;
-  // tile index over ntx by a multiplication with ceil(2^32 / ntx), exact for tiles x ntx < 2^32; 0: ntx = 1
   const int b = xcd_remap(blockIdx.x, gridDim.x);
-  int by = inv_ntx ? (int)__umulhi((uint32_t)b, inv_ntx) : b, bx = b - by * ntx;
-  if (NEE && nty > 0) {                    // the frame of ntx x nty tiles: first and last rows, then columns
-    const int q = b - (d.pery ? 0 : 2 * ntx);
-    if (q < 0) {
-      by = by ? nty - 1 : 0;
-    } else {
-      bx = q & 1 ? ntx - 1 : 0;
-      by = (d.pery ? 0 : 1) + (q >> 1);
-    }
-  }
-  int x0 = bx * tile, y0 = by * tile;
+  const TileIndex at = NEE && nty > 0 ? frame_tile(b, ntx, nty, d.pery != 0) : region_tile(b, ntx, inv_ntx);
+  int x0 = at.bx * tile, y0 = at.by * tile;
   if ((x0 | y0) == 0 && threadIdx.x == 0) d.counter[cur ^ 1] = step + (uint32_t)steps;
   if (NEE) {
     x0 = min(x0, nx - tile);
@@ -2529,10 +2519,10 @@ static int region_t(const void *desc, const void *ddev, int parity, int steps, v
   const int tile = RG::RW - 2 * (steps - 1);
   if (tile < 4 || (NEE && (d.nx < tile || d.ny < tile))) return (int)hipErrorInvalidValue;
   const int ntx = (d.nx + tile - 1) / tile, nty = (d.ny + tile - 1) / tile;
+  if (!frame && !tile_divisor_exact((long long)ntx * nty, ntx)) return (int)hipErrorInvalidValue;
   const int grid = !frame ? ntx * nty : (d.pery ? 0 : 2 * ntx) + (d.perx ? 0 : 2 * (nty - (d.pery ? 0 : 2)));
   hipLaunchKernelGGL((region_kernel<S, NEE, RG>), dim3(grid), dim3(RG::THREADS), 0, (hipStream_t)stream,
-                     (const Desc<typename St<S>::R> *)ddev, ntx, ntx > 1 ? (uint32_t)(((1ull << 32) + ntx - 1) / ntx) : 0u,
-                     parity, steps, frame ? nty : 0);
+                     (const Desc<typename St<S>::R> *)ddev, ntx, tile_divisor(ntx), parity, steps, frame ? nty : 0);
   return (int)hipGetLastError();
 }
 

@@ -1277,11 +1277,13 @@ static lbm_status observe(lbm_ctx *c, lbm_obs *out, double *fields, double *part
                              host_fields ? c->host + kObsOut : nullptr, c->wall_dev(),
                              c->wall_dev() + 4, c->dv.dT != 0 ? c->dv.L / c->dv.dT : 0.0,
                              c->dv.dC != 0 ? c->dv.L / c->dv.dC : 0.0, c->stream);
-  if (e) return hip_fail(c, (hipError_t)e, "observables launch");
-  if (fields && !host_fields) {   // waits for the stream
-    lbm_status fs = export_fields(c, fields, stage);
-    if (fs != LBM_OK) return fs;
-  } else {
+  lbm_status fs = e ? hip_fail(c, (hipError_t)e, "observables launch") : LBM_OK;
+  if (fs == LBM_OK && fields && !host_fields) fs = export_fields(c, fields, stage);   // waits for the stream
+  if (fs != LBM_OK) {
+    (void)hipStreamSynchronize(c->stream);   // nothing writes to c->host any more: it may go to another context
+    return fs;
+  }
+  if (!fields || host_fields) {
     HIP_CHECK(c, hipStreamSynchronize(c->stream), "observables sync");
     if (host_fields) std::memcpy(fields, c->host + kObsOut, host_fields * sizeof(double));
   }

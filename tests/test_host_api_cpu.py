@@ -1,0 +1,83 @@
+"""The host side of the library (csrc/lbm_api.cpp) without a GPU: built with tests/hip_stub.cpp, whose
+HIP calls and launchers only keep a log."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import workloads
+from paper_1708_07525_amd.lbm import OK, Obs, make_params
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+VP, D = ctypes.c_void_p, ctypes.POINTER(ctypes.c_double)
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("host") / "libhost.so")
+    csrc = os.path.join(ROOT, "paper_1708_07525_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-w", "-pthread",
+                    "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+                    os.path.join(csrc, "lbm_api.cpp"), os.path.join(HERE, "hip_stub.cpp"), "-Wl,-z,defs", "-o", so],
+                   check=True)
+    lib = ctypes.CDLL(so)
+    lib.lbm_create.argtypes = [VP, ctypes.POINTER(VP)]
+    lib.lbm_set_fields.argtypes = [VP, D, D, D, D, D]
+    lib.lbm_step.argtypes = [VP, ctypes.c_int64]
+    lib.lbm_observables.argtypes = [VP, VP, D]
+    lib.lbm_get_fields.argtypes = [VP, D]
+    lib.lbm_destroy.argtypes = [VP]
+    lib.lbm_destroy.restype = None
+    lib.stub_calls.argtypes = [ctypes.c_char_p]
+    lib.stub_calls.restype = ctypes.c_longlong
+    lib.stub_fail.argtypes = [ctypes.c_char_p, ctypes.c_int]
+    lib.stub_launches.restype = ctypes.c_char_p
+    return lib
+
+
+@pytest.fixture()
+def lib(built):
+    built.stub_reset()
+    return built
+
+
+class Context:
+    """A context of the stub library; ready: with its initial fields."""
+
+    def __init__(self, lib, nx, ny, prec="fp32", ready=False, **kw):
+        self.lib, self.nx, self.ny, self.h = lib, nx, ny, VP()
+        p = make_params(workloads.cavity_params(nx=nx, ny=ny, **kw), prec)
+        assert lib.lbm_create(ctypes.byref(p), ctypes.byref(self.h)) == OK
+        if ready:
+            assert lib.lbm_set_fields(self.h, None, None, None, None, None) == OK
+
+    def fields(self):
+        f = np.empty((5, self.ny, self.nx))
+        return self.lib.lbm_get_fields(self.h, f.ctypes.data_as(D))
+
+    def look(self, fields=False):
+        f = np.empty((5, self.ny, self.nx)) if fields else None
+        o = Obs()
+        return self.lib.lbm_observables(self.h, ctypes.byref(o), f.ctypes.data_as(D) if fields else None)
+
+    def close(self):
+        self.lib.lbm_destroy(self.h)
+
+
+@pytest.mark.parametrize("n,call", [(200, b"hipMalloc"), (200, b"launch_export"), (64, b"launch_observables")])
+def test_a_failed_look_leaves_nothing_in_flight(lib, n, call):
+    """The observables' kernels write into the context's pinned block, which goes to another context
+    once this one is destroyed: a look that fails after their launch waits for them."""
+    c = Context(lib, n, n, ready=True)
+    lib.lbm_step(c.h, 3)
+    lib.stub_fail(call, 1)
+    assert c.look(fields=True) != OK
+    assert lib.stub_pending() == 0
+    assert c.look(fields=True) == OK
+    c.close()

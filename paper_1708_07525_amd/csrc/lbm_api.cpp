@@ -919,7 +919,7 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
 }
 
 // The march of large lattices (launch_march): steps per launch and rows per chunk, {0, 0} where the
-// tiled launches are faster.  The chunks are as tall as leaves every wave slot of the chip one, so
+// tiled launches are faster or ctx_region has a plan.  The chunks are as tall as leaves every wave slot of the chip one, so
 // that all waves run at once and end together; a chunk costs steps - 1 extra rows at either end,
 // so the lattice must be large enough for tall ones.  Measured (GLUPS, march against the tiled
 // launches; rows per chunk in brackets): FP64 4096^2 42.2 (147) against 27.6, 2048^2 39.5 (37)
@@ -935,7 +935,7 @@ struct MarchPlan {
   int steps, chunk;
 };
 static MarchPlan ctx_march(const lbm_ctx *c) {
-  if (!launch_defaults(c) || c->prec == PREC_FP16S || c->p.nx < 128) return {0, 0};
+  if (!launch_defaults(c) || c->prec == PREC_FP16S || c->p.nx < 128 || ctx_region(c).side) return {0, 0};
   int steps = 0, columns = 0, per_cu = 0;
   march_shape(c->prec, &steps, &columns, &per_cu);
   const int groups = (c->p.nx + columns - 1) / columns;

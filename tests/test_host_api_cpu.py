@@ -81,3 +81,25 @@ def test_a_failed_look_leaves_nothing_in_flight(lib, n, call):
     assert lib.stub_pending() == 0
     assert c.look(fields=True) == OK
     c.close()
+
+
+NODE = ("nee_hot", "nee_robin", "nee_adiabatic", "nee_cold")
+
+
+@pytest.mark.parametrize("nx,ny,prec", [(128, 7200, "fp32"), (135, 7300, "fp32"), (139, 7194, "fp32")])
+def test_one_launch_in_effect(lib, nx, ny, prec):
+    """Narrow lattices between node walls that the region launch's rule and the march's both take: one
+    of the two is in effect, for the getters, plain launches and graph replays alike."""
+    c = Context(lib, nx, ny, prec, ready=True, sides=NODE, Bi_T=1.0, Bi_C=1.0)
+    region, march = lib.lbm_get_region_steps(c.h), lib.lbm_get_march_steps(c.h)
+    assert region == 0 or march == 0
+    lib.stub_reset()
+    assert lib.lbm_step(c.h, 64 + 12) == OK     # a replay (what it leaves of 64) and plain launches
+    log = lib.stub_launches().decode().split()
+    assert log.index("]") > 1
+    for k in log:
+        if k not in ("[", "]", "graph"):
+            assert k.startswith("region" if region else "march" if march else "step"), log
+            if region:
+                assert int(k.split("/")[1]) <= region, log
+    c.close()

@@ -91,8 +91,8 @@ Layout plan_layout(int nx, int ny, int prec) {
   L.off_snap = take((size_t)ND4 * L.plane * rs);
   L.off_counter = take(2 * sizeof(unsigned));
   L.off_desc = take(4 * kDescSlot);
-  // small: wall T (4), wall C (4), partials
-  L.off_small = take((8 + (size_t)L.nblocks_obs * 12) * sizeof(double));
+  // small: wall T (4), wall C (4), obs out (32), partials
+  L.off_small = take((8 + 32 + (size_t)L.nblocks_obs * 12) * sizeof(double));
   L.total = off;
   return L;
 }
@@ -108,7 +108,9 @@ struct lbm_ctx {
   char *base = nullptr;      // device memory (arena or owned)
   bool owned = false;
   bool ready = false;
-  double *host = nullptr;    // pinned: kObsOut observables, then export_doubles of exported fields
+  double *host = nullptr;    // pinned: kObsOut observables, then host_export_doubles of exported fields (see pinned_block)
+  int looks = 0;             // looks without it that could have allocated it
+  size_t exported = 0;       // bytes of fields exported without a block of the pool's largest
   bool unstable = false;     // lbm_observables found a non-finite value: lbm_step refuses to go on
   double *scratch = nullptr; // device address of the fixed scratch on this context's device
   lbm_batch *batch = nullptr;   // the batch this context is attached to, if any
@@ -143,7 +145,8 @@ struct lbm_ctx {
   void *snap() const { return base + lay.off_snap; }
   unsigned *counter() const { return (unsigned *)(base + lay.off_counter); }
   double *wall_dev() const { return (double *)(base + lay.off_small); }
-  double *partials() const { return wall_dev() + 8; }
+  double *obs_out() const { return wall_dev() + 8; }
+  double *partials() const { return wall_dev() + 40; }
   const void *desc() const { return prec == PREC_FP64 ? (const void *)&d64 : (const void *)&d32; }
   // the device copy of the descriptor for population buffer `pc` and field buffer `fc`
   const void *desc_dev(int pc, int fc) const { return base + lay.off_desc + (size_t)(2 * pc + fc) * kDescSlot; }
@@ -577,18 +580,21 @@ LBM_API lbm_status lbm_derive(const lbm_params *p, lbm_derived *out) {
   return LBM_OK;
 }
 
-// Pinned host memory: of every context (kObsOut values, and the fields of a small lattice) and of a
-// call that exports the fields of a large one (HostExport).  Allocating and freeing it costs 0.06-0.3
-// ms, so blocks of three sizes are kept between uses and given back with the last context of the
-// process.  The contexts' blocks are cut from slabs, as many as the contexts that lived at once
-// needed; of the exports' at most kKept stay idle.  A caller that finds none idle takes new memory.
+// Pinned host memory: of the contexts (kObsOut values, and the fields of a small lattice) and of a
+// call that exports the fields of a large one (HostExport).  Allocating and freeing it costs 0.03-0.3
+// ms, and the first use of a large block up to 3 ms of page faults, so blocks of three sizes are kept
+// between uses and given back with the last context of the process, and a caller that finds none idle
+// allocates only where it will look again and again (pinned_block, export_fields): a program with one
+// context at a time must not pay for memory that each context uses once.  The contexts' blocks are cut
+// from slabs, as many as the contexts that lived at once needed; of the exports' at most kKept stay idle.
 class PinnedPool {
  public:
   static constexpr int kClasses = 3;
   static constexpr size_t kBytes[kClasses] = {4 << 10, 260 << 10, 16 << 20};
   static constexpr size_t kSlab[kClasses] = {16, 4, 1};       // blocks of one allocation
   static constexpr size_t kKept = 2;
-  void *take(size_t bytes) {
+  // an idle block, or a new one where the caller may allocate; NULL otherwise
+  void *take(size_t bytes, bool allocate) {
     const int k = size_class(bytes);
     std::lock_guard<std::mutex> lock(mu_);
     if (k < kClasses && !idle_[k].empty()) {
@@ -596,6 +602,7 @@ class PinnedPool {
       idle_[k].pop_back();
       return p;
     }
+    if (!allocate) return nullptr;
     const bool slab = k < kClasses && kSlab[k] > 1;
     try {                      // room first, so that nothing below can throw (nor give() for a slab's block)
       if (slab) {
@@ -658,6 +665,15 @@ static size_t host_export_doubles(const lbm_ctx *c) {
   return n * sizeof(double) <= kHostExport ? n : 0;
 }
 static size_t host_bytes(const lbm_ctx *c) { return (kObsOut + host_export_doubles(c)) * sizeof(double); }
+// c->host, if the context has it: an idle block of the pool's, or from the fourth look on that may
+// allocate a new one.  Without it the results take the way through device memory: 64^2, a look
+// 31 us instead of 21, with fields 51 instead of 29; the block costs 15 us to allocate and 28 to free, so
+// a context of three looks is no slower than without it and one of many loses some 40 us in all.
+constexpr int kLooksBefore = 3;
+static bool pinned_block(lbm_ctx *c, bool allocate) {
+  if (!c->host) c->host = (double *)pinned_pool().take(host_bytes(c), allocate && ++c->looks > kLooksBefore);
+  return c->host != nullptr;
+}
 
 LBM_API lbm_status lbm_create(const lbm_params *p, lbm_ctx **out) {
   if (!p || !out) return LBM_EINVAL;
@@ -695,14 +711,7 @@ LBM_API lbm_status lbm_create(const lbm_params *p, lbm_ctx **out) {
     }
     c->owned = true;
   }
-  pinned_pool().context(1);   // before it takes a block of the pool's
-  c->host = (double *)pinned_pool().take(host_bytes(c));
-  if (!c->host) {
-    pinned_pool().context(-1);
-    if (c->owned) (void)hipFree(c->base);
-    delete c;
-    return LBM_ENOMEM;
-  }
+  pinned_pool().context(1);
   *out = c;
   return LBM_OK;
 }
@@ -1116,6 +1125,10 @@ LBM_API lbm_status lbm_step(lbm_ctx *c, int64_t nsteps) {
 // new; the kernel's stores reach 53 GB/s.
 struct HostExport {
   static constexpr size_t kLeast = 2 << 20;  // bytes from which it pays: see export_fields
+  // bytes a context exports through device memory before it has a block allocated where none is idle (a
+  // larger export at once).  512^2: 650 us a call that way, 430 with a block, but 1700 for the call that
+  // allocates it and touches it first; 1024^2 4900 that way (2600 into touched memory), 2800 for the call that allocates it.
+  static constexpr size_t kBytesBefore = 40 << 20;
   static constexpr size_t kChunkBytes = 2 << 20, kSlots = 8;
   static_assert(kChunkBytes * kSlots <= PinnedPool::kBytes[2], "the pool's blocks hold the slots");
   static constexpr int kMaxThreads = 8;
@@ -1197,8 +1210,8 @@ static bool device_memory(const void *p) {
 }
 
 // FP64 fields of the current level into host memory: through the context's pinned memory (small
-// lattices), through `stage` (5 nx ny doubles of device memory) where it is given, by HostExport
-// (large ones), else through device memory of this call.  Measured against a device buffer
+// lattices, once it has it), through `stage` (5 nx ny doubles of device memory) where it is given, by HostExport
+// (large ones, where its block is idle or the context has exported much), else through device memory of this call.  Measured against a device buffer
 // and a copy for every size: 64^2 22 us against 95, 256^2 0.33 ms against 0.65, 512^2 0.50 against
 // 1.32, 1024^2 1.2 against 4.6, 2048^2 3.9 against 16.3; 200^2, below kLeast, takes 0.11 either way.
 static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = nullptr) {
@@ -1206,7 +1219,7 @@ static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = null
   const size_t n = 5 * (size_t)c->p.nx * c->p.ny, bytes = n * sizeof(double);
   hipError_t he;
   const bool host = !device_memory(fields);   // a caller's array in device memory takes the copy
-  if (host && host_export_doubles(c)) {
+  if (host && c->host && host_export_doubles(c)) {
     double *out = c->host + kObsOut;
     he = (hipError_t)launch_export(c->prec, c->desc(), 0, 0, c->p.ny, out, c->stream);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
@@ -1229,7 +1242,8 @@ static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = null
       return fail(c, LBM_ENOMEM, "field export");
     }
     const size_t pinned_bytes = x.slots * x.rows * row;
-    x.pinned = (double *)pinned_pool().take(pinned_bytes);
+    c->exported += bytes;
+    x.pinned = (double *)pinned_pool().take(pinned_bytes, c->exported >= HostExport::kBytesBefore);
     if (x.pinned) {
       he = hipSuccess;
       for (size_t k = 0; k < x.slots && he == hipSuccess; ++k) {
@@ -1261,33 +1275,40 @@ static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = null
 LBM_API lbm_status lbm_get_fields(lbm_ctx *c, double *fields) {
   if (!c || !fields) return LBM_EINVAL;
   if (!c->ready) return fail(c, LBM_ESTATE, "lbm_get_fields before lbm_set_fields");
+  if (host_export_doubles(c)) (void)pinned_block(c, true);
   return export_fields(c, fields);
 }
 
-// The observables of the current level, with the per-block partial sums in `partials`, the 20
-// result slots in `slots` and, when fields is not NULL, the field export staged in `stage`
-// (NULL: allocated for the call).
+// The observables of the current level, with the per-block partial sums in `partials` and, when fields
+// is not NULL and they do not go through pinned memory, the field export staged in `stage`.  stage NULL: the
+// call may allocate.
 static lbm_status observe(lbm_ctx *c, lbm_obs *out, double *fields, double *partials, double *stage) {
   set_parity(c, c->cur);
   const int nb = c->lay.nblocks_obs;
   // the fields of a small lattice come with the sums, from the same loads and without a launch of their
   // own (64^2, 12 steps and a look: 50.7 to 48.6 us; 80^2 FP16, 30 steps: 90.7 to 84.6)
-  const size_t host_fields = fields && !device_memory(fields) ? host_export_doubles(c) : 0;
-  int e = launch_observables(c->prec, c->desc(), 0, c->snap(), partials, nb, c->host,
+  const bool pinned = pinned_block(c, stage == nullptr);
+  const size_t host_fields = pinned && fields && !device_memory(fields) ? host_export_doubles(c) : 0;
+  int e = launch_observables(c->prec, c->desc(), 0, c->snap(), partials, nb, pinned ? c->host : c->obs_out(),
                              host_fields ? c->host + kObsOut : nullptr, c->wall_dev(),
                              c->wall_dev() + 4, c->dv.dT != 0 ? c->dv.L / c->dv.dT : 0.0,
                              c->dv.dC != 0 ? c->dv.L / c->dv.dC : 0.0, c->stream);
   lbm_status fs = e ? hip_fail(c, (hipError_t)e, "observables launch") : LBM_OK;
+  double copied[kObsOut];
+  if (fs == LBM_OK && !pinned) {
+    const hipError_t he = hipMemcpyAsync(copied, c->obs_out(), sizeof copied, hipMemcpyDeviceToHost, c->stream);
+    if (he != hipSuccess) fs = hip_fail(c, he, "observables copy");
+  }
   if (fs == LBM_OK && fields && !host_fields) fs = export_fields(c, fields, stage);   // waits for the stream
   if (fs != LBM_OK) {
-    (void)hipStreamSynchronize(c->stream);   // nothing writes to c->host any more: it may go to another context
+    (void)hipStreamSynchronize(c->stream);   // nothing writes to c->host (it may go to another context) or copied any more
     return fs;
   }
   if (!fields || host_fields) {
     HIP_CHECK(c, hipStreamSynchronize(c->stream), "observables sync");
     if (host_fields) std::memcpy(fields, c->host + kObsOut, host_fields * sizeof(double));
   }
-  const double *r = c->host;
+  const double *r = pinned ? c->host : copied;
   std::memset(out, 0, sizeof *out);
   out->step = c->step;
   out->mass = r[0];

@@ -195,7 +195,7 @@ int launch_export(int, const void *, int, int, int rows, double *, void *) {
 int observables_blocks(int ny) { return (ny + 3) / 4; }
 StaticScratchLayout static_scratch_layout() { return StaticScratchLayout{16384, 1 << 20, 0, 1 << 16, 1 << 23}; }
 int static_scratch_address(int, double **p) {
-  static double scratch[1];
+  static double scratch[1 << 23];
   *p = scratch;
   return 0;
 }

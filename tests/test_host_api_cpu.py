@@ -31,6 +31,7 @@ def built(tmp_path_factory):
     lib.lbm_set_fields.argtypes = [VP, D, D, D, D, D]
     lib.lbm_step.argtypes = [VP, ctypes.c_int64]
     lib.lbm_observables.argtypes = [VP, VP, D]
+    lib.lbm_observables_static.argtypes = [VP, VP, D]
     lib.lbm_get_fields.argtypes = [VP, D]
     lib.lbm_destroy.argtypes = [VP]
     lib.lbm_destroy.restype = None
@@ -61,10 +62,11 @@ class Context:
         f = np.empty((5, self.ny, self.nx))
         return self.lib.lbm_get_fields(self.h, f.ctypes.data_as(D))
 
-    def look(self, fields=False):
+    def look(self, fields=False, static=False):
         f = np.empty((5, self.ny, self.nx)) if fields else None
         o = Obs()
-        return self.lib.lbm_observables(self.h, ctypes.byref(o), f.ctypes.data_as(D) if fields else None)
+        fn = self.lib.lbm_observables_static if static else self.lib.lbm_observables
+        return fn(self.h, ctypes.byref(o), f.ctypes.data_as(D) if fields else None)
 
     def close(self):
         self.lib.lbm_destroy(self.h)
@@ -103,3 +105,62 @@ def test_one_launch_in_effect(lib, nx, ny, prec):
             if region:
                 assert int(k.split("/")[1]) <= region, log
     c.close()
+
+
+def test_pinned_memory_is_for_contexts_that_look_often(lib):
+    """One context at a time: creating, stepping, three looks and destroying allocate no pinned memory;
+    the fourth look does.  Others take what lies idle, and the last one gives everything back."""
+    for _ in range(2):
+        c = Context(lib, 64, 64, ready=True)
+        for fields in (False, True, False):
+            assert c.look(fields=fields) == OK
+        c.close()
+    assert lib.stub_calls(b"hipHostMalloc") == 0 and lib.stub_calls(b"hipHostFree") == 0
+    c = Context(lib, 64, 64, ready=True)
+    for _ in range(4):
+        assert c.look(fields=True) == OK
+    assert lib.stub_calls(b"hipHostMalloc") == 1
+    d = Context(lib, 60, 60, ready=True)        # of the same size class: its first look finds an idle block
+    mallocs, copies = lib.stub_calls(b"hipMalloc"), lib.stub_calls(b"hipMemcpyAsync")
+    assert d.look(fields=True) == OK
+    assert lib.stub_calls(b"hipMalloc") == mallocs and lib.stub_calls(b"hipMemcpyAsync") == copies
+    assert lib.stub_calls(b"hipHostMalloc") == 1
+    c.close()
+    assert lib.stub_calls(b"hipHostFree") == 0
+    d.close()
+    assert lib.stub_calls(b"hipHostFree") == 1
+
+
+def test_static_looks_allocate_nothing(lib):
+    c = Context(lib, 64, 64, ready=True)
+    lib.stub_reset()
+    for _ in range(8):
+        assert c.look(fields=True, static=True) == OK
+    assert lib.stub_calls(b"hipHostMalloc") == 0 and lib.stub_calls(b"hipMalloc") == 0
+    c.close()
+
+
+def test_looks_without_pinned_memory(lib):
+    """No pinned memory to be had: looks and exports take the way through device memory."""
+    lib.stub_fail(b"hipHostMalloc", 1000)
+    c, big = Context(lib, 64, 64, ready=True), Context(lib, 520, 500, ready=True)
+    for _ in range(6):
+        assert c.look(fields=True) == OK and c.fields() == OK and big.look(fields=True) == OK and big.fields() == OK
+    c.close()
+    big.close()
+
+
+def test_exports_allocate_their_block_once_it_pays(lib):
+    """512 x 512 fields (10.5 MB): through device memory until the context has exported 40 MB; an idle
+    block is taken at once."""
+    c = Context(lib, 512, 512, ready=True)
+    for k in range(4):
+        assert lib.stub_calls(b"hipHostMalloc") == 0
+        assert c.fields() == OK
+    assert lib.stub_calls(b"hipHostMalloc") == 1
+    d = Context(lib, 300, 400, ready=True)
+    mallocs = lib.stub_calls(b"hipMalloc")
+    assert d.fields() == OK
+    assert lib.stub_calls(b"hipMalloc") == mallocs and lib.stub_calls(b"hipHostMalloc") == 1
+    c.close()
+    d.close()

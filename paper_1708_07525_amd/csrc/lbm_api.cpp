@@ -1130,11 +1130,10 @@ struct HostExport {
   // allocates it and touches it first; 1024^2 4900 that way (2600 into touched memory), 2800 for the call that allocates it.
   static constexpr size_t kBytesBefore = 40 << 20;
   static constexpr size_t kChunkBytes = 2 << 20, kSlots = 8;
-  static_assert(kChunkBytes * kSlots <= PinnedPool::kBytes[2], "the pool's blocks hold the slots");
   static constexpr int kMaxThreads = 8;
   lbm_ctx *c;
   double *fields, *pinned;
-  size_t slots;                              // slots of the pinned buffer, rows * nx * 5 doubles each
+  size_t slots;                              // slots of the pinned buffer, rows * nx * 5 doubles each: a block of the pool's
   int rows, chunks;
   std::vector<hipEvent_t> written;           // per slot
   std::mutex mu;
@@ -1227,14 +1226,16 @@ static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = null
     std::memcpy(fields, out, bytes);
     return LBM_OK;
   }
-  if (host && !stage && bytes >= HostExport::kLeast) {
+  // rows above kChunkBytes (52429 columns and more) are chunks of their own, as many slots as the pool's block
+  // holds of them; two at least, so that one is copied while the next is written
+  const size_t row = 5 * (size_t)c->p.nx * sizeof(double), block = PinnedPool::kBytes[2];
+  if (host && !stage && bytes >= HostExport::kLeast && 2 * row <= block) {
     HostExport x{};
     x.c = c;
     x.fields = fields;
-    const size_t row = 5 * (size_t)c->p.nx * sizeof(double);
     x.rows = (int)std::min<size_t>(c->p.ny, std::max<size_t>(1, HostExport::kChunkBytes / row));
     x.chunks = (c->p.ny + x.rows - 1) / x.rows;
-    x.slots = std::min<size_t>(x.chunks, HostExport::kSlots);
+    x.slots = std::min<size_t>({(size_t)x.chunks, HostExport::kSlots, block / (x.rows * row)});
     try {
       x.left.assign(x.chunks, 5);
       x.written.reserve(x.slots);

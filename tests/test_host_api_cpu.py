@@ -164,3 +164,16 @@ def test_exports_allocate_their_block_once_it_pays(lib):
     assert lib.stub_calls(b"hipMalloc") == mallocs and lib.stub_calls(b"hipHostMalloc") == 1
     c.close()
     d.close()
+
+
+@pytest.mark.parametrize("nx,ny,blocks", [(52429, 21, 1), (60000, 20, 1), (200000, 6, 1), (250000, 5, 0)])
+def test_exports_of_wide_rows_keep_their_block(lib, nx, ny, blocks):
+    """Rows above 2 MB: the slots fit the block that the pool keeps, which a second export finds idle; rows
+    above 8 MB go through device memory."""
+    c = Context(lib, nx, ny, ready=True)
+    lib.stub_reset()
+    for _ in range(3):
+        assert c.fields() == OK
+    assert lib.stub_calls(b"hipHostMalloc") == blocks
+    assert lib.stub_calls(b"pinned bytes") == blocks * (16 << 20)
+    c.close()

@@ -1252,9 +1252,10 @@ static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = null
         he = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem);
         if (he == hipSuccess) x.written.push_back(ev);
       }
-      // a thread per half MB: starting one takes some 15 us, copying half a MB into new pages 150 us
+      // a thread per MB: starting one takes some 15 us (256^2 174 us with one per half MB, 149 with one
+      // per MB; 300^2 236 / 159, 400^2 348 / 303, 512^2 and more the same)
       const size_t cpus = std::max(1u, std::thread::hardware_concurrency());
-      const int threads = (int)std::min<size_t>({bytes >> 19, cpus, (size_t)HostExport::kMaxThreads});
+      const int threads = (int)std::min<size_t>({bytes >> 20, cpus, (size_t)HostExport::kMaxThreads});
       if (he == hipSuccess) he = x.run(threads);
       const hipError_t drained = hipStreamSynchronize(c->stream);   // nothing writes to the slots any more
       if (he == hipSuccess) he = drained;

@@ -91,7 +91,7 @@ hipError_t hipGetDevice(int *d) {
   *d = 0;
   return hipSuccess;
 }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipSetDevice(int) { return called("hipSetDevice"); }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
   memset(p, 0, sizeof *p);
   strcpy(p->gcnArchName, "gfx950");

@@ -177,3 +177,16 @@ def test_exports_of_wide_rows_keep_their_block(lib, nx, ny, blocks):
     assert lib.stub_calls(b"hipHostMalloc") == blocks
     assert lib.stub_calls(b"pinned bytes") == blocks * (16 << 20)
     c.close()
+
+
+@pytest.mark.parametrize("n,threads", [(256, 2), (400, 6), (512, 8)])
+def test_exports_start_a_thread_per_mb(lib, n, threads):
+    """256 x 256 fields are 2.6 MB: five threads cost more to start than they save."""
+    keep, c = Context(lib, 1100, 1000, ready=True), Context(lib, n, n, ready=True)
+    assert keep.fields() == OK                  # leaves an idle block
+    lib.stub_reset()
+    assert c.fields() == OK
+    assert lib.stub_calls(b"hipMalloc") == 0
+    assert lib.stub_calls(b"hipSetDevice") == min(threads, len(os.sched_getaffinity(0)))
+    c.close()
+    keep.close()

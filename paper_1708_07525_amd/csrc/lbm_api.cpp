@@ -935,23 +935,56 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
 // against 30.4, 1280 x 1300 33.8 (16) against 27.8, 1024^2 29.3 (11) against 27.8, 700^2 22.1 (6)
 // against 26.1; FP32 4096^2 78.3 (74) against 72.2, 2048^2 72.2 (19) against 63.8, 1536^2 65.5
 // (11) against 58.5, 1280 x 1300 59.2 (8) against 54.1, 1024^2 48.0 (7) against 58.7.  Hence chunks
-// of at least 10 rows in FP64 and 8 in FP32.  Walls through the nodes, where the tiled launch takes
+// of at least 9 rows in FP64 (1000^2 below) and 8 in FP32.  Walls through the nodes, where the tiled launch takes
 // two steps: FP32 4096^2 77.0 against 50.9, 2048^2 66.2 against 48.3, 1280 x 1300 53.4 (8) against 42.1,
 // 1150^2 49.6 (6) against 50.6; FP64 4096^2 40.8 against 22.9, 2048^2 38.9 against 23.5, 900^2 25.4
 // (8) against 19.6, 800^2 22.9 (7) against 22.5, 700^2 19.0 (6) against 19.8: from 7 rows in FP64.  FP16 storage (three levels) lost 2% at 2048^2, 12% at
 // 1536^2 and won 12% at 3000^2: not there.
+// Columns: a strip stores 58, a work-group has four strips, so where the strips are no multiple of four waves
+// stay without one, half of them at 233 columns.  "Packed", the strips of neighbouring chunks share
+// work-groups instead; it pays where the last work-group is thin and costs a little where it is nearly
+// full (the chunks are shorter, the rows of a work-group no longer side by side).  Measured (us per step, packed /
+// whole work-groups / tiled launch; rows per packed chunk): FP32 233 x 9000 37.0 / 50.5 / 38.8 (11), 300 x 6007 31.3 /
+// 35.9 / 33.0 (9), 465 x 9000 62.4 / 68.0 / 65.5 (20), 930 x 3000 (17 strips) 43.3 / 42.5 / 44.1; FP64 233 x 30000
+// 204 / 300 / 215 (74), 465 x 9000 116 / 141 / 127 (40), 1000^2 33.0 / 34.7 / 36.2 (9), 1100 x 1600 (19 strips) 49.8 /
+// 51.0 / 54.5; node walls FP32 300 x 6007 40.3 / 44.7 / 47.7 (9), 580 x 3000 32.9 / 33.3 / 43.5, 760 x 2000 - / 29.9 / 34.4
+// (7), FP64 465 x 3000 52.4 / 59.1 / 65.4 (14).  (FP32 between node walls counts the strips between them.)
+// Walls half a spacing outside, where the tile is the faster three-step one: the columns of the
+// strips may also exceed those of the tiles the less the shorter the chunks are.  FP64 233 x 9000 (290
+// columns against 256, 23 rows) 69.8 packed against 66.7 tiled, 300 x 4200 (348 / 320, 13 rows) 43.6 / 42.2, 465 x 3000 (522 / 480,
+// 14 rows) 47.0 / 44.5, 175 x 12000 (232 / 192, 24 rows) 71.6 / 66.3, but 140 x 20000 (174 / 160, 30 rows) 88.7 / 91.4, 200
+// x 5001 (232 / 224, 10 rows) 36.2 / 37.3; FP32 128 x 20000 (174 / 128, 15 rows) 44.7 / 42.5, 175 x 12000 (232 / 192, 12 rows)
+// 38.9 / 39.9.
 struct MarchPlan {
   int steps, chunk;
+  bool packed;
 };
 static MarchPlan ctx_march(const lbm_ctx *c) {
-  if (!launch_defaults(c) || c->prec == PREC_FP16S || c->p.nx < 128 || ctx_region(c).side) return {0, 0};
+  const MarchPlan none{0, 0, false};
+  if (!launch_defaults(c) || c->prec == PREC_FP16S || c->p.nx < 128 || ctx_region(c).side) return none;
+  const bool nee = node_walls(&c->p), fp64 = c->prec == PREC_FP64;
   int steps = 0, columns = 0, per_cu = 0;
   march_shape(c->prec, &steps, &columns, &per_cu);
-  const int groups = (c->p.nx + columns - 1) / columns;
-  const int chunks = std::max(1, kComputeUnits * per_cu / groups);
+  auto strips_of = [&](int nx) { return (nx + columns - 1) / columns; };
+  auto fill = [](int strips) { return (double)strips / ((strips + kMarchWaves - 1) / kMarchWaves * kMarchWaves); };
+  const int strips = strips_of(c->p.nx);
+  bool packed = fill(strips) < (fp64 ? 0.92 : 0.88);
+  if (nee && !fp64) {
+    const int inner = strips_of(c->p.nx - (c->p.side[LEFT] == SIDE_PERIODIC ? 0 : 2 * kMarchWalls));
+    packed = inner > kMarchWaves && fill(inner) < 0.8;
+  }
+  const int waves = kComputeUnits * per_cu * kMarchWaves;
+  const int chunks = std::max(1, waves / (packed ? strips : (strips + kMarchWaves - 1) / kMarchWaves * kMarchWaves));
   const int chunk = (c->p.ny + chunks - 1) / chunks;
-  const int least = c->prec == PREC_FP32 ? 8 : node_walls(&c->p) ? 7 : 10;
-  return chunk >= least && c->p.ny >= (node_walls(&c->p) ? 64 : 16) ? MarchPlan{steps, chunk} : MarchPlan{0, 0};
+  const int least = !fp64 ? 8 : nee ? 7 : 9;
+  if (chunk < least || c->p.ny < (nee ? 64 : 16)) return none;
+  if (!nee) {
+    int w = 0, h = 0;
+    two_step_tile_shape(c->prec, &w, &h);   // (as wide as the three-step tile)
+    const int tiles = (c->p.nx + w - 1) / w * w;
+    if (tiles < strips * columns * (1.0 - chunk / (fp64 ? 200.0 : 60.0))) return none;
+  }
+  return MarchPlan{steps, chunk, packed};
 }
 
 // n steps with plain launches: three or two steps per launch as ctx_spl allows, the remainder
@@ -979,7 +1012,7 @@ static lbm_status step_plain(lbm_ctx *c, int64_t n) {
   while (n > 0) {
     set_parity(c, c->cur);
     if (mp.steps && n >= mp.steps) {
-      int e = launch_march(c->prec, c->desc(), c->desc_dev(c->cur, c->d4cur), 0, mp.chunk, c->stream);
+      int e = launch_march(c->prec, c->desc(), c->desc_dev(c->cur, c->d4cur), 0, mp.chunk, mp.packed, c->stream);
       if (e) return hip_fail(c, (hipError_t)e, "march kernel launch");
       c->d4cur ^= 1;
       n -= mp.steps;
@@ -1058,7 +1091,8 @@ static lbm_status ensure_graph(lbm_ctx *c) {
         e = (hipError_t)launch_region(c->prec, c->desc(), c->desc_dev(cur, d4), 0, spl, side, cs);
         d4 ^= 1;
       } else if (march) {
-        e = (hipError_t)launch_march(c->prec, c->desc(), c->desc_dev(cur, d4), 0, march, cs);
+        e = (hipError_t)launch_march(c->prec, c->desc(), c->desc_dev(cur, d4), 0, march,
+                                     ctx_march(c).packed, cs);
         d4 ^= 1;
       } else if (spl == 3) {
         e = (hipError_t)launch_step3(c->prec, c->desc(), c->desc_dev(cur, d4), cp, 0, sw, rows3, cs);

@@ -1543,7 +1543,9 @@ __device__ __forceinline__ double from_right(double v) {
 // what a bounce-back returns, so that every node pulls alike; the fixed-value and moving-wall
 // terms are added to the pulls (wall_rules).
 // The four waves of a work-group take neighbouring strips and meet at a barrier every row: their
-// rows lie side by side in the same cache lines.
+// rows lie side by side in the same cache lines.  `across` strips are counted per chunk: a multiple of four,
+// which leaves waves without a strip where nstrips is none (they end at once), or nstrips, where
+// a work-group's waves may stand in two chunks (ctx_march has the choice).
 // Bound: FP64 by memory (1.7 GB a launch at 2048^2 in 410 us; its access pattern alone takes 335
 // us; VALU busy 0.51), FP32 by instruction issue (VALU busy 0.79, 408 lane-instructions per node and
 // step).  Measured (2048^2 banded cavity): FP64 39.5-41.6 GLUPS against 30.4
@@ -1557,7 +1559,6 @@ template <>
 struct March<double> {
   static constexpr int K = 4, NL = 12, WAVES_PER_EU = 2;
 };
-constexpr int kMarchWaves = 4;                               // strips of a work-group
 template <typename S>
 constexpr int kMarchStrip = 64 - 2 * (March<S>::K - 1);      // columns a strip stores
 
@@ -1569,6 +1570,7 @@ constexpr int kMarchStrip = 64 - 2 * (March<S>::K - 1);      // columns a strip 
 constexpr int kFrameRegion = 22;                             // region side of the frame's launch
 template <typename S>
 constexpr int kMarchFrame = kFrameRegion - 2 * (March<S>::K - 1);
+static_assert(kMarchFrame<float> == kMarchWalls && kMarchFrame<double> == kMarchWalls, "the host counts strips between them");
 
 template <typename R>
 struct MarchRows {
@@ -1577,7 +1579,7 @@ struct MarchRows {
 
 template <typename S, bool NEE>
 __global__ void __launch_bounds__(64 * kMarchWaves, March<S>::WAVES_PER_EU)
-    march_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int nstrips, int chunk, int parity) {
+    march_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int nstrips, int across, int chunk, int parity) {
   using R = typename St<S>::R;
   constexpr int CP = CP_RESIDENT;
   using FIO = FieldIO<S, CP>;
@@ -1586,9 +1588,8 @@ __global__ void __launch_bounds__(64 * kMarchWaves, March<S>::WAVES_PER_EU)
   __shared__ R held[kMarchWaves * H * NL * 64 + 2];
   const Desc<R> &d = *dp;
   const int job = xcd_remap(blockIdx.x, gridDim.x);
-  const int groups = (nstrips + kMarchWaves - 1) / kMarchWaves;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
-  const int cy = job / groups, strip = (job - cy * groups) * kMarchWaves + wave;
+  const int q = job * kMarchWaves + wave, cy = q / across, strip = q - cy * across;
   const int nx = d.nx, ny = d.ny, pitch = d.pitch;
   const uint32_t PR = (uint32_t)d.plane * RS;
   const int cur = (d.base_parity ^ parity) & 1;
@@ -1598,10 +1599,10 @@ __global__ void __launch_bounds__(64 * kMarchWaves, March<S>::WAVES_PER_EU)
   ws.d4 = make_rsrc((parity & 1) ? d.d4 : d.d4b, ND4 * PR);
   const uint32_t step = d.counter[cur];
   if (job == 0 && threadIdx.x == 0) d.counter[cur ^ 1] = step + (uint32_t)K;
-  if (strip >= nstrips) return;            // (a wave that has ended counts as arrived at the barriers)
-
   const bool perx = NEE || d.perx != 0, pery = NEE || d.pery != 0;   // (NEE: no wall in reach)
   const int fx = NEE && !d.perx ? kMarchFrame<S> : 0, fy = NEE && !d.pery ? kMarchFrame<S> : 0;
+  const int ya = fy + cy * chunk, yb = min(ya + chunk, ny - fy);
+  if (strip >= nstrips || ya >= yb) return;   // (a wave that has ended counts as arrived at the barriers)
   const int x0 = fx + strip * V - H, xv = x0 + lane;
   // the lane's column: wrapped across periodic sides; beyond a wall the nearest one (its values are
   // never used there, the ghost's are set below)
@@ -1610,7 +1611,6 @@ __global__ void __launch_bounds__(64 * kMarchWaves, March<S>::WAVES_PER_EU)
   const bool inner_x = x0 >= 1 && x0 + 64 <= nx - 1;             // every pull of level 1 stays inside in x
   const bool ghost_l = !perx && xv == -1, ghost_r = !perx && xv == nx;
   const bool mine = lane >= H && lane < H + V && xv < nx - fx;
-  const int ya = fy + cy * chunk, yb = min(ya + chunk, ny - fy);
   // rows of level l: [first(l), last(l)), rows beyond a periodic side counted on
   auto first = [&](int l) { return pery ? ya - (K - l) : max(0, ya - (K - l)); };
   auto last = [&](int l) { return pery ? yb + (K - l) : min(ny, yb + (K - l)); };
@@ -2527,38 +2527,40 @@ static int region_t(const void *desc, const void *ddev, int parity, int steps, v
 }
 
 template <typename S>
-static int march_t(const void *desc, const void *ddev, int parity, int chunk, void *stream) {
+static int march_t(const void *desc, const void *ddev, int parity, int chunk, bool packed, void *stream) {
   const auto &d = *(const Desc<typename St<S>::R> *)desc;
   // one wrap across a periodic side; three frame tiles side by side at least
   if (d.nx < 128 || d.ny < (d.nee ? 64 : 16) || chunk < 1) return (int)hipErrorInvalidValue;
   const int frame = d.nee ? 2 * kMarchFrame<S> : 0;
   const int w = d.nx - (d.perx ? 0 : frame), h = d.ny - (d.pery ? 0 : frame);
   const int nstrips = (w + kMarchStrip<S> - 1) / kMarchStrip<S>, nch = (h + chunk - 1) / chunk;
-  const int groups = (nstrips + kMarchWaves - 1) / kMarchWaves;
+  const int across = packed ? nstrips : (nstrips + kMarchWaves - 1) / kMarchWaves * kMarchWaves;
   const auto *dd = (const Desc<typename St<S>::R> *)ddev;
-  const dim3 grid(groups * nch), block(64 * kMarchWaves);
+  const dim3 grid((across * nch + kMarchWaves - 1) / kMarchWaves), block(64 * kMarchWaves);
   if (d.nee) {
     const int e = region_t<S, true, Region<kFrameRegion>>(desc, ddev, parity, March<S>::K, stream, true);
     if (e) return e;
-    hipLaunchKernelGGL((march_kernel<S, true>), grid, block, 0, (hipStream_t)stream, dd, nstrips, chunk, parity);
+    hipLaunchKernelGGL((march_kernel<S, true>), grid, block, 0, (hipStream_t)stream, dd, nstrips, across, chunk,
+                       parity);
   } else {
-    hipLaunchKernelGGL((march_kernel<S, false>), grid, block, 0, (hipStream_t)stream, dd, nstrips, chunk, parity);
+    hipLaunchKernelGGL((march_kernel<S, false>), grid, block, 0, (hipStream_t)stream, dd, nstrips, across, chunk,
+                       parity);
   }
   return (int)hipGetLastError();
 }
 
-int launch_march(int prec, const void *desc, const void *ddev, int parity, int chunk, void *stream) {
+int launch_march(int prec, const void *desc, const void *ddev, int parity, int chunk, bool packed, void *stream) {
   switch (prec) {
-    case PREC_FP64: return march_t<double>(desc, ddev, parity, chunk, stream);
-    case PREC_FP32: return march_t<float>(desc, ddev, parity, chunk, stream);
+    case PREC_FP64: return march_t<double>(desc, ddev, parity, chunk, packed, stream);
+    case PREC_FP32: return march_t<float>(desc, ddev, parity, chunk, packed, stream);
     default: return (int)hipErrorInvalidValue;   // FP16 storage: one or two steps per launch
   }
 }
 
-void march_shape(int prec, int *steps, int *group_columns, int *groups_per_cu) {
+void march_shape(int prec, int *steps, int *strip_columns, int *groups_per_cu) {
   *steps = prec == PREC_FP64 ? March<double>::K : March<float>::K;
-  *group_columns = kMarchWaves * (prec == PREC_FP64 ? kMarchStrip<double> : kMarchStrip<float>);
-  // work-groups of four waves, one per SIMD, that a CU holds
+  *strip_columns = prec == PREC_FP64 ? kMarchStrip<double> : kMarchStrip<float>;
+  // work-groups of kMarchWaves waves, one per SIMD, that a CU holds
   *groups_per_cu = prec == PREC_FP64 ? March<double>::WAVES_PER_EU : March<float>::WAVES_PER_EU;
 }
 

@@ -151,15 +151,15 @@ int launch_step2(int, const void *, const void *, int, int, int, int, void *) {
 int launch_step3(int, const void *, const void *, int, int, int, int, void *) {
   return launched("launch_step3", "step3");
 }
-int launch_march(int, const void *, const void *, int, int chunk, void *) {
-  return launched("launch_march", "march/" + std::to_string(chunk));
+int launch_march(int, const void *, const void *, int, int chunk, bool packed, void *) {
+  return launched("launch_march", std::string(packed ? "packed/" : "march/") + std::to_string(chunk));
 }
 int launch_region(int, const void *, const void *, int, int steps, int side, void *) {
   return launched("launch_region", "region" + std::to_string(side) + "/" + std::to_string(steps));
 }
 void march_shape(int prec, int *steps, int *columns, int *per_cu) {
   *steps = 4;
-  *columns = 4 * 58;
+  *columns = 58;
   *per_cu = prec == PREC_FP64 ? 2 : 4;
 }
 int launch_step_batch(int, int, const void *, const Item *, const int *, int, int, void *) {

@@ -101,7 +101,7 @@ def test_one_launch_in_effect(lib, nx, ny, prec):
     assert log.index("]") > 1
     for k in log:
         if k not in ("[", "]", "graph"):
-            assert k.startswith("region" if region else "march" if march else "step"), log
+            assert k.startswith("region" if region else ("march", "packed") if march else "step"), log
             if region:
                 assert int(k.split("/")[1]) <= region, log
     c.close()
@@ -190,3 +190,25 @@ def test_exports_start_a_thread_per_mb(lib, n, threads):
     assert lib.stub_calls(b"hipSetDevice") == min(threads, len(os.sched_getaffinity(0)))
     c.close()
     keep.close()
+
+
+HALF = ("hot", "cold", "adiabatic", "adiabatic")
+
+
+@pytest.mark.parametrize("prec,sides,nx,ny,launch", [
+    ("fp32", HALF, 2048, 2048, "march/19"), ("fp64", HALF, 2048, 2048, "march/37"), ("fp32", NODE, 2048, 2048, "march/19"),
+    ("fp32", HALF, 128, 8000, "step3"), ("fp32", HALF, 128, 20000, "step3"), ("fp32", HALF, 233, 4200, "step3"),
+    ("fp32", HALF, 233, 9000, "packed/11"), ("fp32", HALF, 300, 4200, "step3"), ("fp32", HALF, 300, 6007, "packed/9"),
+    ("fp32", HALF, 465, 3000, "step3"), ("fp32", HALF, 1100, 1600, "march/8"), ("fp32", HALF, 180, 30000, "march/30"),
+    ("fp64", HALF, 128, 20000, "step3"), ("fp64", HALF, 233, 9000, "step3"), ("fp64", HALF, 300, 4200, "step3"),
+    ("fp64", HALF, 465, 3000, "step3"), ("fp64", HALF, 233, 30000, "packed/74"), ("fp64", HALF, 1000, 1000, "packed/9"),
+    ("fp64", HALF, 200, 5001, "march/10"), ("fp32", NODE, 300, 4200, "step2"), ("fp32", NODE, 300, 6007, "packed/9"),
+    ("fp32", NODE, 760, 2000, "march/8"), ("fp64", NODE, 465, 3000, "packed/14")])
+def test_march_where_its_strips_are_filled(lib, prec, sides, nx, ny, launch):
+    """Lattices of few columns: the march only where its strips and work-groups hold columns."""
+    c = Context(lib, nx, ny, prec, ready=True, sides=sides, Bi_T=1.0, Bi_C=1.0)
+    lib.stub_reset()
+    assert lib.lbm_step(c.h, 4 if launch[0] in "mp" else int(launch[-1])) == OK
+    assert lib.stub_launches().decode().split() == [launch]
+    assert (lib.lbm_get_march_steps(c.h) == 4) == (launch[0] in "mp")
+    c.close()

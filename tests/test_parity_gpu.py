@@ -573,6 +573,34 @@ def test_march_with_node_walls_matches_one_step(prec, nx, ny, walls):
         s.close()
 
 
+@pytest.mark.parametrize("prec,nx,ny,walls", [
+    ("fp32", 233, 9001, "half_way"), ("fp32", 580, 3001, "periodic_x"), ("fp32", 465, 4003, "periodic_y"),
+    ("fp64", 1000, 1003, "half_way"), ("fp64", 520, 3501, "periodic_x"), ("fp64", 580, 2000, "periodic_y"),
+    ("fp32", 300, 6007, "nee"), ("fp32", 520, 3507, "nee_x"), ("fp64", 300, 2501, "nee"), ("fp64", 140, 8001, "nee_y")])
+def test_march_across_chunks_matches_one_step(prec, nx, ny, walls):
+    """The march with work-groups that hold strips of two chunks (lattices whose strips do not fill
+    work-groups of four) against one step per launch, bit for bit; the last chunk is shorter."""
+    Solver = _solver()
+    sides = {"half_way": ("hot", "cold", "adiabatic", "hot"), "periodic_x": ("periodic", "periodic", "cold", "adiabatic"),
+             "periodic_y": ("adiabatic", "cold", "periodic", "periodic"),
+             "nee": ("nee_hot", "nee_robin", "nee_adiabatic", "nee_cold"),
+             "nee_x": ("nee_hot", "nee_robin", "periodic", "periodic"),
+             "nee_y": ("periodic", "periodic", "nee_cold", "nee_hot")}[walls]
+    lid = [0.0 if k == "periodic" else u for k, u in zip(sides, (0.01, -0.01, 0.015, 0.02))]
+    p = workloads.cavity_params(nx=nx, ny=ny, sides=sides, Ra=1e6, wall_u=tuple(lid), Bi_T=2.0, Bi_C=0.5)
+    rng = np.random.default_rng([nx, ny])
+    kw = dict(phi=rng.uniform(0.4, 0.8, (ny, nx)), T=rng.uniform(0.4, 0.6, (ny, nx)), C=rng.uniform(0.4, 0.6, (ny, nx)))
+    s = [Solver(p, precision=prec, **kw) for _ in range(2)]
+    s[0].set_steps_per_launch(1)
+    assert s[1].get_march_steps() == 4
+    for x in s:
+        x.step(23)
+    d = _state_diff(s[1].get_state(), s[0].get_state())
+    assert d is None, d
+    for x in s:
+        x.close()
+
+
 @pytest.mark.parametrize("prec,nx,ny", [("fp32", 3, 3), ("fp64", 80, 81), ("fp16s", 81, 81), ("fp32", 300, 250),
                                         ("fp32", 512, 103), ("fp64", 1000, 1000), ("fp16s", 333, 2000),
                                         ("fp32", 60000, 17)])

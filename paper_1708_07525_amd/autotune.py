@@ -17,9 +17,9 @@ DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "lbm_dd", "autot
 # part of every key: raised when the kernels' launch choices change (three steps per launch for
 # FP32, a three-step tile with its rest populations in registers, the tile order of the
 # multi-step launches, their taller tiles, the region launch of small and the march of
-# large lattices), so that choices
+# large lattices, the march's rule for lattices of few columns), so that choices
 # timed with older kernels are not applied to newer ones
-KERNEL_GENERATION = 5
+KERNEL_GENERATION = 6
 
 
 def cache_path() -> str:
@@ -63,20 +63,30 @@ def tune(solver, device_name: str, porosity_field: bool, steps: int = 20, path: 
          force: bool = False, node_walls: bool = False):
     """Apply the cached tile shape, cache policy, steps per launch, strip width and multi-step
     tile rows for this solver's class (walls through the boundary nodes are a class of their own), or
-    time all of them and cache the fastest.  Returns (tile_x, tile_y), ms_per_step (None when taken from the cache)."""
+    time all of them and cache the fastest.  The solver's own settings are replaced.  Returns
+    (tile_x, tile_y), ms_per_step (None when taken from the cache)."""
     k = key(device_name, solver.precision, solver.nx, solver.ny, porosity_field, node_walls)
 
-    def launch():                            # "region", "march" or "": the launch in effect by default
-        for name in ("region", "march"):
-            if getattr(solver, f"get_{name}_steps", lambda: 0)():
+    has_launches = hasattr(solver, "get_region_steps")
+
+    def launch():                            # "region", "march" or "": the launch in effect
+        for name in ("region", "march") if has_launches else ():
+            if getattr(solver, f"get_{name}_steps")():
                 return name
         return ""
-    if launch():                             # lattices that take them are classes of their own
-        k += "|" + launch()
+    if has_launches:                         # the key is of the lattice, whatever its caller has set
+        solver.set_tile(0, 0)
+        solver.set_cache_policy(-1)
+        solver.set_steps_per_launch(0)
+        solver.set_strip_width(-1)
+        solver.set_tile_rows(0)
+    default = launch()
+    if default:                              # lattices that take them are classes of their own
+        k += "|" + default
     entries = load(path)
-    if not force and k in entries:
+    if not force and k in entries and entries[k].get("launch", "") in ("", default):
         tx, ty = entries[k]["tile"]
-        if entries[k].get("launch"):         # the launch defaults were the fastest: keep them
+        if entries[k].get("launch"):         # the launch defaults, now in effect, were the fastest
             return (tx, ty), None
         solver.set_tile(tx, ty)
         solver.set_cache_policy(int(entries[k].get("policy", -1)))

@@ -80,3 +80,59 @@ def test_wall_families_are_tuned_apart(tmp_path):
     b = FakeSolver(100, 100)
     autotune.tune(b, "gpu", False, path=path, node_walls=True)
     assert a.timed == 1 and b.timed == 1 and len(autotune.load(path)) == 2
+
+
+class LaunchSolver(FakeSolver):
+    """A stand-in whose lattices of 1500 columns and more march by default, while nothing else is set;
+    tuned to the default launch (fastest == "march") or to a tile."""
+
+    def __init__(self, nx, ny, fastest):
+        super().__init__(nx, ny)
+        self.fastest = fastest
+        self.defaults()
+
+    def defaults(self):
+        self.tile, self.policy, self.spl, self.strip, self.rows = (0, 0), -1, 0, -1, 0
+
+    def get_region_steps(self):
+        return 0
+
+    def get_march_steps(self):
+        at_default = (self.tile, self.policy, self.spl, self.strip, self.rows) == ((0, 0), -1, 0, -1, 0)
+        return 4 if self.nx >= 1500 and at_default else 0
+
+    def autotune(self, steps):
+        self.timed += 1
+        self.defaults()
+        if self.fastest != "march":
+            self.tile, self.policy, self.spl, self.strip, self.rows = (128, 2), 1, 3, 8, 12
+        return self.tile, 0.25
+
+
+def test_a_set_solver_is_tuned_under_its_lattices_key(tmp_path):
+    """What the caller has set before does not choose the cache entry: a 1100^2 lattice, which does not
+    march, keeps its own entry beside that of a 2048^2 lattice of its size class, which does."""
+    path = str(tmp_path / "cache.json")
+    a = LaunchSolver(2048, 2048, "march")
+    a.set_steps_per_launch(2)                   # set by the caller before
+    assert autotune.tune(a, "gpu", False, path=path)[1] == 0.25 and a.get_march_steps() == 4
+    small = LaunchSolver(1100, 1100, "tile")
+    assert autotune.tune(small, "gpu", False, path=path)[1] == 0.25 and small.timed == 1
+    assert small.spl == 3 and len(autotune.load(path)) == 2
+    b = LaunchSolver(2048, 2048, "march")
+    b.set_steps_per_launch(1)                   # a slow setting does not stay
+    assert autotune.tune(b, "gpu", False, path=path)[1] is None and b.timed == 0 and b.get_march_steps() == 4
+    other = LaunchSolver(1100, 1100, "tile")
+    assert autotune.tune(other, "gpu", False, path=path)[1] is None and other.spl == 3 and other.rows == 12
+    assert autotune.tune(b, "gpu", False, path=path, force=True)[1] == 0.25 and b.timed == 1
+    assert len(autotune.load(path)) == 2
+
+
+def test_an_entry_of_another_launch_is_timed_again(tmp_path):
+    """An entry that names a launch which this lattice does not take by default is not applied."""
+    path = str(tmp_path / "cache.json")
+    k = autotune.key("gpu", "fp32", 1100, 1100, False)
+    autotune.store({k: {"tile": [256, 1], "launch": "march"}}, path)
+    s = LaunchSolver(1100, 1100, "tile")
+    assert autotune.tune(s, "gpu", False, path=path)[1] == 0.25 and s.timed == 1 and s.spl == 3
+    assert autotune.load(path)[k]["launch"] == ""

@@ -2032,7 +2032,12 @@ hipError_t batch_capture_steps(lbm_batch *b, int64_t n, hipStream_t s, CaptureFo
       bytes += b->groups[last].bytes;
       if (last > first && bytes > kGroupBytes) break;
     }
-    std::vector<hipStream_t> side(last - first, s);
+    std::vector<hipStream_t> side;
+    try {
+      side.assign(last - first, s);
+    } catch (const std::bad_alloc &) {   // (the caller ends the capture)
+      return hipErrorOutOfMemory;
+    }
     for (size_t k = 1; k < side.size() && e == hipSuccess; ++k) {
       e = fork.stream(&side[k]);
       if (e == hipSuccess) e = fork.order(s, side[k]);

@@ -7,6 +7,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 
 #include "lbm_internal.h"
@@ -18,7 +19,17 @@ std::map<std::string, int> fails;         // calls that are still to fail
 std::string launches;                     // the launches, in order
 bool capturing = false, pending = false;  // pending: a launch since the last wait
 
+// `new` of the library fails while a capture is under way and this is set (not that of this file)
+bool new_fails = false;
+thread_local bool in_capture = false, in_stub = false;
+struct Stub {
+  const bool was = in_stub;
+  Stub() { in_stub = true; }
+  ~Stub() { in_stub = was; }
+};
+
 hipError_t called(const char *name) {
+  Stub here;
   std::lock_guard<std::mutex> lock(mu);
   calls[name] += 1;
   auto f = fails.find(name);
@@ -27,6 +38,7 @@ hipError_t called(const char *name) {
   return hipErrorOutOfMemory;
 }
 int launched(const char *name, const std::string &what) {
+  Stub here;
   const hipError_t e = called(name);
   if (e != hipSuccess) return (int)e;
   std::lock_guard<std::mutex> lock(mu);
@@ -36,7 +48,17 @@ int launched(const char *name, const std::string &what) {
 }
 }  // namespace
 
+void *operator new(size_t n) {
+  if (new_fails && in_capture && !in_stub) throw std::bad_alloc();
+  if (void *p = malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+
 extern "C" {
+void stub_new_fails(int on) { new_fails = on != 0; }
+int stub_in_capture() { return in_capture; }
 void stub_reset() {
   std::lock_guard<std::mutex> lock(mu);
   calls.clear();
@@ -117,11 +139,15 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+  Stub here;
   launches += "[ ";
+  in_capture = true;
   return hipSuccess;
 }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) {
+  Stub here;
   launches += "] ";
+  in_capture = false;
   *g = (hipGraph_t)&calls;
   return hipSuccess;
 }

@@ -212,3 +212,21 @@ def test_march_where_its_strips_are_filled(lib, prec, sides, nx, ny, launch):
     assert lib.stub_launches().decode().split() == [launch]
     assert (lib.lbm_get_march_steps(c.h) == 4) == (launch[0] in "mp")
     c.close()
+
+
+def test_no_memory_while_a_batch_is_captured(lib):
+    """A batch whose capture finds no host memory: an error, the capture ended, and the next call works."""
+    lib.lbm_batch_create.argtypes = [ctypes.c_int32, ctypes.c_int32, VP, ctypes.POINTER(VP)]
+    lib.lbm_batch_attach.argtypes = [VP, VP]
+    lib.lbm_batch_step.argtypes = [VP, ctypes.c_int64]
+    lib.lbm_batch_destroy.argtypes = [VP]
+    c, b = Context(lib, 64, 64, ready=True), VP()
+    assert lib.lbm_batch_create(4, 24, None, ctypes.byref(b)) == OK
+    assert lib.lbm_batch_attach(b, c.h) == OK
+    lib.stub_new_fails(1)
+    assert lib.lbm_batch_step(b, 24) != OK
+    lib.stub_new_fails(0)
+    assert not lib.stub_in_capture()
+    assert lib.lbm_batch_step(b, 24) == OK
+    lib.lbm_batch_destroy(b)
+    c.close()

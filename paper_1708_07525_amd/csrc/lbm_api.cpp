@@ -109,8 +109,6 @@ struct lbm_ctx {
   bool owned = false;
   bool ready = false;
   double *host = nullptr;    // pinned: kObsOut observables, then host_export_doubles of exported fields (see pinned_block)
-  int looks = 0;             // looks without it that could have allocated it
-  size_t exported = 0;       // bytes of fields exported without a block of the pool's largest
   bool unstable = false;     // lbm_observables found a non-finite value: lbm_step refuses to go on
   double *scratch = nullptr; // device address of the fixed scratch on this context's device
   lbm_batch *batch = nullptr;   // the batch this context is attached to, if any
@@ -584,26 +582,35 @@ LBM_API lbm_status lbm_derive(const lbm_params *p, lbm_derived *out) {
 // call that exports the fields of a large one (HostExport).  Allocating and freeing it costs 0.03-0.3
 // ms, and the first use of a large block up to 3 ms of page faults, so blocks of three sizes are kept
 // between uses and given back with the last context of the process, and a caller that finds none idle
-// allocates only where it will look again and again (pinned_block, export_fields): a program with one
-// context at a time must not pay for memory that each context uses once.  The contexts' blocks are cut
-// from slabs, as many as the contexts that lived at once needed; of the exports' at most kKept stay idle.
+// goes without until a block would have paid: a program with one context at a time must not pay for
+// memory that each context uses once.  The contexts' blocks are cut from slabs, as many as the
+// contexts that lived at once needed; of the exports' at most kKept stay idle.
 class PinnedPool {
  public:
   static constexpr int kClasses = 3;
-  static constexpr size_t kBytes[kClasses] = {4 << 10, 260 << 10, 16 << 20};
+  static constexpr size_t kBytes[kClasses] = {4 << 10, 260 << 10, 16 << 20};   // no caller needs more
   static constexpr size_t kSlab[kClasses] = {16, 4, 1};       // blocks of one allocation
   static constexpr size_t kKept = 2;
-  // an idle block, or a new one where the caller may allocate; NULL otherwise
-  void *take(size_t bytes, bool allocate) {
+  // What callers have gone without a block of a size, since there are contexts, before one is allocated: looks,
+  // and bytes of exported fields.  A look takes the way through device memory then: 64^2 31 us instead of 21, with
+  // fields 51 instead of 29; a slab costs 15 us to allocate and 28 to free.  512^2 fields take 650 us that way, 430
+  // with a block, but 1700 in the call that allocates it and touches it first; 1024^2 4900 that way (2600 into
+  // touched memory), 2800 in the call that allocates it, so 1024^2 and more have it at once.
+  static constexpr size_t kPrice[kClasses] = {4, 4, 40 << 20};
+  // an idle block, or a new one once the callers' rents reach its price; NULL otherwise.  rent: looks or
+  // bytes that the caller would have used it for, 0 where it must not allocate
+  void *take(size_t bytes, size_t rent) {
     const int k = size_class(bytes);
     std::lock_guard<std::mutex> lock(mu_);
-    if (k < kClasses && !idle_[k].empty()) {
+    if (!idle_[k].empty()) {
       void *p = idle_[k].back();
       idle_[k].pop_back();
       return p;
     }
-    if (!allocate) return nullptr;
-    const bool slab = k < kClasses && kSlab[k] > 1;
+    if (rent == 0) return nullptr;
+    rent_[k] += rent;
+    if (rent_[k] < kPrice[k]) return nullptr;
+    const bool slab = kSlab[k] > 1;
     try {                      // room first, so that nothing below can throw (nor give() for a slab's block)
       if (slab) {
         slabs_.reserve(slabs_.size() + 1);
@@ -614,8 +621,7 @@ class PinnedPool {
       return nullptr;
     }
     void *p = nullptr;
-    if (hipHostMalloc(&p, k < kClasses ? kSlab[k] * kBytes[k] : bytes, hipHostMallocPortable | hipHostMallocCoherent) !=
-        hipSuccess) {
+    if (hipHostMalloc(&p, kSlab[k] * kBytes[k], hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
       (void)hipGetLastError();
       return nullptr;
     }
@@ -629,7 +635,7 @@ class PinnedPool {
     if (!p) return;
     const int k = size_class(bytes);
     std::lock_guard<std::mutex> lock(mu_);
-    if (k < kClasses && (kSlab[k] > 1 || (contexts_ > 0 && idle_[k].size() < kKept))) idle_[k].push_back(p);
+    if (kSlab[k] > 1 || (contexts_ > 0 && idle_[k].size() < kKept)) idle_[k].push_back(p);
     else (void)hipHostFree(p);
   }
   void context(int change) {   // a context more (1) or less (-1)
@@ -640,16 +646,14 @@ class PinnedPool {
     for (void *p : slabs_) (void)hipHostFree(p);
     slabs_.clear();
     for (auto &v : idle_) v.clear();
+    for (size_t &r : rent_) r = 0;
   }
 
  private:
-  static int size_class(size_t bytes) {
-    int k = 0;
-    while (k < kClasses && bytes > kBytes[k]) ++k;
-    return k;
-  }
+  static int size_class(size_t bytes) { return bytes <= kBytes[0] ? 0 : bytes <= kBytes[1] ? 1 : 2; }
   std::mutex mu_;
   std::vector<void *> idle_[kClasses], slabs_;
+  size_t rent_[kClasses] = {};
   int contexts_ = 0;
 };
 static PinnedPool &pinned_pool() {
@@ -665,13 +669,10 @@ static size_t host_export_doubles(const lbm_ctx *c) {
   return n * sizeof(double) <= kHostExport ? n : 0;
 }
 static size_t host_bytes(const lbm_ctx *c) { return (kObsOut + host_export_doubles(c)) * sizeof(double); }
-// c->host, if the context has it: an idle block of the pool's, or from the fourth look on that may
-// allocate a new one.  Without it the results take the way through device memory: 64^2, a look
-// 31 us instead of 21, with fields 51 instead of 29; the block costs 15 us to allocate and 28 to free, so
-// a context of three looks is no slower than without it and one of many loses some 40 us in all.
-constexpr int kLooksBefore = 3;
+// c->host, if the context has it or the pool a block for it (see PinnedPool::take).  Without it the results take
+// the way through device memory.
 static bool pinned_block(lbm_ctx *c, bool allocate) {
-  if (!c->host) c->host = (double *)pinned_pool().take(host_bytes(c), allocate && ++c->looks > kLooksBefore);
+  if (!c->host) c->host = (double *)pinned_pool().take(host_bytes(c), allocate ? 1 : 0);
   return c->host != nullptr;
 }
 
@@ -1159,10 +1160,6 @@ LBM_API lbm_status lbm_step(lbm_ctx *c, int64_t nsteps) {
 // new; the kernel's stores reach 53 GB/s.
 struct HostExport {
   static constexpr size_t kLeast = 2 << 20;  // bytes from which it pays: see export_fields
-  // bytes a context exports through device memory before it has a block allocated where none is idle (a
-  // larger export at once).  512^2: 650 us a call that way, 430 with a block, but 1700 for the call that
-  // allocates it and touches it first; 1024^2 4900 that way (2600 into touched memory), 2800 for the call that allocates it.
-  static constexpr size_t kBytesBefore = 40 << 20;
   static constexpr size_t kChunkBytes = 2 << 20, kSlots = 8;
   static constexpr int kMaxThreads = 8;
   lbm_ctx *c;
@@ -1244,7 +1241,7 @@ static bool device_memory(const void *p) {
 
 // FP64 fields of the current level into host memory: through the context's pinned memory (small
 // lattices, once it has it), through `stage` (5 nx ny doubles of device memory) where it is given, by HostExport
-// (large ones, where its block is idle or the context has exported much), else through device memory of this call.  Measured against a device buffer
+// (large ones, where the pool has a block), else through device memory of this call.  Measured against a device buffer
 // and a copy for every size: 64^2 22 us against 95, 256^2 0.33 ms against 0.65, 512^2 0.50 against
 // 1.32, 1024^2 1.2 against 4.6, 2048^2 3.9 against 16.3; 200^2, below kLeast, takes 0.11 either way.
 static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = nullptr) {
@@ -1277,8 +1274,7 @@ static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = null
       return fail(c, LBM_ENOMEM, "field export");
     }
     const size_t pinned_bytes = x.slots * x.rows * row;
-    c->exported += bytes;
-    x.pinned = (double *)pinned_pool().take(pinned_bytes, c->exported >= HostExport::kBytesBefore);
+    x.pinned = (double *)pinned_pool().take(pinned_bytes, bytes);
     if (x.pinned) {
       he = hipSuccess;
       for (size_t k = 0; k < x.slots && he == hipSuccess; ++k) {

@@ -131,6 +131,21 @@ def test_pinned_memory_is_for_contexts_that_look_often(lib):
     assert lib.stub_calls(b"hipHostFree") == 1
 
 
+def test_contexts_share_what_they_have_gone_without(lib):
+    """The looks and exports of contexts that live together add up: a block is theirs in turn."""
+    c = [Context(lib, 64, 64, ready=True) for _ in range(5)] + [Context(lib, 512, 512, ready=True) for _ in range(4)]
+    for k, x in enumerate(c[:5]):
+        assert x.look() == OK and lib.stub_calls(b"hipHostMalloc") == (k >= 3)
+    for k, x in enumerate(c[5:]):
+        assert x.fields() == OK and lib.stub_calls(b"hipHostMalloc") == 1 + (k >= 3)
+    for x in c:
+        x.close()
+    assert lib.stub_calls(b"hipHostFree") == 2
+    d = Context(lib, 64, 64, ready=True)        # alone again: the count starts anew
+    assert d.look() == OK and lib.stub_calls(b"hipHostMalloc") == 2
+    d.close()
+
+
 def test_static_looks_allocate_nothing(lib):
     c = Context(lib, 64, 64, ready=True)
     lib.stub_reset()
@@ -151,7 +166,7 @@ def test_looks_without_pinned_memory(lib):
 
 
 def test_exports_allocate_their_block_once_it_pays(lib):
-    """512 x 512 fields (10.5 MB): through device memory until the context has exported 40 MB; an idle
+    """512 x 512 fields (10.5 MB): through device memory until 40 MB have been exported; an idle
     block is taken at once."""
     c = Context(lib, 512, 512, ready=True)
     for k in range(4):

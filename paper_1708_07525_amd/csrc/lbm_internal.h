@@ -89,12 +89,12 @@ constexpr TileIndex region_tile(int b, int ntx, uint32_t divisor) {
   const int by = divisor ? (int)(((unsigned long long)(uint32_t)b * divisor) >> 32) : b;
   return TileIndex{b - by * ntx, by};
 }
-// The frame of ntx x nty tiles: the first and the last row (unless periodic in y), then the other
+// The frame of ntx x (last + 1) tiles: the first and the last row (unless periodic in y), then the other
 // rows' first and last tiles.  Two rows need no quotient, which would not be exact for every
 // width that a lattice can have (from 46508 tiles on).
-constexpr TileIndex frame_tile(int b, int ntx, int nty, bool pery) {
+constexpr TileIndex frame_tile(int b, int ntx, int last, bool pery) {
   const int q = b - (pery ? 0 : 2 * ntx);
-  if (q < 0) return b < ntx ? TileIndex{b, 0} : TileIndex{b - ntx, nty - 1};
+  if (q < 0) return b < ntx ? TileIndex{b, 0} : TileIndex{b - ntx, last};
   return TileIndex{q & 1 ? ntx - 1 : 0, (pery ? 0 : 1) + (q >> 1)};
 }
 

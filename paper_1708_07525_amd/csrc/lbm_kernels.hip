@@ -1855,7 +1855,7 @@ struct Region {
 template <typename S, bool NEE, typename RG>
 __global__ void __launch_bounds__(RG::THREADS, RG::THREADS / 256)
     region_kernel(const Desc<typename St<S>::R> *__restrict__ dp, int ntx, uint32_t inv_ntx, int parity, int steps,
-                  int nty) {
+                  int last) {
   using R = typename St<S>::R;
   using FIO = FieldIO<S, CP_RESIDENT>;
   constexpr int RW = RG::RW, PAD = RG::PAD;
@@ -1871,7 +1871,7 @@ __global__ void __launch_bounds__(RG::THREADS, RG::THREADS / 256)
   const uint32_t step = d.counter[cur];
   const int edge = steps - 1, tile = RW - 2 * edge;
   const int b = xcd_remap(blockIdx.x, gridDim.x);
-  const TileIndex at = NEE && nty > 0 ? frame_tile(b, ntx, nty, d.pery != 0) : region_tile(b, ntx, inv_ntx);
+  const TileIndex at = NEE && last > 0 ? frame_tile(b, ntx, last, d.pery != 0) : region_tile(b, ntx, inv_ntx);
   int x0 = at.bx * tile, y0 = at.by * tile;
   if ((x0 | y0) == 0 && threadIdx.x == 0) d.counter[cur ^ 1] = step + (uint32_t)steps;
   if (NEE) {
@@ -2522,7 +2522,7 @@ static int region_t(const void *desc, const void *ddev, int parity, int steps, v
   if (!frame && !tile_divisor_exact((long long)ntx * nty, ntx)) return (int)hipErrorInvalidValue;
   const int grid = !frame ? ntx * nty : (d.pery ? 0 : 2 * ntx) + (d.perx ? 0 : 2 * (nty - (d.pery ? 0 : 2)));
   hipLaunchKernelGGL((region_kernel<S, NEE, RG>), dim3(grid), dim3(RG::THREADS), 0, (hipStream_t)stream,
-                     (const Desc<typename St<S>::R> *)ddev, ntx, tile_divisor(ntx), parity, steps, frame ? nty : 0);
+                     (const Desc<typename St<S>::R> *)ddev, ntx, tile_divisor(ntx), parity, steps, frame ? nty - 1 : 0);
   return (int)hipGetLastError();
 }
 

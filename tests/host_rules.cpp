@@ -16,7 +16,7 @@ extern "C" long long first_wrong_tile(int ntx, int nty, int frame, int pery, int
   }
   const int rows = pery ? 0 : 2 * ntx, grid = rows + (perx ? 0 : 2 * (nty - (pery ? 0 : 2)));
   for (int b = 0; b < grid; ++b) {
-    const TileIndex t = frame_tile(b, ntx, nty, pery != 0);
+    const TileIndex t = frame_tile(b, ntx, nty - 1, pery != 0);
     const int q = b - rows;
     const int by = q < 0 ? (b / ntx ? nty - 1 : 0) : (pery ? 0 : 1) + q / 2;
     const int bx = q < 0 ? b % ntx : (q % 2 ? ntx - 1 : 0);

@@ -174,7 +174,8 @@ lbm_status lbm_observables(struct lbm_ctx *c, lbm_obs *out, double *fields);
  * sums and the staging of the exported fields live in a fixed device array
  * of the library (about 42 MB per device, held until the process ends) instead of the
  * context's memory and memory allocated by the call (results, and fields of up to 256 KB, 80^2
- * nodes, go through pinned memory where the context has it or the library has a block idle).  Limits: at most 16384 rows (partials of
+ * nodes, go through pinned memory where the context has it or the library has a block idle).
+ * Limits: at most 16384 rows (partials of
  * the reduction), and with fields != NULL at most 1048576 nodes (nx*ny); larger lattices are
  * refused with LBM_EINVAL.  Every context on a device shares that device's array and it keeps
  * the last call's contents (every value a call reads is written by the same call first): calls

@@ -108,7 +108,7 @@ struct lbm_ctx {
   char *base = nullptr;      // device memory (arena or owned)
   bool owned = false;
   bool ready = false;
-  double *host = nullptr;    // pinned: kObsOut observables, then host_export_doubles of exported fields (see pinned_block)
+  double *host = nullptr;    // pinned: kObsOut observables, then the fields of a small lattice; or NULL
   bool unstable = false;     // lbm_observables found a non-finite value: lbm_step refuses to go on
   double *scratch = nullptr; // device address of the fixed scratch on this context's device
   lbm_batch *batch = nullptr;   // the batch this context is attached to, if any
@@ -591,11 +591,11 @@ class PinnedPool {
   static constexpr size_t kBytes[kClasses] = {4 << 10, 260 << 10, 16 << 20};   // no caller needs more
   static constexpr size_t kSlab[kClasses] = {16, 4, 1};       // blocks of one allocation
   static constexpr size_t kKept = 2;
-  // What callers have gone without a block of a size, since there are contexts, before one is allocated: looks,
-  // and bytes of exported fields.  A look takes the way through device memory then: 64^2 31 us instead of 21, with
-  // fields 51 instead of 29; a slab costs 15 us to allocate and 28 to free.  512^2 fields take 650 us that way, 430
-  // with a block, but 1700 in the call that allocates it and touches it first; 1024^2 4900 that way (2600 into
-  // touched memory), 2800 in the call that allocates it, so 1024^2 and more have it at once.
+  // What callers have gone without a block of a size, since there are contexts, before one is allocated: looks, and
+  // bytes of exported fields.  A look takes the way through device memory then: 64^2 31 us instead of 21, with fields
+  // 51 instead of 29; a slab costs 15 us to allocate and 28 to free.  512^2 fields take 650 us that way, 430 with a
+  // block, but 1700 in the call that allocates it and touches it first; 1024^2 4900 that way (2600 into touched
+  // memory), 2800 in the call that allocates it, so 1024^2 and more have it at once.
   static constexpr size_t kPrice[kClasses] = {4, 4, 40 << 20};
   // an idle block, or a new one once the callers' rents reach its price; NULL otherwise.  rent: looks or
   // bytes that the caller would have used it for, 0 where it must not allocate
@@ -834,15 +834,13 @@ LBM_API lbm_status lbm_set_fields(lbm_ctx *c, const double *phi, const double *T
   return LBM_OK;
 }
 
-// Time steps per launch: default_spl (three for FP32 and FP64 storage, two for FP16), or the
-// count set by lbm_set_steps_per_launch, lowered to what the cavity allows.
-// With walls through the nodes the two-step kernel places its last tiles against the far
-// walls, so the lattice must hold one tile.  FP16 storage with walls through the nodes always
-// takes one step per launch: the two-step kernel is slower there (2048^2: 41 against 50
-// GLUPS), and its FP16 results would not match the one-step kernel's bit for bit (the
-// compiler fuses multiply-adds of the boundary rule differently in the two kernels, and
-// stochastic rounding turns a last-bit FP32 difference into a different FP16 value now and
-// then).
+// Time steps per launch: default_spl (three for FP32 and FP64 storage, two for FP16), or the count set by
+// lbm_set_steps_per_launch, lowered to what the cavity allows. With walls through the nodes the two-step kernel
+// places its last tiles against the far walls, so the lattice must hold one tile.  FP16 storage with walls through
+// the nodes takes one step per launch, or the region launch (ctx_region): the two-step kernel is slower there
+// (2048^2: 41 against 50 GLUPS), and its FP16 results would not match the one-step kernel's bit for bit (the compiler
+// fuses multiply-adds of the boundary rule differently in the two kernels, and stochastic rounding turns a last-bit
+// FP32 difference into a different FP16 value now and then).
 static bool two_step_ok(const lbm_ctx *c) {
   if (!node_walls(&c->p)) return true;
   if (c->prec == PREC_FP16S) return false;
@@ -886,9 +884,9 @@ static int ctx_strip(const lbm_ctx *c) {
 // node per thread; so the steps per launch are the most that still leave at most one region per CU,
 // on regions of 16^2 nodes (four waves, one per SIMD) up to about 128^2 nodes, else of 22^2.
 // Measured (us per step, region against the tiled launches; FP32 / FP64 / FP16 storage): 64^2
-// 1.56 / 1.92 / 1.67 (16, 6 steps) against 3.41 / 3.95 / 3.69; 100 x 200 1.96 / 2.38 / 1.97 (16, 4)
-// against 3.37 / 5.74 / 3.74; 200^2 2.21 / 2.95 / 2.46 (22, 5) against 3.49 / 4.23 / 3.85; 256^2
-// 2.49 / 3.31 / 2.62 (22, 4) against 3.50 / 4.35 / 3.84; walls through the nodes 100^2 3.43 / 4.02
+// 1.57 / 1.89 / 1.71 (16, 6 steps) against 3.41 / 3.95 / 3.69; 100 x 200 1.95 / 2.35 / 1.98 (16, 4)
+// against 3.37 / 5.74 / 3.74; 200^2 2.22 / 2.93 / 2.47 (22, 5) against 3.49 / 4.23 / 3.85; 256^2
+// 2.47 / 3.30 / 2.63 (22, 4) against 3.50 / 4.35 / 3.84; walls through the nodes 100^2 3.43 / 4.02
 // (16, 5) against 7.50 / 8.93.  Above that several regions share a CU and three steps on regions
 // of 16^2 nodes still win up to 400^2 nodes (384^2 4.00 / 7.11 / 4.27 against 4.66 / 7.94 / 4.77); 512^2 loses.
 // Node walls above 256 regions, against two steps per launch in FP32 and FP64 and one in FP16:
@@ -928,34 +926,33 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
   return nodes <= 160000 ? RegionPlan{16, 3} : RegionPlan{0, 0};
 }
 
-// The march of large lattices (launch_march): steps per launch and rows per chunk, {0, 0} where the
-// tiled launches are faster or ctx_region has a plan.  The chunks are as tall as leaves every wave slot of the chip one, so
-// that all waves run at once and end together; a chunk costs steps - 1 extra rows at either end,
-// so the lattice must be large enough for tall ones.  Measured (GLUPS, march against the tiled
-// launches; rows per chunk in brackets): FP64 4096^2 42.2 (147) against 27.6, 2048^2 39.5 (37)
-// against 30.4, 1280 x 1300 33.8 (16) against 27.8, 1024^2 29.3 (11) against 27.8, 700^2 22.1 (6)
-// against 26.1; FP32 4096^2 78.3 (74) against 72.2, 2048^2 72.2 (19) against 63.8, 1536^2 65.5
-// (11) against 58.5, 1280 x 1300 59.2 (8) against 54.1, 1024^2 48.0 (7) against 58.7.  Hence chunks
-// of at least 9 rows in FP64 (1000^2 below) and 8 in FP32.  Walls through the nodes, where the tiled launch takes
-// two steps: FP32 4096^2 77.0 against 50.9, 2048^2 66.2 against 48.3, 1280 x 1300 53.4 (8) against 42.1,
-// 1150^2 49.6 (6) against 50.6; FP64 4096^2 40.8 against 22.9, 2048^2 38.9 against 23.5, 900^2 25.4
-// (8) against 19.6, 800^2 22.9 (7) against 22.5, 700^2 19.0 (6) against 19.8: from 7 rows in FP64.  FP16 storage (three levels) lost 2% at 2048^2, 12% at
-// 1536^2 and won 12% at 3000^2: not there.
-// Columns: a strip stores 58, a work-group has four strips, so where the strips are no multiple of four waves
-// stay without one, half of them at 233 columns.  "Packed", the strips of neighbouring chunks share
-// work-groups instead; it pays where the last work-group is thin and costs a little where it is nearly
-// full (the chunks are shorter, the rows of a work-group no longer side by side).  Measured (us per step, packed /
-// whole work-groups / tiled launch; rows per packed chunk): FP32 233 x 9000 37.0 / 50.5 / 38.8 (11), 300 x 6007 31.3 /
-// 35.9 / 33.0 (9), 465 x 9000 62.4 / 68.0 / 65.5 (20), 930 x 3000 (17 strips) 43.3 / 42.5 / 44.1; FP64 233 x 30000
-// 204 / 300 / 215 (74), 465 x 9000 116 / 141 / 127 (40), 1000^2 33.0 / 34.7 / 36.2 (9), 1100 x 1600 (19 strips) 49.8 /
-// 51.0 / 54.5; node walls FP32 300 x 6007 40.3 / 44.7 / 47.7 (9), 580 x 3000 32.9 / 33.3 / 43.5, 760 x 2000 - / 29.9 / 34.4
-// (7), FP64 465 x 3000 52.4 / 59.1 / 65.4 (14).  (FP32 between node walls counts the strips between them.)
-// Walls half a spacing outside, where the tile is the faster three-step one: the columns of the
-// strips may also exceed those of the tiles the less the shorter the chunks are.  FP64 233 x 9000 (290
-// columns against 256, 23 rows) 69.8 packed against 66.7 tiled, 300 x 4200 (348 / 320, 13 rows) 43.6 / 42.2, 465 x 3000 (522 / 480,
-// 14 rows) 47.0 / 44.5, 175 x 12000 (232 / 192, 24 rows) 71.6 / 66.3, but 140 x 20000 (174 / 160, 30 rows) 88.7 / 91.4, 200
-// x 5001 (232 / 224, 10 rows) 36.2 / 37.3; FP32 128 x 20000 (174 / 128, 15 rows) 44.7 / 42.5, 175 x 12000 (232 / 192, 12 rows)
-// 38.9 / 39.9.
+// The march of large lattices (launch_march): steps per launch and rows per chunk, {0, 0} where the tiled launches
+// are faster or ctx_region has a plan.  The chunks are as tall as leaves every wave slot of the chip one, so that all
+// waves run at once and end together; a chunk costs steps - 1 extra rows at either end, so the lattice must be large
+// enough for tall ones.  Measured (GLUPS, march against the tiled launches; rows per chunk in brackets): FP64 4096^2
+// 42.2 (147) against 27.6, 2048^2 39.5 (37) against 30.4, 1280 x 1300 33.8 (16) against 27.8, 1024^2 29.3 (11)
+// against 27.8, 700^2 22.1 (6) against 26.1; FP32 4096^2 78.3 (74) against 72.2, 2048^2 72.2 (19) against 63.8,
+// 1536^2 65.5 (11) against 58.5, 1280 x 1300 59.2 (8) against 54.1, 1024^2 48.0 (7) against 58.7.  Hence chunks of at
+// least 9 rows in FP64 (1000^2 below) and 8 in FP32.  Walls through the nodes, where the tiled launch takes two
+// steps: FP32 4096^2 77.0 against 50.9, 2048^2 66.2 against 48.3, 1280 x 1300 53.4 (8) against 42.1, 1150^2 49.6 (6)
+// against 50.6; FP64 4096^2 40.8 against 22.9, 2048^2 38.9 against 23.5, 900^2 25.4 (8) against 19.6, 800^2 22.9 (7)
+// against 22.5, 700^2 19.0 (6) against 19.8: from 7 rows in FP64.  FP16 storage (three levels) lost 2% at 2048^2, 12%
+// at 1536^2 and won 12% at 3000^2: not there.
+// Columns: a strip stores 58, a work-group has four strips, so where the strips are no multiple of four waves stay
+// without one, half of them at 233 columns.  "Packed", the strips of neighbouring chunks share work-groups instead;
+// it pays where the last work-group is thin and costs a little where it is nearly full (the chunks are shorter, the
+// rows of a work-group no longer side by side).  Measured (us per step, packed / whole work-groups / tiled launch;
+// rows per packed chunk): FP32 233 x 9000 37.0 / 50.5 / 38.8 (11), 300 x 6007 31.3 / 35.9 / 33.0 (9), 465 x 9000 62.4
+// / 68.0 / 65.5 (20), 930 x 3000 (17 strips) 43.3 / 42.5 / 44.1; FP64 233 x 30000 204 / 300 / 215 (74), 465 x 9000
+// 116 / 141 / 127 (40), 1000^2 33.0 / 34.7 / 36.2 (9), 1100 x 1600 (19 strips) 49.8 / 51.0 / 54.5; node walls FP32
+// 300 x 6007 40.3 / 44.7 / 47.7 (9), 580 x 3000 32.9 / 33.3 / 43.5, 760 x 2000 - / 29.9 / 34.4 (7), FP64 465 x 3000
+// 52.4 / 59.1 / 65.4 (14).  (FP32 between node walls counts the strips between them.)
+// Walls half a spacing outside, where the tile is the faster three-step one: the columns of the strips may also
+// exceed those of the tiles the less the shorter the chunks are.  FP64 233 x 9000 (290 columns against 256, 23 rows)
+// 69.8 packed against 66.7 tiled, 300 x 4200 (348 / 320, 13 rows) 43.6 / 42.2, 465 x 3000 (522 / 480, 14 rows) 47.0 /
+// 44.5, 175 x 12000 (232 / 192, 24 rows) 71.6 / 66.3, but 140 x 20000 (174 / 160, 30 rows) 88.7 / 91.4, 200 x 5001
+// (232 / 224, 10 rows) 36.2 / 37.3; FP32 128 x 20000 (174 / 128, 15 rows) 44.7 / 42.5, 175 x 12000 (232 / 192, 12
+// rows) 38.9 / 39.9.
 struct MarchPlan {
   int steps, chunk;
   bool packed;
@@ -1164,7 +1161,7 @@ struct HostExport {
   static constexpr int kMaxThreads = 8;
   lbm_ctx *c;
   double *fields, *pinned;
-  size_t slots;                              // slots of the pinned buffer, rows * nx * 5 doubles each: a block of the pool's
+  size_t slots;                              // slots of the pinned buffer, rows * nx * 5 doubles each
   int rows, chunks;
   std::vector<hipEvent_t> written;           // per slot
   std::mutex mu;
@@ -1239,11 +1236,11 @@ static bool device_memory(const void *p) {
   return at.type == hipMemoryTypeDevice;
 }
 
-// FP64 fields of the current level into host memory: through the context's pinned memory (small
-// lattices, once it has it), through `stage` (5 nx ny doubles of device memory) where it is given, by HostExport
-// (large ones, where the pool has a block), else through device memory of this call.  Measured against a device buffer
-// and a copy for every size: 64^2 22 us against 95, 256^2 0.33 ms against 0.65, 512^2 0.50 against
-// 1.32, 1024^2 1.2 against 4.6, 2048^2 3.9 against 16.3; 200^2, below kLeast, takes 0.11 either way.
+// FP64 fields of the current level into host memory: through the context's pinned memory (small lattices, once it has
+// it), through `stage` (5 nx ny doubles of device memory) where it is given, by HostExport (large ones, where the
+// pool has a block), else through device memory of this call.  Measured against a device buffer and a copy for every
+// size: 64^2 22 us against 95, 256^2 0.33 ms against 0.65, 512^2 0.50 against 1.32, 1024^2 1.2 against 4.6, 2048^2
+// 3.9 against 16.3; 200^2, below kLeast, takes 0.11 either way.
 static lbm_status export_fields(lbm_ctx *c, double *fields, double *stage = nullptr) {
   set_parity(c, c->cur);
   const size_t n = 5 * (size_t)c->p.nx * c->p.ny, bytes = n * sizeof(double);
@@ -1333,7 +1330,7 @@ static lbm_status observe(lbm_ctx *c, lbm_obs *out, double *fields, double *part
   }
   if (fs == LBM_OK && fields && !host_fields) fs = export_fields(c, fields, stage);   // waits for the stream
   if (fs != LBM_OK) {
-    (void)hipStreamSynchronize(c->stream);   // nothing writes to c->host (it may go to another context) or copied any more
+    (void)hipStreamSynchronize(c->stream);   // nothing writes to c->host or `copied` any more
     return fs;
   }
   if (!fields || host_fields) {

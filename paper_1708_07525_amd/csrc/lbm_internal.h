@@ -115,10 +115,10 @@ int launch_step2(int prec, const void *desc, const void *ddev, int cp, int parit
 // storage, walls half a spacing outside; fields read from d4, written to d4b; sw as above;
 // rows: tile rows, 8 (64 x 8, FP64 32 x 8) or, FP32 only, 12 (64 x 12); else hipErrorInvalidValue
 int launch_step3(int prec, const void *desc, const void *ddev, int cp, int parity, int sw, int rows, void *stream);
-// march_shape's `steps` time steps per launch on large lattices: waves march up chunks of `chunk` rows
-// of their strips of columns, kMarchWaves to a work-group (packed: also across two chunks); fields read from d4, written to d4b; FP32 and FP64 storage, at least
-// 128 x 16 nodes, with walls through the nodes 128 x 64 and a region launch for the nodes near a
-// wall (else hipErrorInvalidValue)
+// march_shape's `steps` time steps per launch on large lattices: waves march up chunks of `chunk` rows of their
+// strips of columns, kMarchWaves to a work-group (packed: also across two chunks); fields read from d4, written to
+// d4b; FP32 and FP64 storage, at least 128 x 16 nodes, with walls through the nodes 128 x 64 and a region launch for
+// the nodes near a wall (else hipErrorInvalidValue)
 int launch_march(int prec, const void *desc, const void *ddev, int parity, int chunk, bool packed, void *stream);
 constexpr int kMarchWaves = 4;    // strips of a work-group
 constexpr int kMarchWalls = 16;   // columns and rows along a wall through the nodes that the frame's launch takes

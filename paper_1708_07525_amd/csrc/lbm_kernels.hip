@@ -1542,14 +1542,14 @@ __device__ __forceinline__ double from_right(double v) {
 // Walls half a spacing outside: beyond a wall the ghost column's lane (or the ghost row) is given
 // what a bounce-back returns, so that every node pulls alike; the fixed-value and moving-wall
 // terms are added to the pulls (wall_rules).
-// The four waves of a work-group take neighbouring strips and meet at a barrier every row: their
-// rows lie side by side in the same cache lines.  `across` strips are counted per chunk: a multiple of four,
-// which leaves waves without a strip where nstrips is none (they end at once), or nstrips, where
-// a work-group's waves may stand in two chunks (ctx_march has the choice).
-// Bound: FP64 by memory (1.7 GB a launch at 2048^2 in 410 us; its access pattern alone takes 335
-// us; VALU busy 0.51), FP32 by instruction issue (VALU busy 0.79, 408 lane-instructions per node and
-// step).  Measured (2048^2 banded cavity): FP64 39.5-41.6 GLUPS against 30.4
-// for step3_kernel, FP32 72.2-73.4 against 63.8; without the barrier FP32 62.5, with one wave per
+// The four waves of a work-group take neighbouring strips and meet at a barrier every row: their rows lie side by
+// side in the same cache lines.  `across` strips are counted per chunk: a multiple of four, which leaves waves
+// without a strip where nstrips is none (they end at once), or nstrips, where a work-group's waves may stand in two
+// chunks (ctx_march has the choice).
+// Bound: FP64 by memory (1.74 GB a launch at 2048^2 in 403-427 us, 4.1-4.3 TB/s where a plain copy reaches
+// 5.1; VALU busy 0.51), FP32 by instruction issue (VALU busy 0.80, 408 lane-instructions per node and
+// step).  Measured (2048^2 banded cavity): FP64 39.3-41.6 GLUPS against 30.4
+// for step3_kernel, FP32 72.2-73.5 against 63.8; without the barrier FP32 62.5, with one wave per
 // SIMD (all state in registers) FP64 29.6.  FP16 storage (three levels) lost 2% to step2_kernel.
 template <typename S>
 struct March {      // FP32
@@ -1564,13 +1564,14 @@ constexpr int kMarchStrip = 64 - 2 * (March<S>::K - 1);      // columns a strip 
 
 // NEE, walls through the boundary nodes: the march takes the nodes at least kMarchFrame from a wall,
 // whose K levels never meet one, and region_kernel the frame, in a launch before it (2048^2: FP32
-// 29 us of 255, FP64 51 of 440; as a parallel branch of the graph the fork and join of every launch
+// 26 us of 252, FP64 48 of 430; as a parallel branch of the graph the fork and join of every launch
 // cost more, 59.7 GLUPS against 66.2).  2048^2 FP32 66.2 GLUPS against 48.3 for step2_kernel, FP64
 // 38.9 against 23.5.
 constexpr int kFrameRegion = 22;                             // region side of the frame's launch
 template <typename S>
 constexpr int kMarchFrame = kFrameRegion - 2 * (March<S>::K - 1);
-static_assert(kMarchFrame<float> == kMarchWalls && kMarchFrame<double> == kMarchWalls, "the host counts strips between them");
+static_assert(kMarchFrame<float> == kMarchWalls && kMarchFrame<double> == kMarchWalls,
+              "the host counts strips between them");
 
 template <typename R>
 struct MarchRows {
@@ -1811,7 +1812,8 @@ struct NodeWalls {
   }
   __device__ __forceinline__ void apply(R *fd, R *gd, R *hd) const {
     if (okxm & okxp & okym & okyp) return;
-    // (opaque in each step, so that the products stay fused with the additions: see region_kernel)
+    // opaque in each step, so that no product is taken out of a loop over steps: the compiler would no longer
+    // fuse it with the addition it feeds, and the result would differ from the other kernels'
     R v5 = u5, v6 = u6, v7 = u7, v8 = u8;
     asm volatile("" : "+v"(v5), "+v"(v6), "+v"(v7), "+v"(v8));
     const R w5 = R(1.0 / 36.0);
@@ -2091,7 +2093,7 @@ __device__ __forceinline__ void step_tile2d(const Desc<typename St<S>::R> &d, co
 // Each work-group takes a contiguous run of items
 // (neighbouring tiles of one cavity, so shared halo lines stay in its L2), and runs are
 // laid out over the XCDs in bands as in the single-cavity kernel.  Cavities with walls
-// through the boundary nodes are not batched (the host refuses to attach them).
+// through the boundary nodes take the two-step launch only; a step that it leaves is the cavity's own launch.
 template <typename S, int CP>
 __global__ void __launch_bounds__(256) step_batch_kernel(const Desc<typename St<S>::R> *__restrict__ descs,
                                                          const Item *__restrict__ items,
@@ -2429,8 +2431,8 @@ static int step2_t(const void *desc, const void *ddev, int cp, int parity, int s
   const int ntx = (d.nx + W - 1) / W, nty = (d.ny + H - 1) / H;
   const dim3 grid(ntx * nty), block(SH::THREADS);
   if (d.nee) {
-    // FP16 storage with walls through the nodes runs one step per launch; the tiles placed
-    // against the far sides must fit in the lattice
+    // FP16 storage with walls through the nodes has no two-step tile (one step per launch, or the region
+    // launch); the tiles placed against the far sides must fit in the lattice
     if constexpr (__is_same(S, _Float16)) {
       return (int)hipErrorInvalidValue;
     } else {
@@ -2677,7 +2679,7 @@ int launch_step2_batch_nee(int prec, int cp, const void *descs, const Item *item
   switch (prec) {
     case PREC_FP64: batch2_nee_t<double>(cp, descs, items, range, grid, parity, s); break;
     case PREC_FP32: batch2_nee_t<float>(cp, descs, items, range, grid, parity, s); break;
-    default: return (int)hipErrorInvalidValue;   // FP16 storage: node walls take one step per launch
+    default: return (int)hipErrorInvalidValue;   // FP16 storage: node walls are not batched
   }
   return (int)hipGetLastError();
 }

@@ -952,7 +952,16 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
 // 69.8 packed against 66.7 tiled, 300 x 4200 (348 / 320, 13 rows) 43.6 / 42.2, 465 x 3000 (522 / 480, 14 rows) 47.0 /
 // 44.5, 175 x 12000 (232 / 192, 24 rows) 71.6 / 66.3, but 140 x 20000 (174 / 160, 30 rows) 88.7 / 91.4, 200 x 5001
 // (232 / 224, 10 rows) 36.2 / 37.3; FP32 128 x 20000 (174 / 128, 15 rows) 44.7 / 42.5, 175 x 12000 (232 / 192, 12
-// rows) 38.9 / 39.9.
+// rows) 38.9 / 39.9.  FP32 lattices of three strips keep whole work-groups (150 x 40000 90.7 against 93.2 packed) and
+// march from chunks whose columns make 8.5 full rows: 140 x 8000 (8 rows of 174 columns) 23.8 / 19.9, 140 x 11000
+// 30.5 / 32.6, 172 x 9000 27.4 / 28.7.
+// Rows: very wide lattices fill the chip once with few chunks or with one, part of it then idle (FP64 64000 x 200:
+// 276 work-groups on 512 slots), or more than once.  Where a quarter idles they take the number of chunks whose rows,
+// counted with the extra ones of every chunk, are least in turn, if a tenth fewer: FP64 64000 x 200 307 us per step with
+// 5 chunks, 475 with one, tiled 390; 44000 x 200 203 / 245 / 257; FP32 125000 x 100 157 / 185 / 183.  Few rows
+// between walls through the nodes: the frame takes 32 of them (FP64 20000 x 100 80.0 us counted without them, 90.5
+// with, tiled 86.0), where that leaves chunks of least height; from half of them in FP64 the tiles win (64000 x 64
+// 198 against 161, x 96 235 / 246).
 struct MarchPlan {
   int steps, chunk;
   bool packed;
@@ -966,21 +975,33 @@ static MarchPlan ctx_march(const lbm_ctx *c) {
   auto strips_of = [&](int nx) { return (nx + columns - 1) / columns; };
   auto fill = [](int strips) { return (double)strips / ((strips + kMarchWaves - 1) / kMarchWaves * kMarchWaves); };
   const int strips = strips_of(c->p.nx);
-  bool packed = fill(strips) < (fp64 ? 0.92 : 0.88);
+  bool packed = fill(strips) < (fp64 ? 0.92 : 0.88) && (fp64 || strips > kMarchWaves);
   if (nee && !fp64) {
     const int inner = strips_of(c->p.nx - (c->p.side[LEFT] == SIDE_PERIODIC ? 0 : 2 * kMarchWalls));
     packed = inner > kMarchWaves && fill(inner) < 0.8;
   }
-  const int waves = kComputeUnits * per_cu * kMarchWaves;
-  const int chunks = std::max(1, waves / (packed ? strips : (strips + kMarchWaves - 1) / kMarchWaves * kMarchWaves));
-  const int chunk = (c->p.ny + chunks - 1) / chunks;
-  const int least = !fp64 ? 8 : nee ? 7 : 9;
-  if (chunk < least || c->p.ny < (nee ? 64 : 16)) return none;
+  const int64_t slots = (int64_t)kComputeUnits * per_cu * kMarchWaves;
+  const int64_t across = packed ? strips : (strips + kMarchWaves - 1) / kMarchWaves * kMarchWaves;
+  // (few rows between walls through the nodes: those that the frame leaves)
+  const int rows = c->p.ny - (nee && c->p.ny < 256 && c->p.side[BOTTOM] != SIDE_PERIODIC ? 2 * kMarchWalls : 0);
+  int chunks = (int)std::max<int64_t>(1, slots / across);
+  auto rows_in_turn = [&](int n) { return (across * n + slots - 1) / slots * ((rows + n - 1) / n + 2 * (steps - 1)); };
+  if (across * chunks < slots * 3 / 4 || across > slots) {
+    int best = chunks;
+    for (int n = chunks + 1; n <= 16; ++n)
+      if (rows_in_turn(n) < rows_in_turn(best)) best = n;
+    if (10 * rows_in_turn(best) < 9 * rows_in_turn(chunks)) chunks = best;
+  }
+  int chunk = (rows + chunks - 1) / chunks;
+  const int least = fp64 ? (nee ? 7 : 9) : 8;
+  if (chunk < least) chunk = (c->p.ny + chunks - 1) / chunks;   // (fewer chunks than slots, then)
+  if (chunk < least || c->p.ny < (nee ? (fp64 ? 96 : 64) : 16)) return none;
+  if (!nee && !fp64 && strips < kMarchWaves && chunk * (double)c->p.nx < 8.5 * strips * columns) return none;
   if (!nee) {
     int w = 0, h = 0;
     two_step_tile_shape(c->prec, &w, &h);   // (as wide as the three-step tile)
     const int tiles = (c->p.nx + w - 1) / w * w;
-    if (tiles < strips * columns * (1.0 - chunk / (fp64 ? 200.0 : 60.0))) return none;
+    if (tiles < strips * columns * std::max(0.75, 1.0 - chunk / (fp64 ? 200.0 : 60.0))) return none;
   }
   return MarchPlan{steps, chunk, packed};
 }

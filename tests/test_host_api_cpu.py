@@ -211,16 +211,21 @@ HALF = ("hot", "cold", "adiabatic", "adiabatic")
 
 
 @pytest.mark.parametrize("prec,sides,nx,ny,launch", [
-    ("fp32", HALF, 2048, 2048, "march/19"), ("fp64", HALF, 2048, 2048, "march/37"), ("fp32", NODE, 2048, 2048, "march/19"),
+    ("fp32", HALF, 2048, 2048, "march/19"), ("fp64", HALF, 2048, 2048, "march/37"),
+    ("fp32", NODE, 2048, 2048, "march/19"),
     ("fp32", HALF, 128, 8000, "step3"), ("fp32", HALF, 128, 20000, "step3"), ("fp32", HALF, 233, 4200, "step3"),
     ("fp32", HALF, 233, 9000, "packed/11"), ("fp32", HALF, 300, 4200, "step3"), ("fp32", HALF, 300, 6007, "packed/9"),
     ("fp32", HALF, 465, 3000, "step3"), ("fp32", HALF, 1100, 1600, "march/8"), ("fp32", HALF, 180, 30000, "march/30"),
     ("fp64", HALF, 128, 20000, "step3"), ("fp64", HALF, 233, 9000, "step3"), ("fp64", HALF, 300, 4200, "step3"),
     ("fp64", HALF, 465, 3000, "step3"), ("fp64", HALF, 233, 30000, "packed/74"), ("fp64", HALF, 1000, 1000, "packed/9"),
     ("fp64", HALF, 200, 5001, "march/10"), ("fp32", NODE, 300, 4200, "step2"), ("fp32", NODE, 300, 6007, "packed/9"),
-    ("fp32", NODE, 760, 2000, "march/8"), ("fp64", NODE, 465, 3000, "packed/14")])
+    ("fp32", NODE, 760, 2000, "march/8"), ("fp64", NODE, 465, 3000, "packed/14"),
+    ("fp32", HALF, 140, 8000, "step3"), ("fp32", HALF, 140, 11000, "march/11"), ("fp64", HALF, 64000, 200, "march/40"),
+    ("fp32", HALF, 125000, 100, "march/20"), ("fp64", HALF, 100000, 128, "march/128"),
+    ("fp64", NODE, 20000, 100, "march/14"), ("fp32", NODE, 20000, 100, "march/10"), ("fp64", NODE, 64000, 64, "step2")])
 def test_march_where_its_strips_are_filled(lib, prec, sides, nx, ny, launch):
-    """Lattices of few columns: the march only where its strips and work-groups hold columns."""
+    """Lattices of few columns or few rows: the march only where its strips, its work-groups and the chip's
+    slots are filled."""
     c = Context(lib, nx, ny, prec, ready=True, sides=sides, Bi_T=1.0, Bi_C=1.0)
     lib.stub_reset()
     assert lib.lbm_step(c.h, 4 if launch[0] in "mp" else int(launch[-1])) == OK

@@ -576,10 +576,12 @@ def test_march_with_node_walls_matches_one_step(prec, nx, ny, walls):
 @pytest.mark.parametrize("prec,nx,ny,walls", [
     ("fp32", 233, 9001, "half_way"), ("fp32", 580, 3001, "periodic_x"), ("fp32", 465, 4003, "periodic_y"),
     ("fp64", 1000, 1003, "half_way"), ("fp64", 520, 3501, "periodic_x"), ("fp64", 580, 2000, "periodic_y"),
-    ("fp32", 300, 6007, "nee"), ("fp32", 520, 3507, "nee_x"), ("fp64", 300, 2501, "nee"), ("fp64", 140, 8001, "nee_y")])
+    ("fp32", 300, 6007, "nee"), ("fp32", 520, 3507, "nee_x"), ("fp64", 300, 2501, "nee"), ("fp64", 140, 8001, "nee_y"),
+    ("fp64", 64001, 64, "half_way"), ("fp64", 20003, 100, "nee"), ("fp32", 20003, 97, "nee_y")])
 def test_march_across_chunks_matches_one_step(prec, nx, ny, walls):
     """The march with work-groups that hold strips of two chunks (lattices whose strips do not fill
-    work-groups of four) against one step per launch, bit for bit; the last chunk is shorter."""
+    work-groups of four), and of very wide lattices, in more chunks than the chip holds at once, against
+    one step per launch, bit for bit; the last chunk is shorter."""
     Solver = _solver()
     sides = {"half_way": ("hot", "cold", "adiabatic", "hot"), "periodic_x": ("periodic", "periodic", "cold", "adiabatic"),
              "periodic_y": ("adiabatic", "cold", "periodic", "periodic"),

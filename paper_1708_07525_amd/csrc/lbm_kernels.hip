@@ -1934,10 +1934,11 @@ __global__ void __launch_bounds__(RG::THREADS, RG::THREADS / 256)
   auto P = [](int i) { return NEE ? i : lp(i); };              // LDS plane of population i
   bool active = live;
   for (int s = 0;; ++s) {
-    // between node walls opaque, so that the collision's products of them are formed in every step: kept over the
-    // loop beside the boundary rule's they cost registers (FP32 384^2 7.16 us per step instead of 5.94).  Without the
-    // rule they are kept (64^2 FP32 1.64 to 1.57 us per step, 256^2 2.56 to 2.47, FP64 3.42 to 3.30)
-    if (NEE) asm volatile("" : "+v"(phi), "+v"(ip), "+v"(pa), "+v"(pb));
+    // opaque between node walls, so that the collision's products of them are formed in every step: kept over the
+    // loop beside the boundary rule's they cost registers (FP32 384^2 7.16 us per step instead of 5.94); and in FP32
+    // regions of 16^2, of which a CU holds several (400^2 4.76 instead of 4.61, 64^2 1.57 instead of 1.64).
+    // Elsewhere they are kept (64^2 FP64 1.96 to 1.89 us per step, 256^2 FP32 2.56 to 2.47, FP64 3.42 to 3.30)
+    if (NEE || (__is_same(S, float) && RW == 16)) asm volatile("" : "+v"(phi), "+v"(ip), "+v"(pa), "+v"(pb));
     if (active) collide<R, kScaled<S>>(q, phi, ip, pa, pb, fd, gd, hd, prev);
     if (s == edge) break;
     S(*pop)[RG::SLOTS] = lds[s & 1];

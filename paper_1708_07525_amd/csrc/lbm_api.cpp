@@ -884,16 +884,26 @@ static int ctx_strip(const lbm_ctx *c) {
 // node per thread; so the steps per launch are the most that still leave at most one region per CU,
 // on regions of 16^2 nodes (four waves, one per SIMD) up to about 128^2 nodes, else of 22^2.
 // Measured (us per step, region against the tiled launches; FP32 / FP64 / FP16 storage): 64^2
-// 1.57 / 1.89 / 1.71 (16, 6 steps) against 3.41 / 3.95 / 3.69; 100 x 200 1.95 / 2.35 / 1.98 (16, 4)
-// against 3.37 / 5.74 / 3.74; 200^2 2.22 / 2.93 / 2.47 (22, 5) against 3.49 / 4.23 / 3.85; 256^2
-// 2.47 / 3.30 / 2.63 (22, 4) against 3.50 / 4.35 / 3.84; walls through the nodes 100^2 3.43 / 4.02
+// 1.63 / 1.90 / 1.71 (16, 6 steps) against 3.41 / 3.95 / 3.69; 100 x 200 2.01 / 2.38 / 1.99 (16, 4)
+// against 3.37 / 5.74 / 3.74; 200^2 2.25 / 2.97 / 2.50 (22, 5) against 3.49 / 4.23 / 3.85; 256^2
+// 2.50 / 3.35 / 2.67 (22, 4) against 3.50 / 4.35 / 3.84; walls through the nodes 100^2 3.43 / 4.02
 // (16, 5) against 7.50 / 8.93.  Above that several regions share a CU and three steps on regions
-// of 16^2 nodes still win up to 400^2 nodes (384^2 4.00 / 7.11 / 4.27 against 4.66 / 7.94 / 4.77); 512^2 loses.
+// of 16^2 nodes still win up to 400^2 nodes (384^2 4.00 / 6.80 / 4.27 against 4.66 / 7.14 / 4.77); 512^2 loses.
 // Node walls above 256 regions, against two steps per launch in FP32 and FP64 and one in FP16:
 // FP32 22^2 with 3 steps 512^2 8.56 against 9.61, 768^2 13.8 against 15.3, 1024^2 20.7 against 21.6,
 // 1200^2 30.7 against 30.5; FP64 22^2 with 4 steps 320^2 9.6 against 10.5, but 380 x 400 12.8 against
 // 11.8 (a region fills a CU: the third round of them starts): not there; FP16 16^2 with 3 steps (never 22^2: 256^2 4.8 either way, 200^2 5.2 against 4.9) 256^2
 // 4.8 against 17.5, 400^2 7.3 against 8.7, 768^2 16.8 against 27.3, 900^2 20.0 against 19.4.
+// Several regions per CU on lattices of few rows or columns: a region of 16^2 stores 12^2 nodes (22^2 18^2), so low
+// or narrow lattices take many more regions than the tiles' 64 x 8 (FP64 32 x 8) nodes.  The tiled launches are taken
+// where the regions are too many for the tiles: FP32 and FP16 above 300 + 3.6 per tile (FP32 12000 x 13: 2000
+// regions, 376 tiles, 6.0 us per step against 4.8; 50000 x 3 8.1 / 5.9; but 8000 x 20 1334 / 375, 4.9 / 5.0), FP16
+// also where a low lattice has more than four per CU (8000 x 20 5.6 / 5.0); FP64 where they take more rounds of the
+// chip than the tiles and one (400^2 1156 / 650, 7.9 / 7.3; 340^2 841 / 473, 6.5 / 5.9; 12000 x 13 10.6 / 7.3; but
+// 380^2 1024 / 576, 6.8 / 7.1; 100 x 1600 1206 / 800, 7.9 / 10.1).  Node walls, FP32 above 1.7 to 2 per tile (20000 x
+// 24 2224 / 939, 17.3 / 11.8; 128 x 4000 1784 / 1000, 16.4 / 15.3; but 6000 x 30 668 / 376, 8.0 / 8.3); FP16 low
+// lattices whose one-step launch has 64-node tiles (20000 x 24 16.1 / 11.5, 3000 x 200 16.4 / 14.5; but 2000 x 200,
+// on 256-node tiles, 12.8 / 21.3).
 // Any launch choice of the caller (steps per launch, cache policy, tile, tile order, tile rows)
 // is kept: the region launch is part of the defaults only.
 struct RegionPlan {
@@ -916,14 +926,25 @@ static RegionPlan ctx_region(const lbm_ctx *c) {
   if (fits(16))
     for (int k = 6; k >= 4; --k)
       if (tiles(16, k) <= kRegionTiles) return {16, k};
-  const int64_t nodes = (int64_t)nx * ny;
-  if (nee && c->prec == PREC_FP16S) return fits(16) && nodes <= 800000 ? RegionPlan{16, 3} : RegionPlan{0, 0};
+  const int64_t nodes = (int64_t)nx * ny, regions = tiles(16, 3), regions22 = tiles(22, 3);
+  int w = 0, h = 0;
+  two_step_tile_shape(c->prec, &w, &h);
+  const int64_t tiled = (int64_t)((nx + w - 1) / w) * ((ny + h - 1) / h);   // tiles of the multi-step launch
+  if (nee && c->prec == PREC_FP16S) {
+    const bool low = nx >= 4 * (int64_t)ny && regions > (nx >= 8 * (int64_t)ny ? 700 : 2000) && default_tile(&c->p).tx == 64;
+    return fits(16) && nodes <= 800000 && !low ? RegionPlan{16, 3} : RegionPlan{0, 0};
+  }
   if (fits(22))
     for (int k = 5; k >= 4; --k)
       if (tiles(22, k) <= kRegionTiles) return {22, k};
-  if (nee)
-    return fits(22) && c->prec == PREC_FP32 && nodes <= 1000000 ? RegionPlan{22, 3} : RegionPlan{0, 0};
-  return nodes <= 160000 ? RegionPlan{16, 3} : RegionPlan{0, 0};
+  if (nee) {
+    const bool low = two_step_ok(c) && regions22 > 512 && regions22 > (regions22 > 700 ? 1.7 : 2.0) * tiled;
+    return fits(22) && c->prec == PREC_FP32 && nodes <= 1000000 && !low ? RegionPlan{22, 3} : RegionPlan{0, 0};
+  }
+  const bool low = c->prec == PREC_FP64 ? regions > kRegionTiles * ((tiled + 255) / 256 + 1)
+                                        : regions > 300 + tiled * 36 / 10 ||
+                                              (c->prec == PREC_FP16S && nx >= 8 * (int64_t)ny && regions > 1024);
+  return nodes <= 160000 && !low ? RegionPlan{16, 3} : RegionPlan{0, 0};
 }
 
 // The march of large lattices (launch_march): steps per launch and rows per chunk, {0, 0} where the tiled launches

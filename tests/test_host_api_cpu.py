@@ -234,6 +234,21 @@ def test_march_where_its_strips_are_filled(lib, prec, sides, nx, ny, launch):
     c.close()
 
 
+@pytest.mark.parametrize("prec,sides,nx,ny,steps", [
+    ("fp32", HALF, 384, 384, 3), ("fp32", HALF, 400, 400, 3), ("fp32", HALF, 8000, 20, 3), ("fp32", HALF, 12000, 13, 0),
+    ("fp32", HALF, 50000, 3, 0), ("fp32", HALF, 3, 50000, 3), ("fp32", HALF, 4000, 13, 4), ("fp32", HALF, 10000, 5, 3),
+    ("fp16s", HALF, 8000, 20, 0), ("fp16s", HALF, 64, 2500, 3), ("fp16s", HALF, 400, 400, 3), ("fp64", HALF, 400, 400, 0),
+    ("fp64", HALF, 380, 380, 3), ("fp64", HALF, 340, 340, 0), ("fp64", HALF, 100, 1600, 3), ("fp64", HALF, 12000, 13, 0),
+    ("fp32", NODE, 20000, 24, 0), ("fp32", NODE, 24, 20000, 3), ("fp32", NODE, 6000, 30, 3), ("fp32", NODE, 700, 690, 3),
+    ("fp32", NODE, 128, 4000, 0), ("fp16s", NODE, 20000, 24, 0), ("fp16s", NODE, 2000, 200, 3),
+    ("fp16s", NODE, 3000, 24, 3)])
+def test_region_launch_where_its_regions_are_filled(lib, prec, sides, nx, ny, steps):
+    """Low and narrow lattices: several regions per CU only where they are not many more than the tiles."""
+    c = Context(lib, nx, ny, prec, ready=True, sides=sides, Bi_T=1.0, Bi_C=1.0)
+    assert lib.lbm_get_region_steps(c.h) == steps
+    c.close()
+
+
 def test_no_memory_while_a_batch_is_captured(lib):
     """A batch whose capture finds no host memory: an error, the capture ended, and the next call works."""
     lib.lbm_batch_create.argtypes = [ctypes.c_int32, ctypes.c_int32, VP, ctypes.POINTER(VP)]
